@@ -367,7 +367,7 @@ def describe(name: str, pairs) -> str:
             "all pairs extracted and matched in one step")
 
 
-MATCHER_SOURCES = ("match_fft.hip", "dft.hpp", "epilogue.hpp", "kernels.hpp", "window.hpp", "split_plan.hpp",
+MATCHER_SOURCES = ("match_fft.hip", "match_lane.hpp", "dft.hpp", "epilogue.hpp", "kernels.hpp", "window.hpp", "split_plan.hpp",
                    "abi.hip")
 
 
@@ -612,7 +612,7 @@ def main():
         roof = dict(hbm)
         roof["bound"] = "hbm"
         Ps = sorted(set(plans.values()))
-        kernel = ("match_fft_kernel<P=" + ",".join(str(P) for P in Ps) + "> + split_reduce_kernel, one "
+        kernel = ("match kernels of FFT side " + ",".join(str(P) for P in Ps) + " + split_reduce_kernel, one "
                   "match_batch call")
     key = f"{args.workload}:{path}" + ("" if desc == "cfog" else f":{desc}")
     traffic = traffic_record(key) if path != "mfma" else None

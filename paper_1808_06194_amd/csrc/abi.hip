@@ -147,6 +147,13 @@ const cfog::FftPlan* select_plan(cfog_ctx* ctx, int N, int r, int m) {
   return cfog::choose_fft_plan(N, r);
 }
 
+// The plan a job runs with: its size's, but on images too wide for the lane
+// layout's offsets the one that has none.
+const cfog::FftPlan* job_plan(cfog_ctx* ctx, const cfog_job& j, int m) {
+  const cfog::FftPlan* p = select_plan(ctx, j.N, j.r, m);
+  return p && p->lane && std::max(j.wA, j.wB) > cfog::kLaneMaxWidth ? cfog::wide_plan() : p;
+}
+
 // ------------------------------------------------------------- batch plans
 
 // Channel split of the last round of a launch (split_plan.hpp).
@@ -168,14 +175,14 @@ struct PlainLayout {
 
 PlainLayout plain_layout(cfog_ctx* ctx, const cfog_job& j, int m, bool split_ok) {
   PlainLayout L;
-  L.p = select_plan(ctx, j.N, j.r, m);
+  L.p = job_plan(ctx, j, m);
   if (!L.p) return L;
   const int S = cfog::plan_slots(L.p, ctx->num_cus);
   size_t sb = 0;
   L.sp = split_ok ? plan_split(L.p, j.n_cps, S, m, j.N, j.N + 2 * j.r, 2 * j.r + 1, &sb)
                   : cfog::SplitArgs{j.n_cps, 1, 0, nullptr};
   const int items = cfog::split_items(j.n_cps, L.sp);
-  L.blocks = items;
+  L.blocks = L.p->lane ? std::min(items, S) : items;
   L.split_off = 0;
   L.total = sb;
   return L;
@@ -203,7 +210,7 @@ int build_batch(cfog_ctx* ctx, const cfog_job* jobs, int n_jobs, int m, int obj,
   for (int i = 0; i < n_jobs; ++i) {
     int rc = validate_job(jobs[i], m);
     if (rc != CFOG_OK) return rc;
-    plans[i] = select_plan(ctx, jobs[i].N, jobs[i].r, m);
+    plans[i] = job_plan(ctx, jobs[i], m);
     if (!plans[i]) return CFOG_EUNSUPPORTED;
   }
   B.jobs.resize(n_jobs);
@@ -211,7 +218,7 @@ int build_batch(cfog_ctx* ctx, const cfog_job* jobs, int n_jobs, int m, int obj,
   int nplans = 0;
   const cfog::FftPlan* all = cfog::fft_plans(&nplans);
   std::vector<size_t> split_bytes;
-  for (int p = 0; p < nplans; ++p) {
+  for (int p = 0; p <= nplans; ++p) {  // the last: wide_plan()
     Bucket b{&all[p], (int)B.tasks.size(), 0, 0, cfog::SplitArgs{0, 1, 0, nullptr}, 0};
     int Nmax = 0, Wmax = 0, Kmax = 0;
     for (int i = 0; i < n_jobs; ++i)
@@ -344,6 +351,7 @@ int autotune(cfog_ctx* ctx, const cfog_job& j, int m, hipStream_t st) {
   const cfog::FftPlan* all = cfog::fft_plans(&nplans);
   const cfog::FftPlan* first = cfog::choose_fft_plan(j.N, j.r);
   if (!first) return CFOG_EUNSUPPORTED;
+  if (std::max(j.wA, j.wB) > cfog::kLaneMaxWidth) return CFOG_OK;  // job_plan leaves no choice
   std::vector<const cfog::FftPlan*> cands;
   for (int p = 0; p < nplans && cands.size() < 3; ++p)
     if (all[p].P >= first->P && cfog::plan_fits(&all[p], j.N, j.r)) cands.push_back(&all[p]);

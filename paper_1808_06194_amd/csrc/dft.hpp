@@ -242,4 +242,134 @@ template <int DIR> struct Dft<24, DIR> : DftPfa<8, 3, DIR> {};
 template <int R, int DIR>
 CFOG_HD void dft(float2* v) { Dft<R, DIR>::run(v); }
 
+// rdft<R>(x, X): the forward transform of R real values, X[k] for k = 0..R/2
+// (the others are their conjugates): X[0], and X[R/2] for even R, are real.
+template <int R> struct RDft;
+
+template <> struct RDft<2> {
+  CFOG_HD static void run(const float* x, float2* X) {
+    X[0] = make_float2(x[0] + x[1], 0.f);
+    X[1] = make_float2(x[0] - x[1], 0.f);
+  }
+};
+
+template <> struct RDft<3> {
+  CFOG_HD static void run(const float* x, float2* X) {
+    constexpr float s3 = 0.866025403784438646763723170752936183f;
+    const float t = x[1] + x[2];
+    X[0] = make_float2(x[0] + t, 0.f);
+    X[1] = make_float2(fmaf(-0.5f, t, x[0]), s3 * (x[2] - x[1]));
+  }
+};
+
+template <> struct RDft<4> {
+  CFOG_HD static void run(const float* x, float2* X) {
+    const float s02 = x[0] + x[2], s13 = x[1] + x[3];
+    X[0] = make_float2(s02 + s13, 0.f);
+    X[1] = make_float2(x[0] - x[2], x[3] - x[1]);
+    X[2] = make_float2(s02 - s13, 0.f);
+  }
+};
+
+template <> struct RDft<5> {
+  CFOG_HD static void run(const float* x, float2* X) {
+    constexpr float c1 = (float)cos2pi(1, 5), c2 = (float)cos2pi(2, 5);
+    constexpr float s1 = (float)sin2pi(1, 5), s2 = (float)sin2pi(2, 5);
+    const float t1 = x[1] + x[4], t2 = x[2] + x[3], d1 = x[4] - x[1], d2 = x[3] - x[2];
+    X[0] = make_float2(x[0] + (t1 + t2), 0.f);
+    X[1] = make_float2(fmaf(c2, t2, fmaf(c1, t1, x[0])), fmaf(s2, d2, s1 * d1));
+    X[2] = make_float2(fmaf(c1, t2, fmaf(c2, t1, x[0])), fmaf(-s1, d2, s2 * d1));
+  }
+};
+
+// X[k] of R from its value at k (any residue): the conjugate fills R - k.
+template <int R, int K>
+CFOG_HD void rdft_put(float2* X, float2 v) {
+  constexpr int k = K % R;
+  if constexpr (2 * k <= R) X[k] = v;
+  else X[R - k] = make_float2(v.x, -v.y);
+}
+
+// Composite R = A * B as DftSplit: real inner transforms, whose k1 = 0 values
+// are real and go through a real outer transform.
+template <int A, int B>
+struct RDftSplit {
+  CFOG_HD static void run(const float* x, float2* X) {
+    constexpr int R = A * B, H = A / 2;
+    float2 y[B][H + 1];
+    static_for<0, B>([&](auto bI) {
+      constexpr int b = decltype(bI)::value;
+      float t[A];
+      static_for<0, A>([&](auto aI) { constexpr int a = decltype(aI)::value; t[a] = x[B * a + b]; });
+      RDft<A>::run(t, y[b]);
+    });
+    float r[B];
+    float2 q[B / 2 + 1];
+    static_for<0, B>([&](auto bI) { constexpr int b = decltype(bI)::value; r[b] = y[b][0].x; });
+    RDft<B>::run(r, q);
+    static_for<0, B / 2 + 1>([&](auto kI) { constexpr int k2 = decltype(kI)::value; rdft_put<R, A * k2>(X, q[k2]); });
+    static_for<1, H + 1>([&](auto kI) {
+      constexpr int k1 = decltype(kI)::value;
+      float2 t[B];
+      static_for<0, B>([&](auto bI) {
+        constexpr int b = decltype(bI)::value;
+        t[b] = twiddle<b * k1, R, -1>(y[b][k1]);
+      });
+      Dft<B, -1>::run(t);
+      static_for<0, B>([&](auto k2I) { constexpr int k2 = decltype(k2I)::value; rdft_put<R, k1 + A * k2>(X, t[k2]); });
+    });
+  }
+};
+
+// Coprime R = A * B as DftPfa: no twiddles, so k1 = A/2 stays real too.
+template <int A, int B>
+struct RDftPfa {
+  CFOG_HD static void run(const float* x, float2* X) {
+    constexpr int R = A * B, H = A / 2;
+    constexpr int tA = inv_mod(B % A, A), tB = inv_mod(A % B, B);
+    float2 y[B][H + 1];
+    static_for<0, B>([&](auto bI) {
+      constexpr int b = decltype(bI)::value;
+      float t[A];
+      static_for<0, A>([&](auto aI) { constexpr int a = decltype(aI)::value; t[a] = x[(B * a + A * b) % R]; });
+      RDft<A>::run(t, y[b]);
+    });
+    static_for<0, H + 1>([&](auto kI) {
+      constexpr int k1 = decltype(kI)::value;
+      if constexpr (k1 == 0 || 2 * k1 == A) {
+        float r[B];
+        float2 q[B / 2 + 1];
+        static_for<0, B>([&](auto bI) { constexpr int b = decltype(bI)::value; r[b] = y[b][k1].x; });
+        RDft<B>::run(r, q);
+        static_for<0, B / 2 + 1>([&](auto k2I) {
+          constexpr int k2 = decltype(k2I)::value;
+          rdft_put<R, B * tA * k1 + A * tB * k2>(X, q[k2]);
+        });
+      } else {
+        float2 t[B];
+        static_for<0, B>([&](auto bI) { constexpr int b = decltype(bI)::value; t[b] = y[b][k1]; });
+        Dft<B, -1>::run(t);
+        static_for<0, B>([&](auto k2I) {
+          constexpr int k2 = decltype(k2I)::value;
+          rdft_put<R, B * tA * k1 + A * tB * k2>(X, t[k2]);
+        });
+      }
+    });
+  }
+};
+
+template <> struct RDft<6> : RDftPfa<2, 3> {};
+template <> struct RDft<8> : RDftSplit<4, 2> {};
+template <> struct RDft<9> : RDftSplit<3, 3> {};
+template <> struct RDft<10> : RDftPfa<2, 5> {};
+template <> struct RDft<12> : RDftPfa<4, 3> {};
+template <> struct RDft<15> : RDftPfa<3, 5> {};
+template <> struct RDft<16> : RDftSplit<4, 4> {};
+template <> struct RDft<18> : RDftPfa<2, 9> {};
+template <> struct RDft<20> : RDftPfa<4, 5> {};
+template <> struct RDft<24> : RDftPfa<8, 3> {};
+
+template <int R>
+CFOG_HD void rdft(const float* x, float2* X) { RDft<R>::run(x, X); }
+
 }  // namespace cfog

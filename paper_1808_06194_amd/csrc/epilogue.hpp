@@ -67,8 +67,8 @@ __device__ __forceinline__ double parabola_vertex(double a, double b, double c) 
   return den > 0.0 ? 0.5 * (a - c) / den : 0.0;
 }
 
-// Writes the result of control point cpi of job jd from the correlation
-// Cs[u_y * K + u_x] (LDS, all K*K values visible to the workgroup):
+// Writes the result of control point cpi of job jd from the correlation, read
+// as corr(u_y * K + u_x, u_y, u_x) (all K*K values visible to the workgroup):
 //   SSD(u) = E1 + E2(u) - 2 C(u), summed in FP64 and rounded to FP32
 //   (objective of Eq. 7: -C(u) instead, without the energies),
 // surfaces (if requested), argmin (ties to the smallest index), the smallest
@@ -76,19 +76,20 @@ __device__ __forceinline__ double parabola_vertex(double a, double b, double c) 
 // parabola through the best value and its axis neighbours.  (tx0, ty0):
 // template top-left in A; (sx0, sy0): search-window top-left in B.
 // red: NT/64 ArgminState of LDS scratch.
-template <int NT>
+template <int NT, class Corr>
 __device__ __forceinline__ void ssd_epilogue(const MatchJob& jd, int cpi, int tx0, int ty0, int sx0, int sy0,
-                                             const float* Cs, ArgminState* red) {
+                                             Corr&& corr, ArgminState* red) {
   const int N = jd.N, r = jd.r, K = 2 * r + 1;
-  const bool corr = jd.obj != 0;
+  const bool eq7 = jd.obj != 0;
   ArgminState st{INFINITY, INT_MAX, INFINITY, 0};
-  const double E1 = corr ? 0.0 : box_sum(jd.satA, jd.wA + 1, ty0, tx0, N);
+  const double E1 = eq7 ? 0.0 : box_sum(jd.satA, jd.wA + 1, ty0, tx0, N);
   const int ldB = jd.wB + 1;
   auto value = [&](int idx) -> float {
-    if (corr) return -Cs[idx];
     const int uy = idx / K, ux = idx - uy * K;
+    const float c = corr(idx, uy, ux);
+    if (eq7) return -c;
     const double E2 = box_sum(jd.satB, ldB, sy0 + uy, sx0 + ux, N);
-    return (float)(E1 + E2 - 2.0 * (double)Cs[idx]);
+    return (float)(E1 + E2 - 2.0 * (double)c);
   };
   float* surf = jd.surfaces ? jd.surfaces + (size_t)cpi * K * K : nullptr;
   for (int idx = threadIdx.x; idx < K * K; idx += NT) {

@@ -10,6 +10,7 @@ constexpr int kMaxOrient = 16;        // m <= 16 orientation channels (CFOG extr
 constexpr int kMaxChannels = 64;      // channels of a volume the matcher takes (FHOG: 36)
 constexpr int kMaxGaussRadius = 8;    // Gaussian radius R <= 8 taps each side
 constexpr size_t kMaxLds = 160 * 1024;
+constexpr int kLaneMaxWidth = 1 << 21;  // image widths up to which a window's byte offsets fit 31 bits
 constexpr int kMaxSide = 1 << 16;      // template sides and radii above this are rejected before any
                                        // arithmetic on them (no path supports them anyway)
 
@@ -58,26 +59,6 @@ int launch_fhog(const float* img, int64_t stride, int H, int W, int cell, float*
 size_t extract_lds_bytes(int m, int R);
 size_t extract_workspace_bytes(int H, int W);
 
-// FFT matcher plans: FFT side P = R1 * R2, NT threads per workgroup, lds
-// bytes of dynamic LDS, templates of up to t_rows rows.
-struct FftPlan { int P, R1, R2, NT; size_t lds; int t_rows; };
-const FftPlan* fft_plans(int* count);
-// Smallest supported plan with P >= Ws whose LDS scratch also fits the
-// inverse row pass for K = 2r + 1; nullptr if none.
-const FftPlan* choose_fft_plan(int N, int r);
-// Whether plan p can match template side N with radius r.
-bool plan_fits(const FftPlan* p, int N, int r);
-// Set the dynamic-LDS limits of every kernel of the library on the current
-// device (once per device, from context creation, before any stream capture;
-// safe to call from several host threads).  0 on success.
-int init_kernel_attributes();
-int init_direct_attributes();
-int init_harris_attributes();
-int init_outlier_attributes();
-// Workgroups of this plan that fit the device at once.
-int plan_slots(const FftPlan* p, int num_cus);
-// Launch the FFT matcher.  d_jobs == nullptr: n_tasks control points of job0
-// (plain path).  Otherwise n_tasks (job, cp) pairs from d_tasks over d_jobs.
 // Channel split of a launch's last tasks: tasks [0, n_whole) run whole; every
 // later task runs as G work items, item g taking the channels
 // [g m / G, (g+1) m / G) and writing its correlation surface (K*K floats) to
@@ -91,6 +72,35 @@ struct SplitArgs {
   float* part;
 };
 
+// FFT matcher plans: FFT side P = R1 * R2, NT threads per workgroup, lds
+// bytes of dynamic LDS.  lane: the lane layout of match_lane.hpp, else the
+// group layout of match_fft.hip.
+struct FftPlan {
+  int P, R1, R2, NT;
+  size_t lds;
+  bool lane;
+  int (*launch)(const MatchJob&, const MatchJob*, const int2*, int, int, const SplitArgs&, hipStream_t);
+};
+// The plans that are chosen by size, in increasing order of it.
+const FftPlan* fft_plans(int* count);
+// Smallest supported plan with P >= Ws whose LDS scratch also fits the
+// inverse row pass for K = 2r + 1; nullptr if none.
+const FftPlan* choose_fft_plan(int N, int r);
+// Whether plan p can match template side N with radius r.
+bool plan_fits(const FftPlan* p, int N, int r);
+// The plan for images wider than kLaneMaxWidth (any N, r that some plan takes).
+const FftPlan* wide_plan();
+// Set the dynamic-LDS limits of every kernel of the library on the current
+// device (once per device, from context creation, before any stream capture;
+// safe to call from several host threads).  0 on success.
+int init_kernel_attributes();
+int init_direct_attributes();
+int init_harris_attributes();
+int init_outlier_attributes();
+// Workgroups of this plan that fit the device at once.
+int plan_slots(const FftPlan* p, int num_cus);
+// Launch the FFT matcher.  d_jobs == nullptr: n_tasks control points of job0
+// (plain path).  Otherwise n_tasks (job, cp) pairs from d_tasks over d_jobs.
 // n_blocks: workgroups (a grid-stride loop covers the remaining items).
 int launch_match_fft(const FftPlan* plan, const MatchJob& job0, const MatchJob* d_jobs, const int2* d_tasks,
                      int n_tasks, int n_blocks, const SplitArgs& sp, hipStream_t st);

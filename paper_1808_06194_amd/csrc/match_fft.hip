@@ -18,15 +18,17 @@
 //   x-pass: rows of T_c (or S_c), two real rows packed per complex FFT, the
 //           two half-spectra separated via Z(k) and conj Z(-k);
 //   y-pass: complex column FFTs of the half-spectrum kx in [0, P/2];
-//   ACC(ky, kx) += conj(T^_c) * S^_c  in registers.  Per plan layout: the
-//           row spectra of T_c and S_c side by side in LDS, both x-passes in
-//           one phase and each y-pass column transforming S then T (fused);
-//           or T^_c parked in registers between the T and S passes of the
-//           channel (the DC and Nyquist columns, both real, as one complex
-//           column job where that saves a round);
+//   ACC(ky, kx) += conj(T^_c) * S^_c  in registers, T^_c parked in registers
+//           between the T and S passes of the channel (the DC and Nyquist
+//           columns, both real, as one complex column job where that saves a
+//           round);
 // then one inverse: column IFFTs (kept rows u_y < K) and a C2R row IFFT with
 // two output rows packed per complex FFT (kept columns u_x < K), the SSD
 // assembly in FP64, and a lexicographic argmin + second-best over (SSD, index).
+//
+// Two kernels share this scheme: this file's (small windows, where one control
+// point's transforms fit a few waves, and images too wide for the other's
+// 32-bit offsets) and match_lane.hpp's (windows above 48).
 //
 // Execution: every 1-D FFT of length P = R1 * R2 is owned by a group of
 // G = max(R1, R2) lanes of one wave:
@@ -36,8 +38,7 @@
 // W_P^{k1 j} formed by recurrence from W_P^{k1}, and the exchange between
 // stages through the FFT's own LDS row or column, with t at positions that
 // keep a group's accesses in distinct banks (s1_pos, s1c).  Only the x -> y
-// transposes need workgroup barriers (2 per channel in the fused layout, 4
-// otherwise).
+// transposes need workgroup barriers (4 per channel).
 #include <hip/hip_runtime.h>
 #include <limits.h>
 #include <algorithm>
@@ -46,6 +47,7 @@
 #include "dft.hpp"
 #include "epilogue.hpp"
 #include "kernels.hpp"
+#include "match_lane.hpp"
 #include "window.hpp"
 
 namespace cfog {
@@ -66,12 +68,7 @@ __device__ __forceinline__ int opaque(int v) {
   return v;
 }
 
-// Channel layouts of a plan: T^ parked in registers between the template's
-// and the window's passes (LAY_REG), or both row spectra side by side in LDS
-// (LAY_FUSED).
-enum : int { LAY_REG = 0, LAY_FUSED = 1 };
-
-template <int P_, int R1_, int R2_, int NT_, int LAY_>
+template <int P_, int R1_, int R2_, int NT_>
 struct FftCfg {
   static constexpr int P = P_, R1 = R1_, R2 = R2_, NT = NT_;
   static_assert(P == R1 * R2, "P must equal R1 * R2");
@@ -85,21 +82,11 @@ struct FftCfg {
   // P/2 is a multiple of NG, the P/2 + 1 columns would take a whole round
   // more than P/2 columns, so those two go through one complex column FFT as
   // its real and imaginary parts (the packed job, column index 0): P/2 column
-  // jobs, a round and its accumulators fewer (P = 120 and 192).
+  // jobs, a round and its accumulators fewer.
   static constexpr bool PACK = (P / 2) % NG == 0;
   static constexpr int NCOL = PACK ? P / 2 : PH;   // column jobs of a y-pass
   static constexpr int KF = (NCOL + NG - 1) / NG;  // column rounds per group
-  static constexpr size_t BASE = sizeof(float2) * ((size_t)P * PH + P) + NW * 16;
-  // Fused layout (plans with one workgroup per CU): the row spectra of the
-  // template (XT, up to XT_ROWS rows) and of the window (X, P rows) side by
-  // side, so both x-passes share one phase and each y-pass column transforms
-  // S then T: two barriers per channel instead of four, no T^ registers.
-  // Templates of more rows than XT_ROWS take a larger plan.
-  static constexpr bool FUSE = LAY_ == LAY_FUSED;
-  static constexpr size_t XT_FIT = (kMaxLds - BASE) / (sizeof(float2) * PH) / 2 * 2;
-  static constexpr int XT_ROWS = FUSE ? (int)(XT_FIT < (size_t)P ? XT_FIT : (size_t)P) : 0;
-  static constexpr int T_ROWS = FUSE ? XT_ROWS : P;  // template rows the plan takes
-  static constexpr size_t LDS = BASE + sizeof(float2) * (size_t)XT_ROWS * PH;
+  static constexpr size_t LDS = sizeof(float2) * ((size_t)P * PH + P) + NW * 16;
 };
 
 // Lane identity within the FFT group layout.
@@ -154,61 +141,39 @@ template <class C>
 __device__ __forceinline__ int s1c(int j, int k) { return k * C::R2 + j; }
 
 // One set of rows for the x-pass: nrows x ncols real values at src (leading
-// dim ld), transformed into X (row stride PH).  zero_tail: rows
-// [2 ceil(nrows/2), P) of X are zeroed (a y-pass that reads all P rows).
+// dim ld), transformed into X (row stride PH).
 struct XRows {
   const float* src;
   int64_t ld;
   int nrows, ncols;
   float2* X;
-  bool zero_tail;
 };
 
-// x-pass: forward FFTs of the rows of NS sets (the pairs of set 0, then those
-// of set 1), zero-padded to P, two rows per complex FFT; leaves the
-// half-spectra of the rows in each set's X as [row][kx], kx in [0, P/2].
-template <class C, int NS>
-__device__ __forceinline__ void xpass_fwd(const Lane<C>& L, const XRows (&S)[NS], const float2* tw) {
-  constexpr int P = C::P, R1 = C::R1, R2 = C::R2, PH = C::PH;
-  const int nrp0 = (S[0].nrows + 1) >> 1;
-  const int total = NS > 1 ? nrp0 + ((S[NS - 1].nrows + 1) >> 1) : nrp0;
-  // item i -> (set, pair)
-  auto which = [&](int i, int& s, int& q) {
-    s = (NS > 1 && i >= nrp0) ? 1 : 0;
-    q = s ? i - nrp0 : i;
-  };
-  // the two rows of a pair, zero-padded, packed as one complex row
-  auto load = [&](int i, float2 (&v)[R1]) {
-    int s, q;
-    which(i, s, q);
-    const XRows& R = S[NS > 1 ? s : 0];
-    const int j = L.li;
-    const float* r0 = R.src + (int64_t)(2 * q) * R.ld;
-    const bool has1 = (2 * q + 1) < R.nrows;
-#pragma unroll
-    for (int a = 0; a < R1; ++a) {
-      const int xx = j + R2 * a;
-      float re = 0.f, im = 0.f;
-      if (xx < R.ncols) {
-        re = ldg(r0 + xx);
-        if (has1) im = ldg(r0 + R.ld + xx);
-      }
-      v[a] = make_float2(re, im);
-    }
-  };
+// x-pass: forward FFTs of the rows, zero-padded to P, two rows per complex FFT;
+// leaves the half-spectra of the rows in X as [row][kx], kx in [0, P/2].
+template <class C>
+__device__ __forceinline__ void xpass_fwd(const Lane<C>& L, const XRows& R, const float2* tw) {
+  constexpr int R1 = C::R1, R2 = C::R2, PH = C::PH;
+  const int total = (R.nrows + 1) >> 1;
   // each pair is loaded just before its transform: fetching the next pair
-  // ahead lost on the plans that use this pass (P = 100 at 768 threads;
-  // P = 160 and 192, whose registers spill, by 1%), unlike the prefetching
-  // fused pass of P = 144
-  for (int i = L.g; i < total; i += C::NG) {
-    int s, q;
-    which(i, s, q);
-    const XRows& R = S[NS > 1 ? s : 0];
+  // ahead lost by 1% at P = 192, whose registers spill
+  for (int q = L.g; q < total; q += C::NG) {
     float2* base = R.X + 2 * opaque(q) * PH;
     if (L.li < R2) {
       const int j = L.li;
+      const float* r0 = R.src + (int64_t)(2 * q) * R.ld;
+      const bool has1 = (2 * q + 1) < R.nrows;
       float2 v[R1];
-      load(i, v);
+#pragma unroll
+      for (int a = 0; a < R1; ++a) {
+        const int xx = j + R2 * a;
+        float re = 0.f, im = 0.f;
+        if (xx < R.ncols) {
+          re = ldg(r0 + xx);
+          if (has1) im = ldg(r0 + R.ld + xx);
+        }
+        v[a] = make_float2(re, im);
+      }
       dft<R1, -1>(v);
 #pragma unroll
       for (int k = 0; k < R1; ++k) base[s1_pos<C>(j, k)] = v[k];
@@ -216,8 +181,9 @@ __device__ __forceinline__ void xpass_fwd(const Lane<C>& L, const XRows (&S)[NS]
     wave_sync();
     xpass_stage2<C>(L, base, q, R.nrows, tw);
   }
-#pragma unroll
-  for (int s = 0; s < NS; ++s) xpass_zero_tail<C>(S[s]);
+  // rows [2 ceil(nrows/2), P) are zero padding (an odd last row is zeroed by
+  // its pair)
+  for (int t = threadIdx.x; t < (C::P - 2 * total) * PH; t += C::NT) R.X[2 * total * PH + t] = make_float2(0.f, 0.f);
 }
 
 // Stage 2 of the row FFT of pair q at base (stage 1 done), then the
@@ -268,86 +234,6 @@ __device__ __forceinline__ void xpass_stage2(const Lane<C>& L, float2* base, int
   }
 }
 
-// Rows [2 ceil(nrows/2), P) of a set's half-spectra are zero padding (an odd
-// last row is zeroed by its pair); needed where a y-pass reads all P rows.
-template <class C>
-__device__ __forceinline__ void xpass_zero_tail(const XRows& R) {
-  if (!R.zero_tail) return;
-  const int r0 = 2 * ((R.nrows + 1) >> 1);
-  for (int t = threadIdx.x; t < (C::P - r0) * C::PH; t += C::NT) R.X[r0 * C::PH + t] = make_float2(0.f, 0.f);
-}
-
-// The x-pass of the fused layout: as xpass_fwd over the template's rows then
-// the window's, except that the first pair of this group (template pair L.g)
-// was loaded into vn by the caller during the previous channel's y-pass,
-// which hides its global-memory latency; vn then prefetches the next pair.
-template <class C>
-__device__ __forceinline__ void xpass_fused(const Lane<C>& L, const XRows (&S)[2], const float2* tw,
-                                            float2 (&vn)[C::R1]) {
-  constexpr int P = C::P, R1 = C::R1, R2 = C::R2, PH = C::PH;
-  const int nrp0 = (S[0].nrows + 1) >> 1;
-  const int total = nrp0 + ((S[1].nrows + 1) >> 1);
-  auto load = [&](int i, float2 (&v)[R1]) {
-    const bool s1 = i >= nrp0;
-    const XRows& R = s1 ? S[1] : S[0];
-    const int q = s1 ? i - nrp0 : i;
-    const int j = L.li;
-    const float* r0 = R.src + (int64_t)(2 * q) * R.ld;
-    const bool has1 = (2 * q + 1) < R.nrows;
-#pragma unroll
-    for (int a = 0; a < R1; ++a) {
-      const int xx = j + R2 * a;
-      float re = 0.f, im = 0.f;
-      if (xx < R.ncols) {
-        re = ldg(r0 + xx);
-        if (has1) im = ldg(r0 + R.ld + xx);
-      }
-      v[a] = make_float2(re, im);
-    }
-  };
-  if (L.g >= nrp0 && L.g < total && L.li < R2) load(L.g, vn);  // not covered by the preload
-  for (int i = L.g; i < total; i += C::NG) {
-    const bool s1 = i >= nrp0;
-    const XRows& R = s1 ? S[1] : S[0];
-    const int q = s1 ? i - nrp0 : i;
-    float2* base = R.X + 2 * opaque(q) * PH;
-    if (L.li < R2) {
-      const int j = L.li;
-      float2 v[R1];
-#pragma unroll
-      for (int a = 0; a < R1; ++a) v[a] = vn[a];
-      if (i + C::NG < total) load(i + C::NG, vn);
-      dft<R1, -1>(v);
-#pragma unroll
-      for (int k = 0; k < R1; ++k) base[s1_pos<C>(j, k)] = v[k];
-    }
-    wave_sync();
-    xpass_stage2<C>(L, base, q, R.nrows, tw);
-  }
-  xpass_zero_tail<C>(S[1]);
-}
-
-// Issues the loads of this group's first pair of the fused x-pass (template
-// pair L.g) into vn.
-template <class C>
-__device__ __forceinline__ void xpass_fused_preload(const Lane<C>& L, const XRows& T, float2 (&vn)[C::R1]) {
-  if (L.g < ((T.nrows + 1) >> 1) && L.li < C::R2) {
-    const int j = L.li, q = L.g;
-    const float* r0 = T.src + (int64_t)(2 * q) * T.ld;
-    const bool has1 = (2 * q + 1) < T.nrows;
-#pragma unroll
-    for (int a = 0; a < C::R1; ++a) {
-      const int xx = j + C::R2 * a;
-      float re = 0.f, im = 0.f;
-      if (xx < T.ncols) {
-        re = ldg(r0 + xx);
-        if (has1) im = ldg(r0 + T.ld + xx);
-      }
-      vn[a] = make_float2(re, im);
-    }
-  }
-}
-
 // Row `row` of a y-pass input column: col[row PH], or for the packed job
 // (col = X, the DC column) the DC value plus i times the Nyquist value.
 template <class C>
@@ -391,70 +277,6 @@ __device__ __forceinline__ void packed_mac(float2* col, int k1, const float2 (&z
     acc[k2].x = fmaf(0.25f, us.x - vt.y, acc[k2].x);
     acc[k2].y = fmaf(0.25f, us.y + vt.x, acc[k2].y);
   }
-}
-
-// y-pass of the fused layout.  For each column kx of the group: the window's
-// column FFT in place in X (all P rows), then the template's, whose first
-// stage reads XT (rows < nT, zero beyond) and writes its intermediate into the
-// X column the window's transform has just left; conj(T^) S^ is accumulated
-// into acc[rnd][k2] for ky = k1 + R1 k2.
-template <class C>
-__device__ __forceinline__ void ypass_fused(const Lane<C>& L, const float2* XT, int nT, float2* X, const float2* tw,
-                                            float2 (&acc)[C::KF][C::R2]) {
-  constexpr int R1 = C::R1, R2 = C::R2, PH = C::PH;
-  static_for<0, C::KF>([&](auto rndI) {
-    constexpr int rnd = decltype(rndI)::value;
-    const int kx = L.g + rnd * C::NG;
-    if (kx < C::NCOL) {
-      const bool pk = C::PACK && rnd == 0 && kx == 0;
-      float2* col = X + opaque(kx);
-      const float2* colT = XT + kx;
-      float2 sh[R2];
-      // window: stage 1 in place, stage 2 into registers
-      if (L.li < R2) {
-        const int j = L.li;
-        float2 v[R1];
-#pragma unroll
-        for (int a = 0; a < R1; ++a) v[a] = col_in<C>(col, j + R2 * a, pk);
-        dft<R1, -1>(v);
-#pragma unroll
-        for (int k = 0; k < R1; ++k) col[s1c<C>(j, k) * PH] = v[k];
-      }
-      wave_sync();
-      if (L.li < R1) {
-        const int k1 = L.li;
-        stage2_inputs<C, false>(sh, tw, k1, [&](int b) { return col[s1c<C>(b, k1) * PH]; });
-        dft<R2, -1>(sh);
-      }
-      wave_sync();
-      // template: stage 1 from XT into the X column, stage 2 into registers
-      if (L.li < R2) {
-        const int j = L.li;
-        float2 v[R1];
-#pragma unroll
-        for (int a = 0; a < R1; ++a) {
-          const int row = j + R2 * a;
-          v[a] = row < nT ? col_in<C>(colT, row, pk) : make_float2(0.f, 0.f);
-        }
-        dft<R1, -1>(v);
-#pragma unroll
-        for (int k = 0; k < R1; ++k) col[s1c<C>(j, k) * PH] = v[k];
-      }
-      wave_sync();
-      if (L.li < R1) {
-        const int k1 = L.li;
-        float2 w[R2];
-        stage2_inputs<C, false>(w, tw, k1, [&](int b) { return col[s1c<C>(b, k1) * PH]; });
-        dft<R2, -1>(w);
-        if (pk) {
-          packed_mac<C>(col, k1, sh, w, acc[rnd]);
-        } else {
-#pragma unroll
-          for (int k2 = 0; k2 < R2; ++k2) acc[rnd][k2] = cmac_conj(acc[rnd][k2], w[k2], sh[k2]);
-        }
-      }
-    }
-  });
 }
 
 // y-pass: forward column FFTs of the half-spectrum (rows >= nrows were zeroed
@@ -525,72 +347,31 @@ __device__ __forceinline__ void match_one(const Lane<C>& L, const MatchJob& jd, 
   const size_t planeA = (size_t)jd.hA * jd.wA, planeB = (size_t)jd.hB * jd.wB;
   const float* tA = jd.volA + (size_t)ty0 * jd.wA + tx0;
   const float* sB = jd.volB + (size_t)sy0 * jd.wB + sx0;
-  // fused layout: both x-passes in one phase (template rows into XT, window
-  // rows into X), then one y-pass phase; two barriers per channel
-  auto fused_channels = [&]() {
-    float2* XT = reinterpret_cast<float2*>(reinterpret_cast<char*>(X) + C::BASE);
-    if constexpr (C::P >= 144) {
-      // P = 144 loads the next channel's first template pair during this
-      // channel's y-pass (measured: 1.4%).  At P = 120 (768 threads, 168
-      // VGPRs) the pair held through the y-pass raised the spills from 6 to
-      // 26 VGPRs and made the plan 7% slower.
-      float2 vn[R1];
-      xpass_fused_preload<C>(L, XRows{tA + c0 * planeA, jd.wA, N, N, XT, false}, vn);
-      for (int c = c0; c < c1; ++c) {
-        __syncthreads();  // previous readers of X and XT are done
-        const XRows rows[2] = {{tA + c * planeA, jd.wA, N, N, XT, false}, {sB + c * planeB, jd.wB, Ws, Ws, X, true}};
-        xpass_fused<C>(L, rows, tw, vn);
-        __syncthreads();
-        if (c + 1 < c1) xpass_fused_preload<C>(L, XRows{tA + (c + 1) * planeA, jd.wA, N, N, XT, false}, vn);
-        ypass_fused<C>(L, XT, N, X, tw, acc);
-      }
-    } else {
-      for (int c = c0; c < c1; ++c) {
-        __syncthreads();  // previous readers of X and XT are done
-        const XRows rows[2] = {{tA + c * planeA, jd.wA, N, N, XT, false}, {sB + c * planeB, jd.wB, Ws, Ws, X, true}};
-        xpass_fwd<C, 2>(L, rows, tw);
-        __syncthreads();
-        ypass_fused<C>(L, XT, N, X, tw, acc);
-      }
-    }
-  };
-  // two-phase layout: T^ parked in registers between the template's and the
-  // window's passes; four barriers per channel
-  auto split_channels = [&]() {
-    for (int c = c0; c < c1; ++c) {
-      float2 th[KF][R2];
-      __syncthreads();  // previous readers of X are done
-      const XRows rt[1] = {{tA + c * planeA, jd.wA, N, N, X, true}};
-      xpass_fwd<C, 1>(L, rt, tw);
-      __syncthreads();
-      auto park = [&](auto rndI, auto k2I, int, float2 v) {
-        constexpr int rnd = decltype(rndI)::value, k2 = decltype(k2I)::value;
-        th[rnd][k2] = v;
-      };
-      ypass_fwd<C>(L, X, tw, park, [&](auto rndI, int, const float2 (&w)[R2], float2*) {
-        static_for<0, R2>([&](auto k2I) { park(rndI, k2I, 0, w[decltype(k2I)::value]); });
-      });
-      __syncthreads();
-      const XRows rs[1] = {{sB + c * planeB, jd.wB, Ws, Ws, X, true}};
-      xpass_fwd<C, 1>(L, rs, tw);
-      __syncthreads();
-      auto parked = [&](auto rndI, auto k2I, int) {
-        constexpr int rnd = decltype(rndI)::value, k2 = decltype(k2I)::value;
-        return th[rnd][k2];
-      };
-      ypass_fwd<C>(L, X, tw, [&](auto rndI, auto k2I, int kx, float2 v) {
-        constexpr int rnd = decltype(rndI)::value, k2 = decltype(k2I)::value;
-        acc[rnd][k2] = cmac_conj(acc[rnd][k2], parked(rndI, k2I, kx), v);
-      }, [&](auto rndI, int k1, const float2 (&w)[R2], float2* col) {
-        constexpr int rnd = decltype(rndI)::value;
-        float2 zt[R2];
-        static_for<0, R2>([&](auto k2I) { zt[decltype(k2I)::value] = parked(rndI, k2I, 0); });
-        packed_mac<C>(col, k1, w, zt, acc[rnd]);
-      });
-    }
-  };
-  if constexpr (C::FUSE) fused_channels();  // N <= XT_ROWS (plan_fits)
-  else split_channels();
+  // T^ is parked in registers between the template's and the window's passes;
+  // four barriers per channel
+  for (int c = c0; c < c1; ++c) {
+    float2 th[KF][R2];
+    __syncthreads();  // previous readers of X are done
+    xpass_fwd<C>(L, XRows{tA + c * planeA, jd.wA, N, N, X}, tw);
+    __syncthreads();
+    auto park = [&](auto rndI, auto k2I, int, float2 v) {
+      constexpr int rnd = decltype(rndI)::value, k2 = decltype(k2I)::value;
+      th[rnd][k2] = v;
+    };
+    ypass_fwd<C>(L, X, tw, park, [&](auto rndI, int, const float2 (&w)[R2], float2*) {
+      static_for<0, R2>([&](auto k2I) { park(rndI, k2I, 0, w[decltype(k2I)::value]); });
+    });
+    __syncthreads();
+    xpass_fwd<C>(L, XRows{sB + c * planeB, jd.wB, Ws, Ws, X}, tw);
+    __syncthreads();
+    ypass_fwd<C>(L, X, tw, [&](auto rndI, auto k2I, int, float2 v) {
+      constexpr int rnd = decltype(rndI)::value, k2 = decltype(k2I)::value;
+      acc[rnd][k2] = cmac_conj(acc[rnd][k2], th[rnd][k2], v);
+    }, [&](auto rndI, int k1, const float2 (&w)[R2], float2* col) {
+      constexpr int rnd = decltype(rndI)::value;
+      packed_mac<C>(col, k1, w, th[rnd], acc[rnd]);
+    });
+  }
 
   // ---- inverse along y: each group transforms its own columns in place and
   // keeps the rows u_y < K (no workgroup barrier: a column is group-private).
@@ -691,7 +472,7 @@ __device__ __forceinline__ void match_one(const Lane<C>& L, const MatchJob& jd, 
     for (int i = threadIdx.x; i < K * K; i += NT) stg(part + i, Cs[i]);
     return;
   }
-  ssd_epilogue<NT>(jd, cpi, tx0, ty0, sx0, sy0, Cs, red);
+  ssd_epilogue<NT>(jd, cpi, tx0, ty0, sx0, sy0, [&](int i, int, int) { return Cs[i]; }, red);
 }
 
 // One kernel for both paths: with jobs == nullptr every task t is control
@@ -738,71 +519,111 @@ __global__ __launch_bounds__(C::NT) void match_fft_kernel(MatchJob job0, const M
 }
 
 // ------------------------------------------------------------------ plans
-//  P, R1, R2, NT, layout  (R1 >= R2 keeps the per-lane outputs of stage 2
-//  small).  NT is set per size from measurement: as many waves as the
-//  registers allow, in workgroups that fill a CU's wave slots (P = 32 and
-//  40 at 256 threads instead of 192, 2% faster; P = 60 and 64 at 512
-//  threads: 16 waves per CU where 384 and 320 threads left 12 and 15, 10%
-//  and 15% faster; P = 80-120 at 768 threads, three waves per
-//  SIMD: P = 80 and 90 6% and 5% faster than at 448 and 512, P = 96..108
-//  take every column in one round, P = 120 is 19% faster than at 512;
-//  P = 144 at 512 threads beats 256-384 and 768).  The layout too: the
-//  fused one was 6-18% faster than parking T^ in registers for P = 80..144.
-//  P = 160 and 192 park T^ in registers at 512 threads, where P = 192's
-//  DC/Nyquist packing leaves three whole column rounds: 10% and 18% faster
-//  than parking it in a global workspace at 768 threads, whose round trip
-//  was most of their HBM traffic.
-//  Sizes that lost to the next larger one on every measured (N, r) are left
-//  out: P = 128 (T^ in registers, 256 VGPRs and spills: 25-35% slower than
-//  P = 144), P = 150 (15 x 10, fused, 512 threads, spills: 1-11% slower than
-//  P = 160 on the same windows since P = 160 keeps T^ in registers; its
-//  registers layout spills 161 VGPRs) and P = 180 (15 x 12, several hundred
-//  spilled registers at any workgroup size: twice the time of P = 192).
-#define CFOG_PLANS(X)                  \
-  X(16, 4, 4, 64, LAY_REG)             \
-  X(24, 6, 4, 128, LAY_REG)            \
-  X(32, 8, 4, 256, LAY_REG)            \
-  X(40, 8, 5, 256, LAY_REG)            \
-  X(48, 8, 6, 256, LAY_REG)            \
-  X(60, 10, 6, 512, LAY_REG)           \
-  X(64, 8, 8, 512, LAY_REG)            \
-  X(72, 9, 8, 384, LAY_REG)            \
-  X(80, 10, 8, 768, LAY_FUSED)         \
-  X(90, 10, 9, 768, LAY_FUSED)         \
-  X(96, 12, 8, 768, LAY_FUSED)         \
-  X(100, 10, 10, 768, LAY_FUSED)       \
-  X(108, 12, 9, 768, LAY_FUSED)        \
-  X(120, 12, 10, 768, LAY_FUSED)       \
-  X(144, 12, 12, 512, LAY_FUSED)       \
-  X(160, 16, 10, 512, LAY_REG)         \
-  X(192, 16, 12, 512, LAY_REG)
+//  Group layout, G(P, R1, R2, NT): R1 >= R2 keeps the per-lane outputs of
+//  stage 2 small; NT from measurement: as many waves as the registers allow,
+//  in workgroups that fill a CU's wave slots.  P = 32..48 are level with the
+//  lane layout (46-50, 55-60 and 67-71 against 49, 57 and 65 us per 1,024
+//  points): there a point is a few waves' work on either.
+//  Lane layout, L(P, R1, R2, RA, RB, NT, PF, waves per SIMD): from 49 up, per
+//  1,024 points of template N and radius r, unsplit, before (the group layout)
+//  and after:
+//    N, r     P   before  after     N, r     P   before  after
+//    44,  8   60   141 ->  77 us    88, 20  128   525 -> 402 us (P = 144 before)
+//    44,  9   64   128 ->  95      100, 20  144   546 -> 447
+//    52, 10   72   263 -> 105      110, 20  150   729 -> 500    (P = 160 before)
+//    60, 10   80   247 -> 146      118, 20  160   737 -> 537
+//    66, 12   90   276 -> 192      130, 24  180   951 -> 685    (P = 192 before)
+//    72, 12   96   334 -> 197      128, 32  192   912 -> 811
+//    70, 15  100   319 -> 241
+//    80, 14  108   360 -> 242
+//    80, 20  120   403 -> 285
+//  The factors keep the wave-sized pieces of each phase at a multiple of four
+//  (a SIMD each) and the x2 items at one or two to a thread; up to P = 120 two
+//  or more workgroups share a CU (16 waves at 128 VGPRs, so NT and WPE), above
+//  it one has the plane to itself.  P = 135 (435 us at N + 2r = 135) was no
+//  better than 144.
+#define CFOG_PLANS(G, L)               \
+  G(16, 4, 4, 64)                      \
+  G(24, 6, 4, 128)                     \
+  G(32, 8, 4, 256)                     \
+  G(40, 8, 5, 256)                     \
+  G(48, 8, 6, 256)                     \
+  L(60, 6, 10, 15, 4, 192, 1, 4)       \
+  L(64, 8, 8, 8, 8, 256, 1, 4)         \
+  L(72, 6, 12, 9, 8, 256, 1, 4)        \
+  L(80, 5, 16, 5, 16, 256, 0, 4)       \
+  L(90, 9, 10, 9, 10, 448, 1, 4)       \
+  L(96, 8, 12, 12, 8, 512, 1, 4)       \
+  L(100, 10, 10, 5, 20, 512, 0, 4)     \
+  L(108, 9, 12, 9, 12, 512, 1, 4)      \
+  L(120, 8, 15, 15, 8, 512, 1, 4)      \
+  L(128, 16, 8, 16, 8, 1024)           \
+  L(144, 12, 12, 12, 12, 1024)         \
+  L(150, 10, 15, 15, 10, 768)          \
+  L(160, 10, 16, 20, 8, 896)           \
+  L(180, 20, 9, 15, 12, 960)           \
+  L(192, 24, 8, 24, 8, 512)            \
+  G(192, 16, 12, 512)
+template <class C>
+static int launch_group(const MatchJob& job0, const MatchJob* jobs, const int2* tasks, int n_tasks, int n_blocks,
+                        const SplitArgs& sp, hipStream_t st) {
+  hipLaunchKernelGGL(match_fft_kernel<C>, dim3(n_blocks), dim3(C::NT), C::LDS, st, job0, jobs, tasks, n_tasks, sp);
+  return hipGetLastError() == hipSuccess ? 0 : -2;
+}
 
-#define CFOG_CFG(P_, R1_, R2_, NT_, L_) FftCfg<P_, R1_, R2_, NT_, L_>
+template <class C>
+static int launch_lane(const MatchJob& job0, const MatchJob* jobs, const int2* tasks, int n_tasks, int n_blocks,
+                       const SplitArgs& sp, hipStream_t st) {
+  hipLaunchKernelGGL(match_lane_kernel<C>, dim3(n_blocks), dim3(C::NT), C::LDS, st, job0, jobs, tasks, n_tasks, sp);
+  return hipGetLastError() == hipSuccess ? 0 : -2;
+}
+
+template <class C>
+static constexpr FftPlan group_plan() {
+  return FftPlan{C::P, C::R1, C::R2, C::NT, C::LDS, false, launch_group<C>};
+}
+template <class C>
+static constexpr FftPlan lane_plan() {
+  return FftPlan{C::P, C::R1, C::R2, C::NT, C::LDS, true, launch_lane<C>};
+}
 
 static const FftPlan kPlans[] = {
-#define CFOG_PLAN_ENTRY(P_, R1_, R2_, NT_, L_) \
-  {P_, R1_, R2_, NT_, CFOG_CFG(P_, R1_, R2_, NT_, L_)::LDS, CFOG_CFG(P_, R1_, R2_, NT_, L_)::T_ROWS},
-    CFOG_PLANS(CFOG_PLAN_ENTRY)
+#define CFOG_PLAN_ENTRY(...) group_plan<FftCfg<__VA_ARGS__>>(),
+#define CFOG_LANE_ENTRY(...) lane_plan<LaneCfg<__VA_ARGS__>>(),
+    CFOG_PLANS(CFOG_PLAN_ENTRY, CFOG_LANE_ENTRY)
 #undef CFOG_PLAN_ENTRY
+#undef CFOG_LANE_ENTRY
 };
+constexpr int kNumPlans = sizeof(kPlans) / sizeof(kPlans[0]) - 1;  // those that are chosen by size
+
+// The last entry: the largest group layout, for images wider than the lane
+// layout's 32-bit offsets reach.
+const FftPlan* wide_plan() { return &kPlans[kNumPlans]; }
 
 const FftPlan* fft_plans(int* count) {
-  *count = (int)(sizeof(kPlans) / sizeof(kPlans[0]));
+  *count = kNumPlans;
   return kPlans;
+}
+
+// Whether the group layout p takes template side N with radius r: the K x K
+// correlation has to fit behind the rows of the inverse's row pairs.
+static bool group_fits(const FftPlan* p, int N, int r) {
+  const int Ws = N + 2 * r, K = 2 * r + 1;
+  if (p->P < Ws) return false;
+  const int PH = p->P / 2 + 1;
+  return (long)K * K <= 2L * (long)(p->P - 2 * ((K + 1) / 2)) * PH;
 }
 
 bool plan_fits(const FftPlan* p, int N, int r) {
   if (N < 1 || r < 0 || N > kMaxSide || r > kMaxSide) return false;
-  const int Ws = N + 2 * r, K = 2 * r + 1;
-  if (p->P < Ws || N > p->t_rows) return false;
-  const int PH = p->P / 2 + 1;
-  // the K x K correlation must fit behind the rows of the inverse's row pairs
-  return (long)K * K <= 2L * (long)(p->P - 2 * ((K + 1) / 2)) * PH;
+  // the lane layout has room for any window of its side; templates and radii
+  // are taken up to what the largest group layout takes, on every plan
+  return p->lane ? p->P >= N + 2 * r && group_fits(wide_plan(), N, r) : group_fits(p, N, r);
 }
 
 const FftPlan* choose_fft_plan(int N, int r) {
-  for (const FftPlan& p : kPlans)
-    if (plan_fits(&p, N, r)) return &p;
+  for (int i = 0; i < kNumPlans; ++i)
+    if (plan_fits(&kPlans[i], N, r)) return &kPlans[i];
   return nullptr;
 }
 
@@ -815,13 +636,6 @@ int plan_slots(const FftPlan* p, int num_cus) {
   int per_cu = (i >= 0 && i < 64) ? g_plan_occupancy[i] : 0;
   if (per_cu <= 0) per_cu = std::max(1, std::min((int)(kMaxLds / p->lds), 32 / (p->NT / 64)));
   return num_cus * per_cu;
-}
-
-template <class C>
-static int launch_t(const MatchJob& job0, const MatchJob* jobs, const int2* tasks, int n_tasks, int n_blocks,
-                    const SplitArgs& sp, hipStream_t st) {
-  hipLaunchKernelGGL(match_fft_kernel<C>, dim3(n_blocks), dim3(C::NT), C::LDS, st, job0, jobs, tasks, n_tasks, sp);
-  return hipGetLastError() == hipSuccess ? 0 : -2;
 }
 
 // One workgroup per split task: the sum of its G partial surfaces (in item
@@ -851,7 +665,7 @@ __global__ __launch_bounds__(SR_NT) void split_reduce_kernel(MatchJob job0, cons
     Cs[i] = s;
   }
   __syncthreads();
-  ssd_epilogue<SR_NT>(jd, cpi, bx.tx0, bx.ty0, bx.sx0, bx.sy0, Cs, red);
+  ssd_epilogue<SR_NT>(jd, cpi, bx.tx0, bx.ty0, bx.sx0, bx.sy0, [&](int i, int, int) { return Cs[i]; }, red);
 }
 
 int launch_split_reduce(const MatchJob& job0, const MatchJob* d_jobs, const int2* d_tasks, int n_tasks,
@@ -866,20 +680,21 @@ int launch_split_reduce(const MatchJob& job0, const MatchJob* d_jobs, const int2
 
 int init_match_fft_attributes() {
   int idx = 0;
-#define CFOG_PLAN_ATTR(P_, R1_, R2_, NT_, L_)                                                               \
-  {                                                                                                          \
-    using Cfg = CFOG_CFG(P_, R1_, R2_, NT_, L_);                                                             \
-    if (hipFuncSetAttribute((const void*)match_fft_kernel<Cfg>, hipFuncAttributeMaxDynamicSharedMemorySize,  \
-                            (int)Cfg::LDS) != hipSuccess)                                                    \
-      return -2;                                                                                             \
-    int n = 0;                                                                                               \
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, match_fft_kernel<Cfg>, Cfg::NT, Cfg::LDS) !=        \
-        hipSuccess)                                                                                          \
-      n = 0;                                                                                                 \
-    g_plan_occupancy[idx++] = n;                                                                             \
-  }
-  CFOG_PLANS(CFOG_PLAN_ATTR)
+  auto set = [&](auto* kernel, int nt, size_t lds) {
+    if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+      return false;
+    int n = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, nt, lds) != hipSuccess) n = 0;
+    g_plan_occupancy[idx++] = n;
+    return true;
+  };
+#define CFOG_PLAN_ATTR(...) \
+  if (!set(match_fft_kernel<FftCfg<__VA_ARGS__>>, FftCfg<__VA_ARGS__>::NT, FftCfg<__VA_ARGS__>::LDS)) return -2;
+#define CFOG_LANE_ATTR(...) \
+  if (!set(match_lane_kernel<LaneCfg<__VA_ARGS__>>, LaneCfg<__VA_ARGS__>::NT, LaneCfg<__VA_ARGS__>::LDS)) return -2;
+  CFOG_PLANS(CFOG_PLAN_ATTR, CFOG_LANE_ATTR)
 #undef CFOG_PLAN_ATTR
+#undef CFOG_LANE_ATTR
   if (hipFuncSetAttribute((const void*)split_reduce_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                           (int)kMaxLds) != hipSuccess)
     return -2;
@@ -905,12 +720,7 @@ int init_kernel_attributes() {
 int launch_match_fft(const FftPlan* plan, const MatchJob& job0, const MatchJob* d_jobs, const int2* d_tasks,
                      int n_tasks, int n_blocks, const SplitArgs& sp, hipStream_t st) {
   if (n_tasks <= 0) return 0;
-#define CFOG_PLAN_CASE(P_, R1_, R2_, NT_, L_) \
-  if (plan->P == P_)                          \
-    return launch_t<CFOG_CFG(P_, R1_, R2_, NT_, L_)>(job0, d_jobs, d_tasks, n_tasks, n_blocks, sp, st);
-  CFOG_PLANS(CFOG_PLAN_CASE)
-#undef CFOG_PLAN_CASE
-  return -1;
+  return plan->launch(job0, d_jobs, d_tasks, n_tasks, n_blocks, sp, st);
 }
 
 }  // namespace cfog
