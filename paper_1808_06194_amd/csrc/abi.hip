@@ -157,15 +157,15 @@ const cfog::FftPlan* job_plan(cfog_ctx* ctx, const cfog_job& j, int m) {
 // ------------------------------------------------------------- batch plans
 
 // Channel split of the last round of a launch (split_plan.hpp).
-cfog::SplitArgs plan_split(const cfog::FftPlan* p, int n, int S, int m, int Nmax, int Wsmax, int Kmax,
+cfog::SplitArgs plan_split(cfog_ctx* ctx, const cfog::FftPlan* p, int n, int m, int Nmax, int Wsmax, int Kmax,
                            size_t* bytes) {
-  const cfog::SplitChoice c = cfog::plan_split_choice(p->P, n, S, m, Nmax, Wsmax, Kmax);
+  const cfog::SplitChoice c = cfog::plan_split_choice(p->P, n, cfog::plan_split_slots(p, ctx->num_cus), m, Nmax, Wsmax, Kmax);
   *bytes = c.bytes;
   return cfog::SplitArgs{c.n_whole, c.G, c.slot, nullptr};
 }
 
 // Workspace layout of a plain-path launch of job j: the split partials (when
-// split_ok), one workgroup per work item.
+// split_ok), one workgroup per work item (lane layout: at most those resident).
 struct PlainLayout {
   const cfog::FftPlan* p = nullptr;
   cfog::SplitArgs sp{0, 1, 0, nullptr};
@@ -179,7 +179,7 @@ PlainLayout plain_layout(cfog_ctx* ctx, const cfog_job& j, int m, bool split_ok)
   if (!L.p) return L;
   const int S = cfog::plan_slots(L.p, ctx->num_cus);
   size_t sb = 0;
-  L.sp = split_ok ? plan_split(L.p, j.n_cps, S, m, j.N, j.N + 2 * j.r, 2 * j.r + 1, &sb)
+  L.sp = split_ok ? plan_split(ctx, L.p, j.n_cps, m, j.N, j.N + 2 * j.r, 2 * j.r + 1, &sb)
                   : cfog::SplitArgs{j.n_cps, 1, 0, nullptr};
   const int items = cfog::split_items(j.n_cps, L.sp);
   L.blocks = L.p->lane ? std::min(items, S) : items;
@@ -232,7 +232,7 @@ int build_batch(cfog_ctx* ctx, const cfog_job* jobs, int n_jobs, int m, int obj,
     if (b.count == 0) continue;
     const int S = cfog::plan_slots(b.plan, ctx->num_cus);
     size_t sb = 0;
-    b.sp = plan_split(b.plan, b.count, S, m, Nmax, Wmax, Kmax, &sb);
+    b.sp = plan_split(ctx, b.plan, b.count, m, Nmax, Wmax, Kmax, &sb);
     if (sb > split_budget) {
       b.sp = cfog::SplitArgs{b.count, 1, 0, nullptr};
       sb = 0;
@@ -271,7 +271,7 @@ int enqueue_batch(cfog_ctx* ctx, const BatchPlan& B, char* ws, const void* host,
     cfog::SplitArgs sp = b.sp;
     sp.part = sp.G > 1 ? (float*)(ws + b.split_off) : nullptr;
     return cfog::launch_match_fft(b.plan, cfog::MatchJob{}, d_jobs, d_tasks + b.begin, b.count, b.blocks, sp,
-                                  s) == 0 &&
+                                  ctx->num_cus, s) == 0 &&
            cfog::launch_split_reduce(cfog::MatchJob{}, d_jobs, d_tasks + b.begin, b.count, sp, s) == 0;
   };
   if (B.buckets.size() == 1) {
@@ -378,7 +378,7 @@ int autotune(cfog_ctx* ctx, const cfog_job& j, int m, hipStream_t st) {
     for (int rep = 0; rep < 2 && ok; ++rep) {  // the first launch warms up
       ok = hipEventRecord(e0, st) == hipSuccess &&
            cfog::launch_match_fft(p, dj, nullptr, nullptr, dj.n_cps, blocks, cfog::SplitArgs{dj.n_cps, 1, 0, nullptr},
-                                  st) == 0 &&
+                                  ctx->num_cus, st) == 0 &&
            hipEventRecord(e1, st) == hipSuccess && hipEventSynchronize(e1) == hipSuccess &&
            hipEventElapsedTime(&ms, e0, e1) == hipSuccess;
     }
@@ -703,7 +703,7 @@ static int match_batch_run(cfog_ctx* ctx, const cfog_job* jobs, int32_t n_jobs, 
       cfog::SplitArgs sp = L.sp;
       sp.part = sp.G > 1 ? (float*)(ws + L.split_off) : nullptr;
       const cfog::MatchJob dj = to_device_job(jobs[i], m, obj);
-      if (cfog::launch_match_fft(L.p, dj, nullptr, nullptr, jobs[i].n_cps, L.blocks, sp, st) != 0 ||
+      if (cfog::launch_match_fft(L.p, dj, nullptr, nullptr, jobs[i].n_cps, L.blocks, sp, ctx->num_cus, st) != 0 ||
           cfog::launch_split_reduce(dj, nullptr, nullptr, jobs[i].n_cps, sp, st) != 0)
         return record(ctx, hipGetLastError());
     }

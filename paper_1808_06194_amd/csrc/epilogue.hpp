@@ -84,18 +84,38 @@ __device__ __forceinline__ void ssd_epilogue(const MatchJob& jd, int cpi, int tx
   ArgminState st{INFINITY, INT_MAX, INFINITY, 0};
   const double E1 = eq7 ? 0.0 : box_sum(jd.satA, jd.wA + 1, ty0, tx0, N);
   const int ldB = jd.wB + 1;
-  auto value = [&](int idx) -> float {
+  auto energy = [&](int uy, int ux) { return eq7 ? 0.0 : box_sum(jd.satB, ldB, sy0 + uy, sx0 + ux, N); };
+  auto value = [&](double E2, float c) -> float { return eq7 ? -c : (float)(E1 + E2 - 2.0 * (double)c); };
+  auto value_at = [&](int idx) -> float {
     const int uy = idx / K, ux = idx - uy * K;
-    const float c = corr(idx, uy, ux);
-    if (eq7) return -c;
-    const double E2 = box_sum(jd.satB, ldB, sy0 + uy, sx0 + ux, N);
-    return (float)(E1 + E2 - 2.0 * (double)c);
+    const double E2 = energy(uy, ux);
+    return value(E2, corr(idx, uy, ux));
   };
   float* surf = jd.surfaces ? jd.surfaces + (size_t)cpi * K * K : nullptr;
-  for (int idx = threadIdx.x; idx < K * K; idx += NT) {
-    const float s = value(idx);
-    am_push(st, s, idx);
-    if (surf) stg(surf + idx, s);
+  // EP offsets of a thread at a time: their table reads are in flight together
+  // (one at a time, 9 rounds of a far table's latency at K = 65 and 512
+  // threads)
+  constexpr int EP = 4;
+  for (int b = 0; b < K * K; b += EP * NT) {
+    double E2[EP];
+    int uy[EP], ux[EP];
+#pragma unroll
+    for (int t = 0; t < EP; ++t) {
+      if (b + t * NT >= K * K) break;
+      const int idx = min(b + t * NT + (int)threadIdx.x, K * K - 1);
+      uy[t] = idx / K;
+      ux[t] = idx - uy[t] * K;
+      E2[t] = energy(uy[t], ux[t]);
+    }
+#pragma unroll
+    for (int t = 0; t < EP; ++t) {
+      const int idx = b + t * NT + (int)threadIdx.x;
+      if (idx < K * K) {
+        const float s = value(E2[t], corr(idx, uy[t], ux[t]));
+        am_push(st, s, idx);
+        if (surf) stg(surf + idx, s);
+      }
+    }
   }
   // wave reduction then across waves
 #pragma unroll
@@ -123,9 +143,9 @@ __device__ __forceinline__ void ssd_epilogue(const MatchJob& jd, int cpi, int tx
         // the same FP32 values as the surface output
         float fx = (float)(ux - r), fy = (float)(uy - r);
         if (ux > 0 && ux < K - 1)
-          fx += (float)parabola_vertex(value(st.bi - 1), st.bv, value(st.bi + 1));
+          fx += (float)parabola_vertex(value_at(st.bi - 1), st.bv, value_at(st.bi + 1));
         if (uy > 0 && uy < K - 1)
-          fy += (float)parabola_vertex(value(st.bi - K), st.bv, value(st.bi + K));
+          fy += (float)parabola_vertex(value_at(st.bi - K), st.bv, value_at(st.bi + K));
         jd.subpix[cpi] = make_float2(fx, fy);
       }
     }

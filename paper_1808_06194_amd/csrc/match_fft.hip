@@ -521,75 +521,88 @@ __global__ __launch_bounds__(C::NT) void match_fft_kernel(MatchJob job0, const M
 // ------------------------------------------------------------------ plans
 //  Group layout, G(P, R1, R2, NT): R1 >= R2 keeps the per-lane outputs of
 //  stage 2 small; NT from measurement: as many waves as the registers allow,
-//  in workgroups that fill a CU's wave slots.  P = 32..48 are level with the
+//  in workgroups that fill a CU's wave slots.  P = 32..48 were level with the
 //  lane layout (46-50, 55-60 and 67-71 against 49, 57 and 65 us per 1,024
 //  points): there a point is a few waves' work on either.
-//  Lane layout, L(P, R1, R2, RA, RB, NT, PF, waves per SIMD): from 49 up, per
-//  1,024 points of template N and radius r, unsplit, before (the group layout)
-//  and after:
+//  Lane layout, L((P, R1, R2, RA, RB, I1, I2), full, spread), each a workgroup
+//  (NT, PF, waves per SIMD): from 49 up, per 1,024 points of template N and
+//  radius r, unsplit, before (the group layout) and after:
 //    N, r     P   before  after     N, r     P   before  after
-//    44,  8   60   141 ->  77 us    88, 20  128   525 -> 402 us (P = 144 before)
-//    44,  9   64   128 ->  95      100, 20  144   546 -> 447
-//    52, 10   72   263 -> 105      110, 20  150   729 -> 500    (P = 160 before)
-//    60, 10   80   247 -> 146      118, 20  160   737 -> 537
-//    66, 12   90   276 -> 192      130, 24  180   951 -> 685    (P = 192 before)
-//    72, 12   96   334 -> 197      128, 32  192   912 -> 811
-//    70, 15  100   319 -> 241
-//    80, 14  108   360 -> 242
-//    80, 20  120   403 -> 285
+//    44,  8   60   142 ->  80 us    72, 12   96   336 -> 205 us
+//    44,  9   64   129 ->  99       70, 15  100   319 -> 238
+//    52, 10   72   261 -> 107       80, 14  108   356 -> 254
+//    60, 10   80   246 -> 151       80, 20  120   405 -> 294
+//    66, 12   90   278 -> 185      100, 20  144   541 -> 449
+//                                  118, 20  160   732 -> 555
+//                                  128, 32  192   922 -> 849
 //  The factors keep the wave-sized pieces of each phase at a multiple of four
 //  (a SIMD each) and the x2 items at one or two to a thread; up to P = 120 two
 //  or more workgroups share a CU (16 waves at 128 VGPRs, so NT and WPE), above
-//  it one has the plane to itself.  P = 135 (435 us at N + 2r = 135) was no
-//  better than 144.
-#define CFOG_PLANS(G, L)               \
-  G(16, 4, 4, 64)                      \
-  G(24, 6, 4, 128)                     \
-  G(32, 8, 4, 256)                     \
-  G(40, 8, 5, 256)                     \
-  G(48, 8, 6, 256)                     \
-  L(60, 6, 10, 15, 4, 192, 1, 4)       \
-  L(64, 8, 8, 8, 8, 256, 1, 4)         \
-  L(72, 6, 12, 9, 8, 256, 1, 4)        \
-  L(80, 5, 16, 5, 16, 256, 0, 4)       \
-  L(90, 9, 10, 9, 10, 448, 1, 4)       \
-  L(96, 8, 12, 12, 8, 512, 1, 4)       \
-  L(100, 10, 10, 5, 20, 512, 0, 4)     \
-  L(108, 9, 12, 9, 12, 512, 1, 4)      \
-  L(120, 8, 15, 15, 8, 512, 1, 4)      \
-  L(128, 16, 8, 16, 8, 1024)           \
-  L(144, 12, 12, 12, 12, 1024)         \
-  L(150, 10, 15, 15, 10, 768)          \
-  L(160, 10, 16, 20, 8, 896)           \
-  L(180, 20, 9, 15, 12, 960)           \
-  L(192, 24, 8, 24, 8, 512)            \
+//  it one has the plane to itself.  Spread is for launches that leave each
+//  workgroup its CU, where a point's own waves are all there is to hide
+//  latency: 200 points took 61 -> 48, 70 -> 50, 73 -> 54, 104 -> 71, 71 -> 66,
+//  80 -> 66, 99 -> 84, 94 -> 79, 104 -> 94 us with it from P = 60 to 120.
+#define CFOG_PLANS(G, L)                                         \
+  G(16, 4, 4, 64)                                                \
+  G(24, 6, 4, 128)                                               \
+  G(32, 8, 4, 256)                                               \
+  G(40, 8, 5, 256)                                               \
+  G(48, 8, 6, 256)                                               \
+  L((60, 6, 10, 15, 4, 10, 6), (192, 1, 4), (512, 1, 4))         \
+  L((64, 8, 8, 8, 8, 8, 8), (256, 1, 4), (512, 1, 4))            \
+  L((72, 6, 12, 9, 8, 9, 8), (256, 1, 4), (512, 1, 4))           \
+  L((80, 5, 16, 5, 16, 10, 8), (256, 0, 4), (1024, 1, 4))        \
+  L((90, 9, 10, 9, 10, 10, 9), (512, 1, 4), (768, 1, 4))         \
+  L((96, 8, 12, 12, 8, 12, 8), (512, 1, 4), (768, 1, 4))         \
+  L((100, 10, 10, 5, 20, 10, 10), (512, 0, 4), (1024, 1, 4))     \
+  L((108, 9, 12, 9, 12, 12, 9), (512, 1, 4), (1024, 1, 4))       \
+  L((120, 8, 15, 15, 8, 12, 10), (512, 1, 4), (768, 1, 4))       \
+  L((144, 12, 12, 12, 12, 12, 12), (1024, 1, 4), (1024, 1, 4))   \
+  L((160, 10, 16, 20, 8, 16, 10), (896, 0, 4), (896, 0, 4))      \
+  L((192, 24, 8, 24, 8, 16, 12), (512, 0, 2), (512, 0, 2))       \
   G(192, 16, 12, 512)
+
+#define CFOG_ARGS(...) __VA_ARGS__
+#define CFOG_LANE_CFG(PLAN, TEAM) LaneCfg<CFOG_ARGS PLAN, CFOG_ARGS TEAM>
+
 template <class C>
 static int launch_group(const MatchJob& job0, const MatchJob* jobs, const int2* tasks, int n_tasks, int n_blocks,
-                        const SplitArgs& sp, hipStream_t st) {
+                        const SplitArgs& sp, int, hipStream_t st) {
   hipLaunchKernelGGL(match_fft_kernel<C>, dim3(n_blocks), dim3(C::NT), C::LDS, st, job0, jobs, tasks, n_tasks, sp);
   return hipGetLastError() == hipSuccess ? 0 : -2;
 }
 
-template <class C>
+// Workgroups of W that a CU holds (its registers allow W::WPE waves to a SIMD).
+template <class W>
+constexpr int resident() {
+  return std::max(1, std::min((int)(kMaxLds / W::LDS), 4 * W::WPE / W::NW));
+}
+
+// C, or where the whole launch is resident at once with the larger workgroup,
+// W: the points then have the CUs to themselves, and more waves to a point is
+// what is left.
+template <class C, class W>
 static int launch_lane(const MatchJob& job0, const MatchJob* jobs, const int2* tasks, int n_tasks, int n_blocks,
-                       const SplitArgs& sp, hipStream_t st) {
-  hipLaunchKernelGGL(match_lane_kernel<C>, dim3(n_blocks), dim3(C::NT), C::LDS, st, job0, jobs, tasks, n_tasks, sp);
+                       const SplitArgs& sp, int num_cus, hipStream_t st) {
+  if (n_blocks <= resident<W>() * num_cus)
+    hipLaunchKernelGGL(match_lane_kernel<W>, dim3(n_blocks), dim3(W::NT), W::LDS, st, job0, jobs, tasks, n_tasks, sp);
+  else
+    hipLaunchKernelGGL(match_lane_kernel<C>, dim3(n_blocks), dim3(C::NT), C::LDS, st, job0, jobs, tasks, n_tasks, sp);
   return hipGetLastError() == hipSuccess ? 0 : -2;
 }
 
 template <class C>
 static constexpr FftPlan group_plan() {
-  return FftPlan{C::P, C::R1, C::R2, C::NT, C::LDS, false, launch_group<C>};
+  return FftPlan{C::P, C::R1, C::R2, C::NT, C::LDS, C::P, false, launch_group<C>};
 }
-template <class C>
+template <class C, class W>
 static constexpr FftPlan lane_plan() {
-  return FftPlan{C::P, C::R1, C::R2, C::NT, C::LDS, true, launch_lane<C>};
+  return FftPlan{C::P, C::R1, C::R2, C::NT, C::LDS, C::P == 144 ? 134 : C::P, true, launch_lane<C, W>};
 }
 
 static const FftPlan kPlans[] = {
 #define CFOG_PLAN_ENTRY(...) group_plan<FftCfg<__VA_ARGS__>>(),
-#define CFOG_LANE_ENTRY(...) lane_plan<LaneCfg<__VA_ARGS__>>(),
+#define CFOG_LANE_ENTRY(PLAN, FULL, SPREAD) lane_plan<CFOG_LANE_CFG(PLAN, FULL), CFOG_LANE_CFG(PLAN, SPREAD)>(),
     CFOG_PLANS(CFOG_PLAN_ENTRY, CFOG_LANE_ENTRY)
 #undef CFOG_PLAN_ENTRY
 #undef CFOG_LANE_ENTRY
@@ -605,20 +618,9 @@ const FftPlan* fft_plans(int* count) {
   return kPlans;
 }
 
-// Whether the group layout p takes template side N with radius r: the K x K
-// correlation has to fit behind the rows of the inverse's row pairs.
-static bool group_fits(const FftPlan* p, int N, int r) {
-  const int Ws = N + 2 * r, K = 2 * r + 1;
-  if (p->P < Ws) return false;
-  const int PH = p->P / 2 + 1;
-  return (long)K * K <= 2L * (long)(p->P - 2 * ((K + 1) / 2)) * PH;
-}
-
 bool plan_fits(const FftPlan* p, int N, int r) {
   if (N < 1 || r < 0 || N > kMaxSide || r > kMaxSide) return false;
-  // the lane layout has room for any window of its side; templates and radii
-  // are taken up to what the largest group layout takes, on every plan
-  return p->lane ? p->P >= N + 2 * r && group_fits(wide_plan(), N, r) : group_fits(p, N, r);
+  return p->P >= N + 2 * r && N <= p->t_rows && offsets_fit(p->P, 2 * r + 1);
 }
 
 const FftPlan* choose_fft_plan(int N, int r) {
@@ -638,14 +640,23 @@ int plan_slots(const FftPlan* p, int num_cus) {
   return num_cus * per_cu;
 }
 
-// One workgroup per split task: the sum of its G partial surfaces (in item
-// order) into LDS, then the epilogue of the whole sum.
+// Slots the channel split of a launch's last round is planned for.  Lane
+// layout: two workgroups to a CU up to P = 72 and one above, the group
+// layout's numbers, and not as many as fit, so that the same points are split
+// into the same groups and their partial sums keep their roundings (see
+// lane_inverse); the launches still fill every slot.
+int plan_split_slots(const FftPlan* p, int num_cus) {
+  return p->lane ? num_cus * (p->P <= 72 ? 2 : 1) : plan_slots(p, num_cus);
+}
+
+// One workgroup per split task: the epilogue over the sum of its G partial
+// surfaces (in item order), which each thread forms as it goes.  Bound by the
+// latency of its reads, so all of an offset's are in flight together.
 constexpr int SR_NT = 1024;
+constexpr int SR_MAX_G = 16;  // plan_split_choice's limit
 __global__ __launch_bounds__(SR_NT) void split_reduce_kernel(MatchJob job0, const MatchJob* __restrict__ jobs,
                                                             const int2* __restrict__ tasks, SplitArgs sp) {
-  extern __shared__ float4 sr_lds[];
-  ArgminState* red = reinterpret_cast<ArgminState*>(sr_lds);
-  float* Cs = reinterpret_cast<float*>(red + SR_NT / 64);
+  __shared__ ArgminState red[SR_NT / 64];
   const int t = sp.n_whole + blockIdx.x;
   MatchJob jd = job0;
   int cpi = t;
@@ -655,34 +666,38 @@ __global__ __launch_bounds__(SR_NT) void split_reduce_kernel(MatchJob job0, cons
     cpi = tk.y;
   }
   const int4 cp = jd.cps[cpi];
-  const int K = 2 * jd.r + 1;
   const CpBoxes bx = cp_boxes(cp.x, cp.y, cp.z, cp.w, jd.N, jd.r, jd.hA, jd.wA, jd.hB, jd.wB);
   if (!bx.inside) return;  // reported by the task's first item
   const float* p = sp.part + (size_t)blockIdx.x * sp.G * sp.slot;
-  for (int i = threadIdx.x; i < K * K; i += SR_NT) {
-    float s = ldg(p + i);
-    for (int g = 1; g < sp.G; ++g) s += ldg(p + (size_t)g * sp.slot + i);
-    Cs[i] = s;
-  }
-  __syncthreads();
-  ssd_epilogue<SR_NT>(jd, cpi, bx.tx0, bx.ty0, bx.sx0, bx.sy0, [&](int i, int, int) { return Cs[i]; }, red);
+  auto corr = [&](int idx, int, int) -> float {
+    float v[SR_MAX_G];
+#pragma unroll
+    for (int g = 0; g < SR_MAX_G; ++g)
+      if (g < sp.G) v[g] = ldg(p + (size_t)g * sp.slot + idx);
+    float s = v[0];
+#pragma unroll
+    for (int g = 1; g < SR_MAX_G; ++g)
+      if (g < sp.G) s += v[g];
+    return s;
+  };
+  ssd_epilogue<SR_NT>(jd, cpi, bx.tx0, bx.ty0, bx.sx0, bx.sy0, corr, red);
 }
 
 int launch_split_reduce(const MatchJob& job0, const MatchJob* d_jobs, const int2* d_tasks, int n_tasks,
                         const SplitArgs& sp, hipStream_t st) {
   if (sp.G <= 1 || n_tasks <= sp.n_whole) return 0;
-  const size_t lds = sizeof(ArgminState) * (SR_NT / 64) + sizeof(float) * (size_t)sp.slot;
-  if (lds > kMaxLds) return -1;
-  hipLaunchKernelGGL(split_reduce_kernel, dim3(n_tasks - sp.n_whole), dim3(SR_NT), lds, st, job0, d_jobs, d_tasks,
-                     sp);
+  if (sp.G > SR_MAX_G) return -1;
+  hipLaunchKernelGGL(split_reduce_kernel, dim3(n_tasks - sp.n_whole), dim3(SR_NT), 0, st, job0, d_jobs, d_tasks, sp);
   return hipGetLastError() == hipSuccess ? 0 : -2;
 }
 
 int init_match_fft_attributes() {
   int idx = 0;
+  auto allow = [&](auto* kernel, size_t lds) {
+    return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess;
+  };
   auto set = [&](auto* kernel, int nt, size_t lds) {
-    if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-      return false;
+    if (!allow(kernel, lds)) return false;
     int n = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, nt, lds) != hipSuccess) n = 0;
     g_plan_occupancy[idx++] = n;
@@ -690,14 +705,15 @@ int init_match_fft_attributes() {
   };
 #define CFOG_PLAN_ATTR(...) \
   if (!set(match_fft_kernel<FftCfg<__VA_ARGS__>>, FftCfg<__VA_ARGS__>::NT, FftCfg<__VA_ARGS__>::LDS)) return -2;
-#define CFOG_LANE_ATTR(...) \
-  if (!set(match_lane_kernel<LaneCfg<__VA_ARGS__>>, LaneCfg<__VA_ARGS__>::NT, LaneCfg<__VA_ARGS__>::LDS)) return -2;
+#define CFOG_LANE_ATTR(PLAN, FULL, SPREAD)                                                     \
+  {                                                                                            \
+    using C = CFOG_LANE_CFG(PLAN, FULL);                                                       \
+    using W = CFOG_LANE_CFG(PLAN, SPREAD);                                                     \
+    if (!set(match_lane_kernel<C>, C::NT, C::LDS) || !allow(match_lane_kernel<W>, W::LDS)) return -2; \
+  }
   CFOG_PLANS(CFOG_PLAN_ATTR, CFOG_LANE_ATTR)
 #undef CFOG_PLAN_ATTR
 #undef CFOG_LANE_ATTR
-  if (hipFuncSetAttribute((const void*)split_reduce_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                          (int)kMaxLds) != hipSuccess)
-    return -2;
   return 0;
 }
 
@@ -718,9 +734,9 @@ int init_kernel_attributes() {
 }
 
 int launch_match_fft(const FftPlan* plan, const MatchJob& job0, const MatchJob* d_jobs, const int2* d_tasks,
-                     int n_tasks, int n_blocks, const SplitArgs& sp, hipStream_t st) {
+                     int n_tasks, int n_blocks, const SplitArgs& sp, int num_cus, hipStream_t st) {
   if (n_tasks <= 0) return 0;
-  return plan->launch(job0, d_jobs, d_tasks, n_tasks, n_blocks, sp, st);
+  return plan->launch(job0, d_jobs, d_tasks, n_tasks, n_blocks, sp, num_cus, st);
 }
 
 }  // namespace cfog

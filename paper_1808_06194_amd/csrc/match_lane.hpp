@@ -5,9 +5,8 @@
 // A channel's samples are real, so along y only half of the spectrum is formed:
 // with P = RA RB and ky = k1 + RA k2, the first stage is a real transform of
 // RA values, and its outputs k1 = 0..RA/2 are the only ones taken further.  The
-// rows ky of the plane so formed, with weight 2 where -ky is not among them,
-// carry the whole correlation:
-//   C(u) = Re sum_{rows ky} w(ky) sum_kx ACC(ky, kx) W^{-(ky u_y + kx u_x)}.
+// rows ky of the plane so formed carry the whole correlation, the others being
+// their conjugates.
 // k1 = 0 is real itself (RB/2 + 1 rows), k1 = 1..RA/2 take RB rows each, so
 // the plane has about P/2 rows of P complex values.
 //
@@ -30,9 +29,9 @@
 // the barrier at its end.  Against the group layout it has no separation of
 // packed real rows (24 LDS permutes and as many extra LDS writes per row
 // pair), no 48-byte pieces of rows to load, no idle lanes in the groups and
-// half the plane, so that up to P = 120 two workgroups share a CU: 447 us per
-// 1,024 points against 546 at P = 144, 285 against 403 at P = 120, 105 against
-// 263 at P = 72 (the plan table in match_fft.hip has every size).
+// half the plane, so that up to P = 120 two workgroups share a CU: 449 us per
+// 1,024 points against 541 at P = 144, 294 against 405 at P = 120, 107 against
+// 261 at P = 72 (the plan table in match_fft.hip has every size).
 // Measured and not taken: two channels as one complex signal over all ky
 // (twice the plane: at P >= 144 in two classes of ky with every volume row
 // read twice; 642 us at P = 144, 1206 at P = 192); loads of two or three
@@ -49,17 +48,27 @@ namespace cfog {
 
 constexpr int gcd_of(int a, int b) { return b ? gcd_of(b, a % b) : a; }
 
+// Offsets K per axis that a side takes: those whose K x K correlation the group
+// layout has room for behind the rows of its inverse's row pairs.
+constexpr bool offsets_fit(int P, int K) { return K * K <= 2 * (P - 2 * ((K + 1) / 2)) * (P / 2 + 1); }
+constexpr int max_offsets(int P) {
+  int K = 1;
+  while (offsets_fit(P, K + 2)) K += 2;
+  return K;
+}
+
 // PF: y1 items of a thread whose loads are issued during the x2 phase before.
 // WPE: waves per SIMD that the registers are held to.
 // Coprime R1, R2 use the prime-factor map (DftPfa in dft.hpp): no twiddles
 // between the x stages.  Column x = (R2 a + R1 b) mod P of the plane is then
 // kept at position a R2 + b, so that the accesses are those of the
 // common-factor case, where position and column are the same.
-template <int P_, int R1_, int R2_, int RA_, int RB_, int NT_, int PF_ = 0, int WPE_ = 0>
+template <int P_, int R1_, int R2_, int RA_, int RB_, int I1_, int I2_, int NT_, int PF_ = 0, int WPE_ = 0>
 struct LaneCfg {
-  static constexpr int P = P_, R1 = R1_, R2 = R2_, RA = RA_, RB = RB_, NT = NT_, PF = PF_;
+  static constexpr int P = P_, R1 = R1_, R2 = R2_, RA = RA_, RB = RB_, I1 = I1_, I2 = I2_, NT = NT_, PF = PF_;
   static constexpr int WPE = WPE_ ? WPE_ : (NT + 255) / 256;  // waves per SIMD the registers must allow
-  static_assert(P == R1 * R2 && P == RA * RB, "factors");
+  static_assert(P == R1 * R2 && P == RA * RB && P == I1 * I2, "factors");
+  static constexpr int PH = P / 2 + 1;
   static_assert(NT % 64 == 0 && NT <= 1024, "bad workgroup size");
   static constexpr bool PFA = gcd_of(R1, R2) == 1;
   static constexpr int LD = P | 1;
@@ -71,44 +80,47 @@ struct LaneCfg {
   static constexpr int KS2 = (ROWS * R1 + NT - 1) / NT;  // x2 items per thread
   static constexpr int NW = NT / 64;
   static_assert(KS2 <= 8, "accumulators");
-  static constexpr int NTW = KH * RB + (PFA ? 0 : P);
-  // plane, twiddles, column positions, the surface's rows, argmin scratch
+  // the inverse (lane_inverse): whether its DC and Nyquist columns are one
+  // complex column, its row pairs at the largest K the side takes, and the
+  // items of a thread
+  static constexpr bool PACK = P == 120 || P == 192;
+  static constexpr int NCOL = PACK ? P / 2 : PH;
+  static constexpr int MAXK = max_offsets(P);
+  static constexpr int KP2 = ((MAXK + 1) / 2 * I2 + NT - 1) / NT;
+  static constexpr int LDP = P | 1;
+  static_assert(P * PH <= ROWS * LD && (MAXK + 1) / 2 * LDP + (MAXK * MAXK + 1) / 2 <= ROWS * LD, "inverse in the plane");
+  static constexpr int NTW = KH * RB + (PFA ? 0 : P) + I1;
+  // plane, twiddles, column positions, argmin scratch
   static constexpr size_t LDS =
-      (sizeof(float2) * ((size_t)ROWS * LD + NTW) + 2 * sizeof(short) * P + 15) / 16 * 16 + sizeof(ArgminState) * NW;
+      (sizeof(float2) * ((size_t)ROWS * LD + NTW) + sizeof(short) * P + 15) / 16 * 16 + sizeof(ArgminState) * NW;
   static_assert(LDS <= kMaxLds, "LDS");
 };
 
 // The tables of a plan, formed at compile time and copied to LDS by each
-// workgroup (forming them there took a small call's workgroups 2 us).
+// workgroup.
 template <class C>
 struct LaneTables {
-  float2 tw[C::NTW];          // y twiddles W_P^{k1 j} at (k1 - 1) RB + j, then x twiddles W_P^{k j} at k R2 + j
-  unsigned short pos[C::P];   // position of column x in the plane
-  unsigned short row[C::P];   // offset in floats / 2 | component << 15 of the surface's row u_y (lane_inverse)
+  float2 tw[C::NTW];         // y twiddles W_P^{k1 j} at (k1 - 1) RB + j, x twiddles W_P^{k j} at k R2 + j, W_P^k, k < I1
+  unsigned short pos[C::P];  // position of column x in the plane
 };
 
 template <class C>
 constexpr LaneTables<C> make_lane_tables() {
   LaneTables<C> t{};
+  int n = 0;
+  auto put = [&](int e) {
+    t.tw[n].x = (float)cos2pi(e, C::P);
+    t.tw[n++].y = (float)-sin2pi(e, C::P);
+  };
   for (int k = 1; k <= C::KH; ++k)
-    for (int j = 0; j < C::RB; ++j) {
-      t.tw[(k - 1) * C::RB + j].x = (float)cos2pi(k * j, C::P);
-      t.tw[(k - 1) * C::RB + j].y = (float)-sin2pi(k * j, C::P);
-    }
+    for (int j = 0; j < C::RB; ++j) put(k * j);
   if (!C::PFA)
     for (int k = 0; k < C::R1; ++k)
-      for (int j = 0; j < C::R2; ++j) {
-        t.tw[C::KH * C::RB + k * C::R2 + j].x = (float)cos2pi(k * j, C::P);
-        t.tw[C::KH * C::RB + k * C::R2 + j].y = (float)-sin2pi(k * j, C::P);
-      }
+      for (int j = 0; j < C::R2; ++j) put(k * j);
+  for (int k = 0; k < C::I1; ++k) put(k);
   const int ta = inv_mod(C::R2 % C::R1, C::R1), tb = inv_mod(C::R1 % C::R2, C::R2);
-  for (int x = 0; x < C::P; ++x) {
+  for (int x = 0; x < C::P; ++x)
     t.pos[x] = (unsigned short)(C::PFA ? (x * ta) % C::R1 * C::R2 + (x * tb) % C::R2 : x);
-    // u_y = n2 + RB n1; the values of one n2 share the slots of its column
-    const int n1 = x / C::RB, n2 = x % C::RB;
-    const int slot = n1 == 0 ? n2 / 2 : C::ROW1 + (n1 - 1) / 2 * C::RB + n2, part = n1 == 0 ? n2 % 2 : (n1 - 1) % 2;
-    t.row[x] = (unsigned short)(slot | part << 15);
-  }
   return t;
 }
 
@@ -276,84 +288,160 @@ __device__ __forceinline__ void lane_x2(const float2* X, Sink&& sink) {
   });
 }
 
-// The inverse of the accumulators, weighted, for the columns u_x < K.  Ends
-// before the closing barrier.
+// The inputs of a stage-2 DFT of the inverse: w[b] = get(b) W^{+k1 b}, the
+// powers by recurrence from t1 = W^{-k1}.
+template <int R2, class Get>
+__device__ __forceinline__ void inverse_stage2(float2 (&w)[R2], float2 t1, Get&& get) {
+  t1.y = -t1.y;
+  float2 t = t1;
+  w[0] = get(0);
+#pragma unroll
+  for (int b = 1; b < R2; ++b) {
+    if (b > 1) t = cmul(t, t1);
+    w[b] = cmul(get(b), t);
+  }
+}
+
+// The inverse of the accumulators: returns the correlation as [u_y K + u_x], in
+// the plane.
+//
+// Its order of operations is the group layout's (match_fft.hip: columns
+// kx <= P/2 in two stages of I1 I2, then two real rows per complex FFT), and
+// not the one that would suit the plane best.  All K x K values are close to
+// their mean, which enters in the last stages, so it is the roundings there
+// that decide between offsets whose SSDs are equal to rounding: with another
+// order, 8 of 135,000 points of ordinary scenes returned another offset than
+// the group layout does.
 template <class C>
-__device__ __forceinline__ void lane_inverse(float2* X, float2 (&acc)[C::KS2][C::R2], const float2* twy,
-                                             const float2* twx, const unsigned short* pos, int K) {
-  constexpr int R1 = C::R1, R2 = C::R2, RA = C::RA, RB = C::RB, LD = C::LD, NT = C::NT, ROWS = C::ROWS;
-  constexpr int KH = C::KH, ROW1 = C::ROW1;
-  auto conj_tw = [](float2 t) { return make_float2(t.x, -t.y); };
+__device__ __forceinline__ const float* lane_inverse(float2* X, float2 (&acc)[C::KS2][C::R2], const float2* twi, int K) {
+  constexpr int P = C::P, PH = C::PH, R1 = C::R1, R2 = C::R2, I1 = C::I1, I2 = C::I2, NT = C::NT;
+  constexpr int RA = C::RA, RB = C::RB, ROWS = C::ROWS, ROW1 = C::ROW1, KH = C::KH, LDP = C::LDP;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));  // no index of the inverse is kept across the channel loop
+  // the accumulators as the half plane X[ky][kx <= P/2] (Hermitian symmetry)
   static_for<0, C::KS2>([&](auto sI) {
     constexpr int s = decltype(sI)::value;
-    if constexpr (s > 0 && C::WPE > 2) __builtin_amdgcn_sched_barrier(0);
-    const int i = threadIdx.x + s * NT;
+    const int i = tid + s * NT;
     if (C::KS2 * NT == ROWS * R1 || i < ROWS * R1) {
       const int k1 = i / ROWS, row = i - k1 * ROWS;
-      float2* p = X + row * LD + k1 * R2;
-      // rows whose -ky is a row too (or the row itself) count once
-      const bool once = row == 0 || (RB % 2 == 0 && row == RB / 2) || (RA % 2 == 0 && row >= ROW1 + (KH - 1) * RB);
-      const float w = once ? 1.0f / ((float)C::P * C::P) : 2.0f / ((float)C::P * C::P);
-      float2 v[R2];
-#pragma unroll
-      for (int k = 0; k < R2; ++k) v[k] = cscale(acc[s][k], w);
-      dft<R2, +1>(v);
-#pragma unroll
-      for (int n2 = 0; n2 < R2; ++n2) p[n2] = (C::PFA || n2 == 0) ? v[n2] : cmul(v[n2], conj_tw(twx[k1 * R2 + n2]));
+      const int q = row < ROW1 ? 0 : (row - ROW1) / RB + 1;
+      const int ky = row < ROW1 ? RA * row : q + RA * (row - ROW1 - (q - 1) * RB);
+      // rows whose -ky is a row too (or the row itself)
+      const bool once = row == 0 || (RB % 2 == 0 && row == RB / 2) || (RA % 2 == 0 && q == KH);
+      static_for<0, R2>([&](auto kI) {
+        constexpr int k2 = decltype(kI)::value;
+        int kx = k1 + R1 * k2;
+        if constexpr (C::PFA) {
+          constexpr int ta = inv_mod(R2 % R1, R1), tb = inv_mod(R1 % R2, R2);
+          kx = (R2 * ta * k1 + R1 * tb * k2) % P;
+        }
+        if (2 * kx <= P) X[ky * PH + kx] = acc[s][k2];
+        if (!once && (2 * kx >= P || kx == 0)) X[(P - ky) * PH + (kx ? P - kx : 0)] = make_float2(acc[s][k2].x, -acc[s][k2].y);
+      });
     }
   });
   __syncthreads();
+  // columns, in place: u_y = k1 + I1 k2 ends up in row k1 I2 + k2.  The DC and
+  // Nyquist columns are real: where PACK, they are the real and the imaginary
+  // part of one.
 #pragma unroll 1
-  for (int i = threadIdx.x; i < ROWS * R2; i += NT) {
-    const int n2 = i / ROWS, row = i - n2 * ROWS;
-    float2* p = X + row * LD + n2;
-    float2 v[R1];
+  for (int i = tid; i < C::NCOL * I2; i += NT) {
+    const int j = i / C::NCOL, kx = i - j * C::NCOL;
+    float2* col = X + j * PH + kx;
+    float2 v[I1];
 #pragma unroll
-    for (int k = 0; k < R1; ++k) v[k] = p[k * R2];
-    dft<R1, +1>(v);
+    for (int a = 0; a < I1; ++a) {
+      v[a] = col[a * I2 * PH];
+      if (C::PACK && kx == 0) {
+        const float2 n = col[a * I2 * PH + P / 2];
+        v[a] = make_float2(v[a].x - n.y, v[a].y + n.x);
+      }
+    }
+    dft<I1, +1>(v);
 #pragma unroll
-    for (int n1 = 0; n1 < R1; ++n1) p[n1 * R2] = v[n1];
+    for (int k = 0; k < I1; ++k) col[k * I2 * PH] = v[k];
   }
   __syncthreads();
-  const float inv = 1.0f / (float)K;
 #pragma unroll 1
-  for (int i = threadIdx.x; i < K * (KH + 1); i += NT) {
-    const int k1 = (int)(((float)i + 0.5f) * inv), ux = i - k1 * K, p = C::PFA ? pos[ux] : ux;
-    float2* col = X + (k1 ? ROW1 + (k1 - 1) * RB : 0) * LD + p;
-    float2 v[RB];
+  for (int i = tid; i < C::NCOL * I1; i += NT) {
+    const int k1 = i / C::NCOL, kx = i - k1 * C::NCOL;
+    float2* col = X + k1 * I2 * PH + kx;
+    float2 w[I2];
+    inverse_stage2<I2>(w, twi[k1], [&](int b) { return col[b * PH]; });
+    dft<I2, +1>(w);
 #pragma unroll
-    for (int b = 0; b < RB; ++b) v[b] = (b < ROW1 || k1) ? col[b * LD] : make_float2(0.f, 0.f);
-    dft<RB, +1>(v);
-    if (k1 == 0) {  // only the real parts count: two to a slot
-#pragma unroll
-      for (int t = 0; t < (RB + 1) / 2; ++t) col[t * LD] = make_float2(v[2 * t].x, 2 * t + 1 < RB ? v[2 * t + 1].x : 0.f);
-    } else {
-#pragma unroll
-      for (int n2 = 0; n2 < RB; ++n2) col[n2 * LD] = cmul(v[n2], conj_tw(twy[(k1 - 1) * RB + n2]));
+    for (int k2 = 0; k2 < I2; ++k2) {
+      if (C::PACK && kx == 0) {
+        col[k2 * PH] = make_float2(w[k2].x, 0.f);
+        col[k2 * PH + P / 2] = make_float2(w[k2].y, 0.f);
+      } else {
+        col[k2 * PH] = w[k2];
+      }
     }
   }
   __syncthreads();
+  // rows 2p and 2p + 1 as one complex row.  Once every thread holds its
+  // inputs, the stage-1 outputs go to the start of the plane, pair by pair, and
+  // the surface behind them.
+  const int npair = (K + 1) >> 1;
+  float2 v[C::KP2][I1];
+  static_for<0, C::KP2>([&](auto sI) {
+    constexpr int s = decltype(sI)::value;
+    const int i = tid + s * NT, p = i / I2, j = i - p * I2;
+    if (p < npair) {
+      const float2* r1 = X + (2 * p % I1 * I2 + 2 * p / I1) * PH;
+      const float2* r2 = X + ((2 * p + 1) % I1 * I2 + (2 * p + 1) / I1) * PH;
+      const bool has2 = 2 * p + 1 < K;
+#pragma unroll
+      for (int a = 0; a < I1; ++a) {
+        const int kx = j + I2 * a;
+        const bool lo = kx <= P / 2;
+        const int kk = lo ? kx : P - kx;
+        const float2 v1 = r1[kk];
+        const float2 v2 = has2 ? r2[kk] : make_float2(0.f, 0.f);
+        v[s][a] = lo ? make_float2(v1.x - v2.y, v1.y + v2.x) : make_float2(v1.x + v2.y, v2.x - v1.y);
+      }
+    }
+  });
+  __syncthreads();
+  static_for<0, C::KP2>([&](auto sI) {
+    constexpr int s = decltype(sI)::value;
+    const int i = tid + s * NT, p = i / I2, j = i - p * I2;
+    if (p < npair) {
+      float2* r = X + p * LDP + j;
+      dft<I1, +1>(v[s]);
+#pragma unroll
+      for (int k = 0; k < I1; ++k) r[k * I2] = v[s][k];
+    }
+  });
+  __syncthreads();
+  float* Cs = reinterpret_cast<float*>(X + npair * LDP);
+  const float norm = 1.0f / ((float)P * (float)P);
 #pragma unroll 1
-  for (int i = threadIdx.x; i < K * RB; i += NT) {
-    const int n2 = (int)(((float)i + 0.5f) * inv), ux = i - n2 * K, p = C::PFA ? pos[ux] : ux;
-    float* r0 = reinterpret_cast<float*>(X) + ((n2 >> 1) * LD + p) * 2 + (n2 & 1);
-    float2* col = X + (ROW1 + n2) * LD + p;
-    float2 v[RA];
-    v[0] = make_float2(*r0, 0.f);
+  for (int i = tid; i < npair * I1; i += NT) {
+    const int p = i / I1, k1 = i - p * I1;
+    const float2* r = X + p * LDP + k1 * I2;
+    float2 w[I2];
+    inverse_stage2<I2>(w, twi[k1], [&](int b) { return r[b]; });
+    dft<I2, +1>(w);
+    float* c = Cs + 2 * p * K + k1;
 #pragma unroll
-    for (int k = 1; k < RA; ++k) v[k] = k <= KH ? col[(k - 1) * RB * LD] : make_float2(0.f, 0.f);
-    dft<RA, +1>(v);
-    *r0 = v[0].x;
-#pragma unroll
-    for (int t = 0; t < KH; ++t) col[t * RB * LD] = make_float2(v[1 + 2 * t].x, 2 + 2 * t < RA ? v[2 + 2 * t].x : 0.f);
+    for (int k2 = 0; k2 < I2; ++k2) {
+      if (k1 + I1 * k2 < K) {
+        c[I1 * k2] = w[k2].x * norm;
+        if (2 * p + 1 < K) c[K + I1 * k2] = w[k2].y * norm;
+      }
+    }
   }
+  __syncthreads();
+  return Cs;
 }
 
 // Control point cpi of job jd over the channels [c0, c1): as match_one in
 // match_fft.hip.
 template <class C>
 __device__ __forceinline__ void lane_match_one(const MatchJob& jd, int cpi, float2* X, const float2* twy,
-                                               const float2* twx, const unsigned short* pos, const unsigned short* rows,
+                                               const float2* twx, const float2* twi, const unsigned short* pos,
                                                ArgminState* red, int c0, int c1, float* __restrict__ part, int g) {
   constexpr int NT = C::NT, KS2 = C::KS2, R2 = C::R2;
   const int4 cp = jd.cps[cpi];
@@ -363,6 +451,7 @@ __device__ __forceinline__ void lane_match_one(const MatchJob& jd, int cpi, floa
     if (g == 0) oob_result<NT>(jd, cpi);
     return;
   }
+  const float* Cs;
   {
     const size_t planeA = (size_t)jd.hA * jd.wA, planeB = (size_t)jd.hB * jd.wB;
     const float* tA = jd.volA + c0 * planeA + (size_t)bx.ty0 * jd.wA + bx.tx0;
@@ -412,22 +501,13 @@ __device__ __forceinline__ void lane_match_one(const MatchJob& jd, int cpi, floa
       });
       __syncthreads();
     }
-    lane_inverse<C>(X, acc, twy, twx, pos, K);
-    __syncthreads();
+    Cs = lane_inverse<C>(X, acc, twi, K);
   }
-  const float* Xf = reinterpret_cast<const float*>(X);
-  auto corr = [&](int, int uy, int ux) -> float {
-    const int row = rows[uy];
-    return Xf[((row & 0x7fff) * C::LD + (C::PFA ? pos[ux] : ux)) * 2 + (row >> 15)];
-  };
   if (part) {
-    for (int i = threadIdx.x; i < K * K; i += NT) {
-      const int uy = i / K;
-      stg(part + i, corr(i, uy, i - uy * K));
-    }
+    for (int i = threadIdx.x; i < K * K; i += NT) stg(part + i, Cs[i]);
     return;
   }
-  ssd_epilogue<NT>(jd, cpi, bx.tx0, bx.ty0, bx.sx0, bx.sy0, corr, red);
+  ssd_epilogue<NT>(jd, cpi, bx.tx0, bx.ty0, bx.sx0, bx.sy0, [&](int i, int, int) { return Cs[i]; }, red);
 }
 
 // The kernel: arguments and work items as match_fft_kernel.
@@ -438,14 +518,11 @@ __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::WPE)))
   float2* X = smem;
   float2* tw = X + (size_t)C::ROWS * C::LD;
   const float2* twx = tw + C::KH * C::RB;
+  const float2* twi = tw + C::NTW - C::I1;
   unsigned short* pos = reinterpret_cast<unsigned short*>(tw + C::NTW);
-  unsigned short* rows = pos + C::P;
   ArgminState* red = reinterpret_cast<ArgminState*>(reinterpret_cast<char*>(smem) + C::LDS - sizeof(ArgminState) * C::NW);
   for (int i = threadIdx.x; i < C::NTW; i += C::NT) tw[i] = kLaneTables<C>.tw[i];
-  for (int i = threadIdx.x; i < C::P; i += C::NT) {
-    pos[i] = kLaneTables<C>.pos[i];
-    rows[i] = kLaneTables<C>.row[i];
-  }
+  for (int i = threadIdx.x; i < C::P; i += C::NT) pos[i] = kLaneTables<C>.pos[i];
   const int n_items = split_items(n_tasks, sp);
   for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
     __syncthreads();  // tables ready / previous item's reduction done
@@ -464,7 +541,7 @@ __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::WPE)))
       cpi = tk.y;
     }
     float* part = G > 1 ? sp.part + (size_t)(it - sp.n_whole) * sp.slot : nullptr;
-    lane_match_one<C>(jd, cpi, X, tw, twx, pos, rows, red, g * jd.m / G, (g + 1) * jd.m / G, part, g);
+    lane_match_one<C>(jd, cpi, X, tw, twx, twi, pos, red, g * jd.m / G, (g + 1) * jd.m / G, part, g);
   }
 }
 

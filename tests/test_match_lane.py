@@ -13,7 +13,7 @@ from paper_1808_06194_amd import cfog, synth
 from tests import parity
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-SIDES = (60, 64, 72, 80, 90, 96, 100, 108, 120, 128, 144, 150, 160, 180, 192)
+SIDES = (60, 64, 72, 80, 90, 96, 100, 108, 120, 144, 160, 192)
 
 
 def test_rdft_codelets_host_build(tmp_path):
@@ -27,19 +27,18 @@ def test_rdft_codelets_host_build(tmp_path):
     assert r.returncode == 0, r.stdout
 
 
+def _takes(P, N, r):
+    """A side holds the window, a template of at most 134 rows at 144, and the
+    K x K correlation behind the rows of the group layout's inverse."""
+    K = 2 * r + 1
+    return P >= N + 2 * r and N <= (134 if P == 144 else P) and K * K <= 2 * (P - 2 * ((K + 1) // 2)) * (P // 2 + 1)
+
+
 def test_sizes_taken():
-    """A template side and radius are taken where a 192-point side holds the
-    window and, behind the rows of the inverse's pairs, the K x K correlation;
-    the side is the smallest that holds the window."""
-    sides = (16, 24, 32, 40, 48) + SIDES
     for N in range(1, 200):
         for r in range(0, 100):
-            K, ws = 2 * r + 1, N + 2 * r
-            taken = ws <= 192 and K * K <= 2 * (192 - 2 * ((K + 1) // 2)) * 97
-            P = cfog.fft_size(N, r)
-            assert (P > 0) == taken, (N, r, P)
-            if P >= 60:
-                assert P == next(s for s in sides[5:] if s >= ws), (N, r, P)
+            fit = [P for P in (16, 24, 32, 40, 48) + SIDES if _takes(P, N, r)]
+            assert cfog.fft_size(N, r) == (fit[0] if fit else 0), (N, r)
 
 
 def _edges():
@@ -48,10 +47,12 @@ def _edges():
         r = 3 + P // 16
         yield P, P - 2 * r, r, 9                       # the window fills the side
         yield P, prev + 1 - 2 * (r // 2), r // 2, 2     # the smallest window of the side
+        r = max(r for r in range(P // 2) if _takes(P, 1, r))
+        yield P, min(P - 2 * r, 134), r, 3              # the most offsets
         prev = P
     yield 60, 60, 0, 1                                  # one offset, one channel
-    yield 72, 7, 31, 3                                  # a small template in a large window
     yield 144, 1, 40, 1                                 # a template of one pixel
+    yield 144, 134, 5, 2                                # the most template rows
     yield 192, 191, 0, 5
 
 
@@ -84,6 +85,13 @@ def test_every_side_at_its_edges(P, N, r, m):
                 E1, E2 = O.energies(DA, DB, cp, N, r)
                 parity.check_point(k, res, O.ssd_surface_direct(DA, DB, cp, N, r), E1, E2, r, s[k])
             assert res["status"][4] == cfog.CP_OUT_OF_BOUNDS and np.isnan(s[4]).all()
+        # more points than are resident at once: the smaller workgroups, the same roundings
+        many = torch.from_numpy(np.tile(cps, (700, 1))).cuda()
+        surf = torch.full((len(many), K, K), -1.0, device="cuda")
+        cfog.match_batch([cfog.Job(vA, sA, vB, sB, many, N, r, surfaces=surf)], m=m,
+                         flags=cfog.PATH_PLAIN_FFT | cfog.NO_SPLIT)
+        torch.cuda.synchronize()
+        assert np.array_equal(surf.cpu().numpy(), np.tile(s, (700, 1, 1)), equal_nan=True)
     finally:
         cfog.set_plan(N, r, 0)
 
