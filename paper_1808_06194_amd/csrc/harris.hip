@@ -3,16 +3,26 @@
 // on each cell is read and its k pixels with the largest Harris response
 // become feature points, which are the control points the matcher takes.
 //
-// One workgroup per chip, everything in LDS (two chips per CU); lanes map to
-// chip columns and the four waves take every fourth row, so no index is
-// divided; the Gaussian radius is a template parameter (unrolled taps):
+// One workgroup per chip, its arrays in LDS (three chips per CU); the Gaussian
+// radius is a template parameter (unrolled taps):
 //   1. the chip (clipped to the image);
 //   2. gradients by [-1, 0, 1] with the chip's borders replicated;
 //   3. the structure tensor products gx^2, gx gy, gy^2 (formed on the fly)
 //      smoothed by a normalised Gaussian (horizontal then vertical pass,
 //      chip borders replicated) and the response R = det - kappa trace^2;
-//   4. k rounds of a workgroup argmax (largest R, ties to the smallest
-//      row-major index), each marking its winner as taken.
+//   4. each wave's k largest responses (ties to the smallest row-major index),
+//      and of these 4 k candidates the first k.
+//
+// What bounds it: LDS traffic and the vector units, about evenly; the image
+// itself is read once.  So a thread takes four adjacent columns through the
+// gradients and the horizontal pass (16-byte LDS accesses, the products of
+// 4 + 2 R positions formed once for four sums) and 16 rows of a column through
+// the vertical pass (16 + 2 R reads instead of 16 (2 R + 1)), and the responses
+// stay in its registers: a round of the maximum is a wave's reduction without a
+// barrier, and the candidates are ranked all at once.
+//   64 x 64 chips of a 4096 x 4096 image, 4 points each, sigma 1: 175 us
+//   with a thread per pixel in every pass and k workgroup reductions over the
+//   responses in LDS, 80 us so.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <limits.h>
@@ -36,29 +46,46 @@ struct HarrisArgs {
   float* resp;
 };
 
-constexpr int HR_LD = HR_MAX_CHIP;  // LDS row stride of every chip array
 constexpr int HR_NW = HR_NT / 64;
+constexpr int HR_RPT = HR_MAX_CHIP / HR_NW;       // rows of a thread's column in the vertical pass
+constexpr int HR_LDC = HR_MAX_CHIP;               // LDS row stride of the chip, later of sum gy^2
+constexpr int HR_QR = HR_NT / (HR_MAX_CHIP / 4);  // rows that the workgroup covers with a quad of columns per thread
 
-// Dynamic LDS: five 64 x 64 arrays (80 KB, so two chips share a CU; the
-// argmax scratch lives in a dead array, as any static LDS would push a
-// workgroup past half of the CU's 160 KB).  The chip is dead once the
-// gradients exist and shares storage with the first smoothed product; the
-// response reuses gx.
-static size_t harris_lds_bytes() { return (size_t)5 * HR_LD * HR_LD * sizeof(float); }
+// Gradients (then sum gx^2 and sum gx gy) have the Gaussian's replicated
+// columns on both sides: PAD, a multiple of 4.
+template <int R>
+struct HarrisLds {
+  static constexpr int PAD = (R + 3) / 4 * 4;
+  static constexpr int LD = HR_MAX_CHIP + 2 * PAD;
+};
+template <int R>
+static size_t harris_lds_bytes(int chip) {
+  // the candidates (HR_NW k values and indices) reuse the arrays
+  return std::max((size_t)(2 * HarrisLds<R>::LD + HR_LDC) * chip, (size_t)HR_NW * HR_MAX_K * 2) * sizeof(float);
+}
+
+// The largest value of the wave, in every lane.
+__device__ __forceinline__ float wave_max(float v) {
+#define HR_DPP_MAX(ctrl, rows)                                                                                     \
+  v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, v),                   \
+                                                                     __builtin_bit_cast(int, v), ctrl, rows, 0xf, false)))
+  HR_DPP_MAX(0x111, 0xf);  // row_shr:1
+  HR_DPP_MAX(0x112, 0xf);
+  HR_DPP_MAX(0x114, 0xf);
+  HR_DPP_MAX(0x118, 0xf);
+  HR_DPP_MAX(0x142, 0xa);  // row_bcast:15
+  HR_DPP_MAX(0x143, 0xc);  // row_bcast:31
+#undef HR_DPP_MAX
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
+}
 
 template <int R>
 __global__ __launch_bounds__(HR_NT) void harris_grid_kernel(HarrisArgs a) {
-  extern __shared__ float hsm[];
-  constexpr int CC = HR_LD * HR_LD;
-  float* gx = hsm;
-  float* gy = gx + CC;
-  float* ta = gy + CC;
-  float* tb = ta + CC;
-  float* tc = tb + CC;
-  float* img = ta;  // read only by the gradient pass
-  float* Rv = gx;   // written by the vertical pass, after the last gx read
-  float* bestv = tb;                                 // HR_NW values, after the vertical pass
-  int* besti = reinterpret_cast<int*>(tb + HR_NW);   // their indices
+  extern __shared__ __attribute__((aligned(16))) float hsm[];
+  constexpr int PAD = HarrisLds<R>::PAD, LD = HarrisLds<R>::LD, QN = 4 + 2 * PAD;
+  float* gx = hsm + PAD;  // later sum gx^2
+  float* gy = gx + LD * a.chip;  // later sum gx gy
+  float* img = hsm + 2 * LD * a.chip;  // later sum gy^2
   const int cell = blockIdx.x, ci = cell / a.n, cj = cell - ci * a.n;
   // chip of cell (ci, cj): centred at ((2 cj + 1) W / 2n, (2 ci + 1) H / 2n), clipped
   const int cy = (int)(((int64_t)(2 * ci + 1) * a.H) / (2 * a.n));
@@ -71,147 +98,207 @@ __global__ __launch_bounds__(HR_NT) void harris_grid_kernel(HarrisArgs a) {
 #pragma unroll
   for (int j = 0; j <= R; ++j) wt[j] = a.w[j];
 
-  constexpr int RPW = HR_LD / HR_NW;  // rows per wave (the row loops below are unrolled over them)
   {
     // all loads of the chip issued before the first LDS store
-    float v[RPW];
+    float v[HR_RPT];
     const float* src = a.img + (int64_t)y0 * a.stride + x0 + x;
 #pragma unroll
-    for (int t = 0; t < RPW; ++t) {
+    for (int t = 0; t < HR_RPT; ++t) {
       const int y = wv + HR_NW * t;
       if (col && y < h) v[t] = src[(int64_t)y * a.stride];
     }
 #pragma unroll
-    for (int t = 0; t < RPW; ++t) {
+    for (int t = 0; t < HR_RPT; ++t) {
       const int y = wv + HR_NW * t;
-      if (col && y < h) img[y * HR_LD + x] = v[t];
+      if (col && y < h) img[y * HR_LDC + x] = v[t];
     }
   }
   __syncthreads();
-  const int xp = min(x + 1, w - 1), xm = max(x - 1, 0);
+  // gradients: columns x4 .. x4 + 3 of the rows yq + HR_QR t; a row is one
+  // wave's (the sixteen lanes of its quads) until the vertical pass
+  const int x4 = (threadIdx.x & 15) * 4, yq = threadIdx.x >> 4;
+  const int xl = max(x4 - 1, 0), xr = min(x4 + 4, w - 1);
+  const bool last = x4 <= w - 1 && w - 1 < x4 + 4;  // the quad of the chip's last column
 #pragma unroll
-  for (int t = 0; t < RPW; ++t) {
-    const int y = wv + HR_NW * t;
-    if (col && y < h) {
-      const float* row = img + y * HR_LD;
-      gx[y * HR_LD + x] = row[xp] - row[xm];
-      gy[y * HR_LD + x] = img[min(y + 1, h - 1) * HR_LD + x] - img[max(y - 1, 0) * HR_LD + x];
-    }
-  }
-  __syncthreads();
-  // horizontal pass of the three products (columns clamped to the chip)
-  int xs[2 * R + 1];
+  for (int t = 0; t < HR_MAX_CHIP / HR_QR; ++t) {
+    const int y = yq + HR_QR * t;
+    if (x4 < w && y < h) {
+      const float* row = img + y * HR_LDC;
+      const float4 c4 = *reinterpret_cast<const float4*>(row + x4);
+      const float4 d4 = *reinterpret_cast<const float4*>(img + min(y + 1, h - 1) * HR_LDC + x4);
+      const float4 u4 = *reinterpret_cast<const float4*>(img + max(y - 1, 0) * HR_LDC + x4);
+      const float c[6] = {row[xl], c4.x, c4.y, c4.z, c4.w, row[xr]};
+      float g[4], e[4] = {d4.x - u4.x, d4.y - u4.y, d4.z - u4.z, d4.w - u4.w};
 #pragma unroll
-  for (int j = -R; j <= R; ++j) xs[j + R] = min(max(x + j, 0), w - 1);
+      for (int i = 0; i < 4; ++i) g[i] = (x4 + i < w - 1 ? c[i + 2] : c[i + 1]) - c[i];
+      float* px = gx + y * LD + x4;
+      float* py = gy + y * LD + x4;
+      if (PAD > 0 && last) {  // the last column again, to the quad's end and past it
 #pragma unroll
-  for (int t = 0; t < RPW; ++t) {
-    const int y = wv + HR_NW * t;
-    if (col && y < h) {
-      const float* rx = gx + y * HR_LD;
-      const float* ry = gy + y * HR_LD;
-      float sa = 0.f, sb = 0.f, sc = 0.f;
+        for (int i = 1; i < 4; ++i)
+          if (x4 + i > w - 1) {
+            g[i] = g[i - 1];
+            e[i] = e[i - 1];
+          }
 #pragma unroll
-      for (int j = -R; j <= R; ++j) {
-        const float u = rx[xs[j + R]], v = ry[xs[j + R]], wj = wt[j < 0 ? -j : j];
-        sa = fmaf(wj, u * u, sa);
-        sb = fmaf(wj, u * v, sb);
-        sc = fmaf(wj, v * v, sc);
+        for (int p = 4; p < 4 + PAD; p += 4) {
+          *reinterpret_cast<float4*>(px + p) = make_float4(g[3], g[3], g[3], g[3]);
+          *reinterpret_cast<float4*>(py + p) = make_float4(e[3], e[3], e[3], e[3]);
+        }
       }
-      ta[y * HR_LD + x] = sa;
-      tb[y * HR_LD + x] = sb;
-      tc[y * HR_LD + x] = sc;
-    }
-  }
-  __syncthreads();
-  // vertical pass (rows clamped to the chip) and the response
+      if (PAD > 0 && x4 == 0) {
 #pragma unroll
-  for (int t = 0; t < RPW; ++t) {
-    const int y = wv + HR_NW * t;
-    if (col && y < h) {
-      float sa = 0.f, sb = 0.f, sc = 0.f;
-#pragma unroll
-      for (int j = -R; j <= R; ++j) {
-        const int q = min(max(y + j, 0), h - 1) * HR_LD + x;
-        const float wj = wt[j < 0 ? -j : j];
-        sa = fmaf(wj, ta[q], sa);
-        sb = fmaf(wj, tb[q], sb);
-        sc = fmaf(wj, tc[q], sc);
+        for (int p = 4; p <= PAD; p += 4) {
+          *reinterpret_cast<float4*>(px - p) = make_float4(g[0], g[0], g[0], g[0]);
+          *reinterpret_cast<float4*>(py - p) = make_float4(e[0], e[0], e[0], e[0]);
+        }
       }
-      const float tr = sa + sc;
-      Rv[y * HR_LD + x] = sa * sc - sb * sb - a.kappa * tr * tr;
+      *reinterpret_cast<float4*>(px) = make_float4(g[0], g[1], g[2], g[3]);
+      *reinterpret_cast<float4*>(py) = make_float4(e[0], e[1], e[2], e[3]);
     }
   }
   __syncthreads();
+  // horizontal pass of the three products, in place
+#pragma unroll
+  for (int t = 0; t < HR_MAX_CHIP / HR_QR; ++t) {
+    const int y = yq + HR_QR * t;
+    const bool in = x4 < w && y < h;
+    float4 sa, sb, sc;
+    if (in) {
+      float uu[QN], uv[QN], vv[QN];
+#pragma unroll
+      for (int q = 0; q < QN; q += 4) {
+        const float4 u = *reinterpret_cast<const float4*>(gx + y * LD + x4 - PAD + q);
+        const float4 v = *reinterpret_cast<const float4*>(gy + y * LD + x4 - PAD + q);
+        const float us[4] = {u.x, u.y, u.z, u.w}, vs[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          uu[q + i] = us[i] * us[i];
+          uv[q + i] = us[i] * vs[i];
+          vv[q + i] = vs[i] * vs[i];
+        }
+      }
+      auto taps = [&](const float (&p)[QN]) {
+        float s[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = -R; j <= R; ++j)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) s[i] = fmaf(wt[j < 0 ? -j : j], p[PAD + i + j], s[i]);
+        return make_float4(s[0], s[1], s[2], s[3]);
+      };
+      sa = taps(uu);
+      sb = taps(uv);
+      sc = taps(vv);
+    }
+    // the row's sixteen lanes have read it
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (in) {
+      *reinterpret_cast<float4*>(gx + y * LD + x4) = sa;
+      *reinterpret_cast<float4*>(gy + y * LD + x4) = sb;
+      *reinterpret_cast<float4*>(img + y * HR_LDC + x4) = sc;
+    }
+  }
+  __syncthreads();
+  // vertical pass (rows clamped to the chip) and the response, of column x and
+  // the rows yv .. yv + HR_RPT - 1; what is outside the chip is NaN
+  const int yv = wv * HR_RPT;
+  float rv[HR_RPT];
+  {
+    const int xc = min(x, w - 1);
+    auto taps = [&](const float* p, int ld, float (&s)[HR_RPT]) {
+      float win[HR_RPT + 2 * R];
+#pragma unroll
+      for (int t = 0; t < HR_RPT + 2 * R; ++t) win[t] = p[min(max(yv + t - R, 0), h - 1) * ld + xc];
+#pragma unroll
+      for (int t = 0; t < HR_RPT; ++t) {
+        s[t] = 0.f;
+#pragma unroll
+        for (int j = -R; j <= R; ++j) s[t] = fmaf(wt[j < 0 ? -j : j], win[t + j + R], s[t]);
+      }
+    };
+    float sa[HR_RPT], sb[HR_RPT], sc[HR_RPT];
+    taps(gx, LD, sa);
+    taps(gy, LD, sb);
+    taps(img, HR_LDC, sc);
+#pragma unroll
+    for (int t = 0; t < HR_RPT; ++t) {
+      const float tr = sa[t] + sc[t];
+      const float r = sa[t] * sc[t] - sb[t] * sb[t] - a.kappa * tr * tr;
+      rv[t] = col && yv + t < h ? r : NAN;
+    }
+  }
+  __syncthreads();  // the arrays are dead: the candidates reuse them
 
-  const int lane = x;
+  // this wave's k largest in order, as (value, row-major index); INT_MAX: none
+  // left.  A taken response becomes NaN, which never wins.
+  float* cv = hsm;
+  int* cidx = reinterpret_cast<int*>(hsm + HR_NW * a.k);
+  float bv;
+  int bt;
+  auto scan = [&] {
+    bv = -INFINITY;
+    bt = HR_RPT;
+#pragma unroll
+    for (int t = 0; t < HR_RPT; ++t)
+      if (rv[t] > bv) {
+        bv = rv[t];
+        bt = t;
+      }
+  };
+  scan();
   for (int q = 0; q < a.k; ++q) {
-    float bv = -INFINITY;
-    int bi = INT_MAX;
+    const float mx = wave_max(bv);
+    int bi = bt < HR_RPT && bv == mx ? (yv + bt) * w + x : INT_MAX;
+    const int mine = bi;
+    const uint64_t tied = __ballot(bi != INT_MAX);
+    if (tied & (tied - 1)) {  // several columns hold it: the smallest index
 #pragma unroll
-    for (int t = 0; t < RPW; ++t) {  // increasing row-major index per thread
-      const int y = wv + HR_NW * t;
-      if (col && y < h) {
-        const float v = Rv[y * HR_LD + x];
-        if (v > bv) {  // taken pixels hold NaN and never win
-          bv = v;
-          bi = y * w + x;
-        }
-      }
+      for (int o = 32; o > 0; o >>= 1) bi = min(bi, __shfl_xor(bi, o, 64));
+    } else if (tied) {
+      bi = __builtin_amdgcn_readlane(bi, __builtin_ctzll(tied));
     }
+    if (mine == bi && bi != INT_MAX) {
+      cv[wv * a.k + q] = bv;
+      cidx[wv * a.k + q] = bi;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      const float ov = __shfl_xor(bv, o, 64);
-      const int oi = __shfl_xor(bi, o, 64);
-      if (ov > bv || (ov == bv && oi < bi)) {
-        bv = ov;
-        bi = oi;
-      }
+      for (int t = 0; t < HR_RPT; ++t)
+        if (t == bt) rv[t] = NAN;
+      scan();
     }
-    if (lane == 0) {
-      bestv[wv] = bv;
-      besti[wv] = bi;
+    if (!tied) {
+      if (x == 0) cidx[wv * a.k + q] = INT_MAX;
     }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      for (int u = 1; u < HR_NW; ++u)
-        if (bestv[u] > bv || (bestv[u] == bv && besti[u] < bi)) {
-          bv = bestv[u];
-          bi = besti[u];
-        }
-      const int o = cell * a.k + q;
-      if (bi != INT_MAX) {
-        const int yy = bi / w, xx = bi - yy * w;
-        a.cps[o] = cfog_cp{x0 + xx, y0 + yy, x0 + xx, y0 + yy};
-        if (a.resp) a.resp[o] = bv;
-        Rv[yy * HR_LD + xx] = NAN;
-      } else {  // no finite response left (a non-finite chip)
-        a.cps[o] = cfog_cp{-1, -1, -1, -1};
-        if (a.resp) a.resp[o] = NAN;
-      }
-    }
-    __syncthreads();
   }
-}
-
-template <int R>
-static int set_harris_attr() {
-  return hipFuncSetAttribute((const void*)harris_grid_kernel<R>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)harris_lds_bytes()) == hipSuccess
-             ? 0
-             : -2;
-}
-
-int init_harris_attributes() {
-  if (set_harris_attr<0>() || set_harris_attr<1>() || set_harris_attr<2>() || set_harris_attr<3>() ||
-      set_harris_attr<4>() || set_harris_attr<5>() || set_harris_attr<6>() || set_harris_attr<7>() ||
-      set_harris_attr<8>())
-    return -2;
-  return 0;
+  __syncthreads();
+  // the place of each candidate among all
+  const int nc = HR_NW * a.k;
+  if ((int)threadIdx.x < nc) {
+    const int i = threadIdx.x, bi = cidx[i];
+    const float v = cv[i];
+    int before = 0, valid = 0;
+    for (int u = 0; u < nc; ++u) {
+      const int oi = cidx[u];
+      const float ov = cv[u];
+      valid += oi != INT_MAX;
+      before += oi != INT_MAX && (ov > v || (ov == v && oi < bi));
+    }
+    if (bi != INT_MAX && before < a.k) {
+      const int o = cell * a.k + before, yy = bi / w, xx = bi - yy * w;
+      a.cps[o] = cfog_cp{x0 + xx, y0 + yy, x0 + xx, y0 + yy};
+      if (a.resp) a.resp[o] = v;
+    }
+    if (i < a.k && i >= valid) {  // no finite response left (a non-finite chip)
+      const int o = cell * a.k + i;
+      a.cps[o] = cfog_cp{-1, -1, -1, -1};
+      if (a.resp) a.resp[o] = NAN;
+    }
+  }
 }
 
 template <int R>
 static int launch_harris(const HarrisArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(harris_grid_kernel<R>, dim3(a.n * a.n), dim3(HR_NT), harris_lds_bytes(), st, a);
+  hipLaunchKernelGGL(harris_grid_kernel<R>, dim3(a.n * a.n), dim3(HR_NT), harris_lds_bytes<R>(a.chip), st, a);
   return hipGetLastError() == hipSuccess ? 0 : -2;
 }
 

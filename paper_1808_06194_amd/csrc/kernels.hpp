@@ -96,7 +96,6 @@ const FftPlan* wide_plan();
 // safe to call from several host threads).  0 on success.
 int init_kernel_attributes();
 int init_direct_attributes();
-int init_harris_attributes();
 int init_outlier_attributes();
 // Workgroups of this plan that fit the device at once.
 int plan_slots(const FftPlan* p, int num_cus);

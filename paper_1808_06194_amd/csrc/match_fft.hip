@@ -727,7 +727,6 @@ int init_kernel_attributes() {
   int rc = init_match_fft_attributes();
   if (rc == 0) rc = init_extract_attributes();
   if (rc == 0) rc = init_direct_attributes();
-  if (rc == 0) rc = init_harris_attributes();
   if (rc == 0) rc = init_outlier_attributes();
   if (rc == 0) done.push_back(dev);
   return rc;
