@@ -538,7 +538,6 @@ int cfog_extract_scheme(cfog_ctx* ctx, const float* d_img, int32_t H, int32_t W,
   int R = gauss_radius < 0 ? (int)(4.0 * sigma + 0.5) : gauss_radius;
   if (R > cfog::kMaxGaussRadius) return CFOG_EUNSUPPORTED;
   if (!aligned(d_sat, 8)) return CFOG_EINVAL;
-  if (cfog::extract_lds_bytes(m, R) > cfog::kMaxLds) return CFOG_EUNSUPPORTED;
   const size_t need = d_sat ? cfog::extract_workspace_bytes(H, W) : 0;
   if (need && d_ws && ws_bytes < need) return CFOG_ENOMEM;
   if (!aligned(d_ws, 8)) return CFOG_EINVAL;
@@ -547,7 +546,7 @@ int cfog_extract_scheme(cfog_ctx* ctx, const float* d_img, int32_t H, int32_t W,
     if (rc != CFOG_OK) return rc;
   }
   int rc = cfog::launch_extract(d_img, row_stride, H, W, m, sigma, R, d_vol, d_sat, d_ws, (hipStream_t)stream,
-                                scheme);
+                                scheme, ctx->num_cus);
   if (rc == -1) return CFOG_EUNSUPPORTED;
   if (rc != 0) return record(ctx, hipGetLastError());
   return CFOG_OK;
@@ -588,7 +587,6 @@ int cfog_extract_batch(cfog_ctx* ctx, const cfog_image* imgs, int32_t n, int32_t
   }
   const int R = gauss_radius < 0 ? (int)(4.0 * sigma + 0.5) : gauss_radius;
   if (R > cfog::kMaxGaussRadius) return CFOG_EUNSUPPORTED;
-  if (cfog::extract_lds_bytes(m, R) > cfog::kMaxLds) return CFOG_EUNSUPPORTED;
   if (!aligned(d_ws, 8)) return CFOG_EINVAL;
   const size_t need = cfog_extract_batch_workspace_size(imgs, n);
   if (need && d_ws && ws_bytes < need) return CFOG_ENOMEM;
@@ -597,7 +595,8 @@ int cfog_extract_batch(cfog_ctx* ctx, const cfog_image* imgs, int32_t n, int32_t
     if (rc != CFOG_OK) return rc;
   }
   const std::vector<cfog::ExtractImage> v = batch_images(imgs, n);
-  const int rc = cfog::launch_extract_batch(v.data(), n, m, sigma, R, d_ws, (hipStream_t)stream, scheme);
+  const int rc = cfog::launch_extract_batch(v.data(), n, m, sigma, R, d_ws, (hipStream_t)stream, scheme,
+                                             ctx->num_cus);
   if (rc == -1) return CFOG_EUNSUPPORTED;
   if (rc != 0) return record(ctx, hipGetLastError());
   return CFOG_OK;

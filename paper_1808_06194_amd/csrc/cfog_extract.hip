@@ -5,9 +5,11 @@
 // contiguous H*W plane per orientation); SAT [(H+1)][(W+1)] fp64 with a zero
 // first row and column, SAT(y+1, x+1) = sum_{y'<=y, x'<=x} Q(y', x').
 //
-// The volume and table writes are nontemporal stores: they stream past the
-// caches, which nothing reads again before the matcher (measured on the
-// extraction's write pattern alone: 10-13% faster than cached stores).
+// The volume and finished table writes are nontemporal stores: they stream past
+// the caches, which nothing reads again before the matcher (measured on the
+// extraction's write pattern alone: 10-13% faster than cached stores).  The
+// tile-local prefixes, which kernel 3 reads again, are cached ones (two
+// 2048^2 images: 116.1 -> 113.7 us).
 //
 // Kernel 1 (cfog_extract_kernel<R, M>) produces a 64 x 32 output tile for all
 // m channels:
@@ -142,7 +144,7 @@ __device__ __forceinline__ void tile_sat_prefix(double (&q)[EX_RUN], double* qx,
   for (int o = 0; o < EX_RUN; ++o) {
     q[o] += up;
     const int gyy = y0 + orow + o;
-    if (gyy < H && gxx < W) __builtin_nontemporal_store(q[o], sat + (size_t)(gyy + 1) * W1 + gxx + 1);
+    if (gyy < H && gxx < W) sat[(size_t)(gyy + 1) * W1 + gxx + 1] = q[o];
     if (oc == TX - 1 && gyy < H) rc[(size_t)gyy * ntx + blockIdx.x] = q[o];
   }
   if (rg == NRG - 1 && gxx < W) bt[(size_t)blockIdx.y * W + gxx] = q[EX_RUN - 1];
@@ -154,8 +156,8 @@ __device__ __forceinline__ void tile_sat_prefix(double (&q)[EX_RUN], double* qx,
 constexpr int CF_TX = 128;
 constexpr int CF_TY = 16;
 
-// LDS geometry of the CFOG tile for Gaussian radius R.
-template <int R>
+// LDS geometry of the CFOG tile for Gaussian radius R, CG channels at a time.
+template <int R, int CG>
 struct ExTile {
   static constexpr int TX = CF_TX, TY = CF_TY;
   static constexpr int IW = TX + 2 * R + 2, IH = TY + 2 * R + 2;  // image tile (+1 for the gradient)
@@ -171,10 +173,10 @@ struct ExTile {
   // the spatially smoothed channels 0 and 1 of a thread's 4 outputs, needed
   // again by the circular orientation smoothing after the last channel
   static constexpr size_t KEEP = 2 * EX_RUN * EX_NT;  // floats, [value][thread]
-  // LDS: [channel plane | KEEP] then HB; the image tile shares the first
-  // region (it is dead once the gradients are in registers)
-  static constexpr size_t A = (GP + KEEP) > IMG ? (GP + KEEP) : IMG;
-  static constexpr size_t BYTES = 4 * (A + HB);
+  // LDS: [channel planes | KEEP] then the row passes; the image tile shares the
+  // first region (it is dead once the gradients are in registers)
+  static constexpr size_t A = (CG * GP + KEEP) > IMG ? (CG * GP + KEEP) : IMG;
+  static constexpr size_t BYTES = 4 * (A + CG * HB);
   // halo-tile pixels of a thread: thread t takes column t % TX of the rows
   // t / TX + RPP i (NROW of them), and the 2R columns right of the first TX
   // are spread over the threads (NEXTRA each)
@@ -193,19 +195,22 @@ struct ExTile {
 // M > 0: the channel count fixed at compile time (the channel loop unrolls
 // and the orientation smoothing's register rotation disappears); M = 0 reads
 // it from the arguments.  S1: scheme 1 instead of Eq. 2, fixed at compile
-// time so that the per-pixel channel value carries no branch.
-template <int R, int M, bool S1>
-__global__ __launch_bounds__(EX_NT) __attribute__((amdgpu_waves_per_eu(M > 0 ? 8 : 1, 8))) void cfog_extract_kernel(ExtractArgs a) {
-  using T = ExTile<R>;
+// time so that the per-pixel channel value carries no branch.  CG: channels
+// that go through a pass between two barriers, each with planes of its own.
+// Several are for launches that leave each tile its CU, where the passes'
+// latencies and barriers X
+template <int R, int M, bool S1, int CG>
+__global__ __launch_bounds__(EX_NT) __attribute__((amdgpu_waves_per_eu(M > 0 && CG == 1 ? 8 : 1, 8))) void cfog_extract_kernel(ExtractArgs a) {
+  using T = ExTile<R, CG>;
   constexpr int TX = T::TX, TY = T::TY;
   constexpr int IW = T::IW, IH = T::IH, GW = T::GW, GH = T::GH, GWP = T::GWP;
   extern __shared__ float4 lds4[];
   float* lds = reinterpret_cast<float*>(lds4);
   const int m = M > 0 ? M : a.m;
-  float* gk = lds;                                   // GH * GWP: one oriented-gradient channel
-  float* keep = gk + T::GP;                          // KEEP: Gs_0, Gs_1 of this thread's outputs
+  float* gk = lds;                                   // CG planes GH * GWP: oriented-gradient channels
+  float* keep = gk + CG * T::GP;                        // KEEP: Gs_0, Gs_1 of this thread's outputs
   float* img = lds;                                  // IH * IW, read only by the gradient pass
-  float* Hb = lds + T::A;                            // GH * TX row-pass outputs
+  float* Hb = lds + T::A;                            // CG planes GH * TX: row-pass outputs
   double* qx = reinterpret_cast<double*>(gk);        // the tile prefix's carries, after the last channel
   static_assert(T::GP * sizeof(float) >= ((EX_NT / TX) * TX + (EX_NT / 64) * EX_RUN) * sizeof(double),
                 "tile prefix carries");
@@ -301,7 +306,7 @@ __global__ __launch_bounds__(EX_NT) __attribute__((amdgpu_waves_per_eu(M > 0 ? 8
   // oriented gradient g_k of one pixel from its two gradient values:
   // |cos(theta_k) gx + sin(theta_k) gy| (Eq. 2), or for scheme 1
   // |g| max(0, 1 - circular distance of the bin position to k)
-  auto form_channel = [&](int k) {
+  auto form_channel = [&](int k, float* gk) {
     const float ck = a.cs[k], sk = a.sn[k], kf = (float)k;
     auto g_of = [&](float2 uv) {
       if constexpr (S1) {
@@ -328,7 +333,9 @@ __global__ __launch_bounds__(EX_NT) __attribute__((amdgpu_waves_per_eu(M > 0 ? 8
     }
   };
   __syncthreads();  // every read of the image tile is done: the channel plane shares its storage
-  form_channel(0);
+#pragma unroll
+  for (int c = 0; c < CG; ++c)
+    if (c < m) form_channel(c, gk + c * T::GP);
   __syncthreads();
 
   // C. per channel: the horizontal Gaussian of the oriented gradient (the
@@ -357,8 +364,7 @@ __global__ __launch_bounds__(EX_NT) __attribute__((amdgpu_waves_per_eu(M > 0 ? 8
       }
     }
   };
-  auto channel = [&](int k) {
-    float* hb = Hb;
+  auto row_pass = [&](const float* gk, float* hb) {
     // horizontal pass: each thread four consecutive outputs of one row from
     // 16-byte reads of the channel plane (QPR threads cover a row)
 #pragma unroll
@@ -387,7 +393,8 @@ __global__ __launch_bounds__(EX_NT) __attribute__((amdgpu_waves_per_eu(M > 0 ? 8
         *reinterpret_cast<float4*>(hb + r * TX + c4) = make_float4(o4[0], o4[1], o4[2], o4[3]);
       }
     }
-    __syncthreads();
+  };
+  auto col_pass = [&](int k, const float* hb) {
     float cur[EX_RUN];
     {
       const float* col = hb + orow * TX + oc;  // col[t*TX] = row orow - R + t
@@ -415,16 +422,27 @@ __global__ __launch_bounds__(EX_NT) __attribute__((amdgpu_waves_per_eu(M > 0 ? 8
     }
 #pragma unroll
     for (int o = 0; o < EX_RUN; ++o) { pm2[o] = pm1[o]; pm1[o] = cur[o]; }
-    // the next channel's values: the channel plane was last read by this
-    // channel's row pass, which the barrier above has closed
-    if (k + 1 < m) form_channel(k + 1);
-    __syncthreads();  // every read of Hb is done and the next channel is formed
+  };
+  auto channels = [&](int k) {  // k .. k + CG - 1
+#pragma unroll
+    for (int c = 0; c < CG; ++c)
+      if (k + c < m) row_pass(gk + c * T::GP, Hb + c * T::HB);
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < CG; ++c)
+      if (k + c < m) col_pass(k + c, Hb + c * T::HB);
+    // the next channels' values: their planes were last read by the row
+    // passes, which the barrier above has closed
+#pragma unroll
+    for (int c = 0; c < CG; ++c)
+      if (k + CG + c < m) form_channel(k + CG + c, gk + c * T::GP);
+    __syncthreads();  // every read of Hb is done and the next channels are formed
   };
   if constexpr (M > 0) {
 #pragma unroll
-    for (int k = 0; k < M; ++k) channel(k);
+    for (int k = 0; k < M; k += CG) channels(k);
   } else {
-    for (int k = 0; k < m; ++k) channel(k);
+    for (int k = 0; k < m; k += CG) channels(k);
   }
   {
     float d[EX_RUN], g0[EX_RUN], g1[EX_RUN];
@@ -728,15 +746,39 @@ __global__ __launch_bounds__(SAT_NT) void sat_carry_kernel(SatBatch b) {
   }
 }
 
+// The column prefix above tile row ty at column x, from the bottom rows: the
+// sums of sat_carry_kernel in its order, where its waves have one or two tile
+// rows each.
+__device__ __forceinline__ double column_carry(const double* bt, int W, int nty, int ty, int x) {
+  const bool two = nty > SAT_WAVES;
+  double run = 0.0;
+  for (int i = 0; i < ty; i += 8) {
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = i + u < ty ? bt[(size_t)(i + u) * W + x] : 0.0;
+#pragma unroll
+    for (int u = 0; u < 8; u += 2) run = two ? run + (v[u] + v[u + 1]) : run + v[u] + v[u + 1];
+  }
+  return run;
+}
+
 // Kernel 3: SAT = L + row carry + column carry + corner, in place; zero row 0
 // and column 0.  One workgroup per TX x TY extraction tile, one thread per
 // pixel column of a row group of EX_RUN rows (TX and TY as in the extraction
 // kernel that wrote the tile-local prefixes).  The tile's values and carries
 // are loaded first, so their latency overlaps the corner's reduction.
-template <int TX, int TY>
+// CARRY: kernel 2's prefixes are formed here, by each workgroup its own (the
+// same sums in the same order), and kernel 2 is not launched: for few tiles, whose
+// columns and rows are short, a launch costs more than summing them again (333 x
+// 251: 17.2 -> 15.4 us; 8 such images, 384 tiles: 25.1 -> 23.0; 1280 x 720, 450
+// tiles: 24.0 -> 23.9).
+constexpr int SAT_OWN_COLS = 64;             // tiles along x: a wave's lanes
+constexpr int SAT_OWN_ROWS = 2 * SAT_WAVES;  // tiles along y (column_carry)
+template <int TX, int TY, bool CARRY>
 __global__ __launch_bounds__(EX_NT) void sat_fix_kernel(SatBatch b) {
   static_assert((EX_NT / TX) * EX_RUN == TY, "tile geometry");
   __shared__ double corner_part[EX_NT / 64];
+  __shared__ double col_carry[CARRY ? TX : 1], row_carry[CARRY ? TY : 1];
   const SatImage I = b.im[blockIdx.z];
   if (!I.sat || (int)blockIdx.x >= I.ntx || (int)blockIdx.y >= I.nty) return;  // beyond this image's tiles
   double* const sat = I.sat;
@@ -751,19 +793,38 @@ __global__ __launch_bounds__(EX_NT) void sat_fix_kernel(SatBatch b) {
   double* const p0 = sat + (size_t)(y0 + rg * EX_RUN + 1) * W1 + gxx + 1;
   bool ok[EX_RUN];
   double l[EX_RUN], r[EX_RUN];
-  const double colc = gxx < W ? bt[(size_t)ty * W + gxx] : 0.0;
+  double colc = 0.0;
+  if (!CARRY && gxx < W) colc = bt[(size_t)ty * W + gxx];
 #pragma unroll
   for (int o = 0; o < EX_RUN; ++o) {
     const int gyy = y0 + rg * EX_RUN + o;
     ok[o] = gxx < W && gyy < H;
     l[o] = ok[o] ? p0[(size_t)o * W1] : 0.0;
-    r[o] = ok[o] ? rc[(size_t)gyy * ntx + tx] : 0.0;
+    if (!CARRY) r[o] = ok[o] ? rc[(size_t)gyy * ntx + tx] : 0.0;
   }
   // corner = sum_{j' < tx} (column prefix of bottom rows at the last column of tile j')
   double cpart = 0.0;
-  for (int j = tid; j < tx; j += EX_NT) {
-    const int xl = min(W, (j + 1) * TX) - 1;
-    cpart += bt[(size_t)ty * W + xl];
+  if constexpr (CARRY) {
+    // the first waves the columns, the next one the corner, the others the rows
+    constexpr int CW = TX / 64;
+    const int lane = tid & 63;
+    if (wv < CW) {
+      col_carry[oc] = gxx < W ? column_carry(bt, W, I.nty, ty, gxx) : 0.0;
+    } else if (wv == CW) {
+      if (lane < tx) cpart = column_carry(bt, W, I.nty, ty, min(W, (lane + 1) * TX) - 1);
+    } else {
+      for (int y = wv - CW - 1; y < TY; y += EX_NT / 64 - CW - 1) {
+        const double v = lane < ntx && y0 + y < H ? rc[(size_t)(y0 + y) * ntx + lane] : 0.0;
+        double tot;
+        const double ex = wave_excl_scan(v, tot);
+        if (lane == tx) row_carry[y] = ex;
+      }
+    }
+  } else {
+    for (int j = tid; j < tx; j += EX_NT) {
+      const int xl = min(W, (j + 1) * TX) - 1;
+      cpart += bt[(size_t)ty * W + xl];
+    }
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) cpart += __shfl_xor(cpart, o, 64);
@@ -772,6 +833,11 @@ __global__ __launch_bounds__(EX_NT) void sat_fix_kernel(SatBatch b) {
   double corner = 0.0;
 #pragma unroll
   for (int k = 0; k < EX_NT / 64; ++k) corner += corner_part[k];
+  if constexpr (CARRY) {
+    colc = col_carry[oc];
+#pragma unroll
+    for (int o = 0; o < EX_RUN; ++o) r[o] = row_carry[rg * EX_RUN + o];
+  }
 #pragma unroll
   for (int o = 0; o < EX_RUN; ++o)
     if (ok[o]) __builtin_nontemporal_store(l[o] + r[o] + colc + corner, p0 + (size_t)o * W1);
@@ -783,23 +849,10 @@ __global__ __launch_bounds__(EX_NT) void sat_fix_kernel(SatBatch b) {
   }
 }
 
-static size_t lds_bytes(int m, int R) {
-  (void)m;
-  switch (R) {
-    case 0: return ExTile<0>::BYTES;
-    case 1: return ExTile<1>::BYTES;
-    case 2: return ExTile<2>::BYTES;
-    case 3: return ExTile<3>::BYTES;
-    case 4: return ExTile<4>::BYTES;
-    case 5: return ExTile<5>::BYTES;
-    case 6: return ExTile<6>::BYTES;
-    case 7: return ExTile<7>::BYTES;
-    case 8: return ExTile<8>::BYTES;
-    default: return (size_t)-1;
-  }
-}
-
-size_t extract_lds_bytes(int m, int R) { return lds_bytes(m, R); }
+// Channels at a time where each tile of a launch has its CU (three planes of
+// the largest radius fit).
+constexpr int EX_CG = 3;
+static_assert(ExTile<kMaxGaussRadius, EX_CG>::BYTES <= kMaxLds, "LDS");
 
 // The carries of a TX x TY tiling: right columns [H][ntx], bottom rows [nty][W].
 static size_t carry_bytes(int H, int W, int TX, int TY) {
@@ -812,34 +865,38 @@ size_t extract_workspace_bytes(int H, int W) {
   return std::max(carry_bytes(H, W, CF_TX, CF_TY), carry_bytes(H, W, EX_TX, EX_TY));
 }
 
-template <int R, bool S1>
-static int launch_rs(const ExtractArgs& a, dim3 grid, hipStream_t st) {
-  const size_t lds = lds_bytes(a.m, R);
-  if constexpr (R == 3) {
-    if (a.m == 9) {  // the paper's parameters (sigma 0.8, nine orientations)
-      hipLaunchKernelGGL((cfog_extract_kernel<R, 9, S1>), grid, dim3(EX_NT), lds, st, a);
-      return hipGetLastError() == hipSuccess ? 0 : -2;
-    }
-  }
-  hipLaunchKernelGGL((cfog_extract_kernel<R, 0, S1>), grid, dim3(EX_NT), lds, st, a);
+template <int R, int M, bool S1, int CG>
+static int launch_k(const ExtractArgs& a, dim3 grid, hipStream_t st) {
+  hipLaunchKernelGGL((cfog_extract_kernel<R, M, S1, CG>), grid, dim3(EX_NT), (ExTile<R, CG>::BYTES), st, a);
   return hipGetLastError() == hipSuccess ? 0 : -2;
 }
 
+// M = 9 at R = 3: the paper's parameters (sigma 0.8, nine orientations).
+template <int R, bool S1>
+static int launch_rs(const ExtractArgs& a, dim3 grid, bool spread, hipStream_t st) {
+  if constexpr (R == 3)
+    if (a.m == 9) return spread ? launch_k<R, 9, S1, EX_CG>(a, grid, st) : launch_k<R, 9, S1, 1>(a, grid, st);
+  return spread ? launch_k<R, 0, S1, EX_CG>(a, grid, st) : launch_k<R, 0, S1, 1>(a, grid, st);
+}
+
 template <int R>
-static int launch_r(const ExtractArgs& a, dim3 grid, hipStream_t st) {
-  return a.scheme == 1 ? launch_rs<R, true>(a, grid, st) : launch_rs<R, false>(a, grid, st);
+static int launch_r(const ExtractArgs& a, dim3 grid, bool spread, hipStream_t st) {
+  return a.scheme == 1 ? launch_rs<R, true>(a, grid, spread, st) : launch_rs<R, false>(a, grid, spread, st);
+}
+
+template <int R, int M, bool S1, int CG>
+static int set_attr_k() {
+  return hipFuncSetAttribute((const void*)cfog_extract_kernel<R, M, S1, CG>,
+                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)ExTile<R, CG>::BYTES) == hipSuccess
+             ? 0
+             : -2;
 }
 
 template <int R, bool S1>
 static int set_attr_s() {
-  if (hipFuncSetAttribute((const void*)cfog_extract_kernel<R, 0, S1>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                          (int)kMaxLds) != hipSuccess)
-    return -2;
-  if constexpr (R == 3) {
-    if (hipFuncSetAttribute((const void*)cfog_extract_kernel<R, 9, S1>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)kMaxLds) != hipSuccess)
-      return -2;
-  }
+  if (set_attr_k<R, 0, S1, 1>() || set_attr_k<R, 0, S1, EX_CG>()) return -2;
+  if constexpr (R == 3)
+    if (set_attr_k<R, 9, S1, 1>() || set_attr_k<R, 9, S1, EX_CG>()) return -2;
   return 0;
 }
 
@@ -867,19 +924,26 @@ int init_extract_attributes() {
 }
 
 // The SAT carries and fix-up of the images of one launch (tiles of TX x TY).
+constexpr int SAT_OWN_TILES = 512;
 template <int TX, int TY>
 static int launch_sat(const SatBatch& b, int n, hipStream_t st) {
   int carry_blocks = 0, ntx = 0, nty = 0;
+  int64_t tiles = 0;
   for (int i = 0; i < n; ++i) {
     const SatImage& I = b.im[i];
     if (!I.sat) continue;
+    tiles += (int64_t)I.ntx * I.nty;
     carry_blocks = std::max(carry_blocks, (I.H + SAT_WAVES - 1) / SAT_WAVES + (I.W + 63) / 64);
     ntx = std::max(ntx, I.ntx);
     nty = std::max(nty, I.nty);
   }
   if (!carry_blocks) return 0;
-  hipLaunchKernelGGL(sat_carry_kernel, dim3(carry_blocks, n), dim3(SAT_NT), 0, st, b);
-  hipLaunchKernelGGL((sat_fix_kernel<TX, TY>), dim3(ntx, nty, n), dim3(EX_NT), 0, st, b);
+  if (ntx <= SAT_OWN_COLS && nty <= SAT_OWN_ROWS && tiles <= SAT_OWN_TILES) {
+    hipLaunchKernelGGL((sat_fix_kernel<TX, TY, true>), dim3(ntx, nty, n), dim3(EX_NT), 0, st, b);
+  } else {
+    hipLaunchKernelGGL(sat_carry_kernel, dim3(carry_blocks, n), dim3(SAT_NT), 0, st, b);
+    hipLaunchKernelGGL((sat_fix_kernel<TX, TY, false>), dim3(ntx, nty, n), dim3(EX_NT), 0, st, b);
+  }
   return hipGetLastError() == hipSuccess ? 0 : -2;
 }
 
@@ -891,8 +955,8 @@ size_t extract_batch_workspace_bytes(const int* H, const int* W, const bool* wit
 }
 
 int launch_extract_batch(const ExtractImage* ims, int n, int m, float sigma, int R, void* ws, hipStream_t st,
-                         int scheme) {
-  if (lds_bytes(m, R) > kMaxLds || R < 0 || R > kMaxGaussRadius) return -1;
+                         int scheme, int num_cus) {
+  if (R < 0 || R > kMaxGaussRadius) return -1;
   ExtractArgs a{};
   a.scheme = scheme;
   a.m = m;
@@ -922,6 +986,7 @@ int launch_extract_batch(const ExtractImage* ims, int n, int m, float sigma, int
     const int nb = std::min(kExBatch, n - i0);
     SatBatch sb{};
     int ntx = 0, nty = 0;
+    int64_t tiles = 0;
     for (int i = 0; i < nb; ++i) {
       const int j = order[i0 + i];
       const ExtractImage& src = ims[j];
@@ -935,22 +1000,24 @@ int launch_extract_batch(const ExtractImage* ims, int n, int m, float sigma, int
         I.bt = I.rc + (size_t)src.H * I.ntx;
       }
       sb.im[i] = SatImage{I.sat, I.rc, I.bt, I.H, I.W, I.ntx, I.nty};
+      tiles += (int64_t)I.ntx * I.nty;
       ntx = std::max(ntx, I.ntx);
       nty = std::max(nty, I.nty);
     }
     for (int i = nb; i < kExBatch; ++i) a.im[i] = ExImage{};
     const dim3 grid(ntx, nty, nb);
+    const bool spread = tiles <= num_cus;
     int rc = -1;
     switch (R) {
-      case 0: rc = launch_r<0>(a, grid, st); break;
-      case 1: rc = launch_r<1>(a, grid, st); break;
-      case 2: rc = launch_r<2>(a, grid, st); break;
-      case 3: rc = launch_r<3>(a, grid, st); break;
-      case 4: rc = launch_r<4>(a, grid, st); break;
-      case 5: rc = launch_r<5>(a, grid, st); break;
-      case 6: rc = launch_r<6>(a, grid, st); break;
-      case 7: rc = launch_r<7>(a, grid, st); break;
-      case 8: rc = launch_r<8>(a, grid, st); break;
+      case 0: rc = launch_r<0>(a, grid, spread, st); break;
+      case 1: rc = launch_r<1>(a, grid, spread, st); break;
+      case 2: rc = launch_r<2>(a, grid, spread, st); break;
+      case 3: rc = launch_r<3>(a, grid, spread, st); break;
+      case 4: rc = launch_r<4>(a, grid, spread, st); break;
+      case 5: rc = launch_r<5>(a, grid, spread, st); break;
+      case 6: rc = launch_r<6>(a, grid, spread, st); break;
+      case 7: rc = launch_r<7>(a, grid, spread, st); break;
+      case 8: rc = launch_r<8>(a, grid, spread, st); break;
       default: return -1;
     }
     if (rc != 0) return rc;
@@ -961,9 +1028,9 @@ int launch_extract_batch(const ExtractImage* ims, int n, int m, float sigma, int
 }
 
 int launch_extract(const float* img, int64_t stride, int H, int W, int m, float sigma, int R, float* vol,
-                   double* sat, void* ws, hipStream_t st, int scheme) {
+                   double* sat, void* ws, hipStream_t st, int scheme, int num_cus) {
   const ExtractImage im{img, stride, H, W, vol, sat};
-  return launch_extract_batch(&im, 1, m, sigma, R, ws, st, scheme);
+  return launch_extract_batch(&im, 1, m, sigma, R, ws, st, scheme, num_cus);
 }
 
 }  // namespace cfog
