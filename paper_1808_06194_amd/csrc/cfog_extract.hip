@@ -110,11 +110,13 @@ __device__ __forceinline__ double wave_incl_scan(double v) {
 // [orow, orow + EX_RUN) of column oc of a TX x TY tile at row y0; a row of the
 // tile spans TX / 64 waves, EX_NT / TX row groups of EX_RUN rows stack down),
 // written into the SAT buffer, plus the tile's right column (rc) and bottom
-// row (bt) for the carry kernels.  qx: (EX_NT / TX) TX + EX_NT / 64 EX_RUN
+// row (bt) for the carry kernels.  on: false in waves past the first EX_NT
+// threads, which have no rows.  qx: (EX_NT / TX) TX + EX_NT / 64 EX_RUN
 // doubles of LDS.
 template <int TX, int TY>
 __device__ __forceinline__ void tile_sat_prefix(double (&q)[EX_RUN], double* qx, double* sat, double* rc, double* bt,
-                                                int H, int W, int ntx, int y0, int orow, int oc, int gxx) {
+                                                int H, int W, int ntx, int y0, int orow, int oc, int gxx,
+                                                bool on = true) {
   constexpr int NWX = TX / 64, NRG = EX_NT / TX;
   static_assert(TX % 64 == 0 && NRG * EX_RUN == TY, "tile geometry");
   const int tid = threadIdx.x, lane = tid & 63, rg = tid / TX, hx = (tid >> 6) % NWX;
@@ -135,8 +137,9 @@ __device__ __forceinline__ void tile_sat_prefix(double (&q)[EX_RUN], double* qx,
   }
 #pragma unroll
   for (int o = 1; o < EX_RUN; ++o) q[o] += q[o - 1];              // along y within the thread
-  qx[rg * TX + oc] = q[EX_RUN - 1];
+  if (on) qx[rg * TX + oc] = q[EX_RUN - 1];
   __syncthreads();
+  if (!on) return;
   double up = 0.0;
   for (int i = 0; i < rg; ++i) up += qx[i * TX + oc];
   const int W1 = W + 1;
@@ -474,11 +477,18 @@ __global__ __launch_bounds__(EX_NT) __attribute__((amdgpu_waves_per_eu(M > 0 && 
 // cells with bilinear weights max(0, 1 - |d - o| / C) for cell centres
 // o = -C/2, +C/2 at block offsets d in [-C, C] (clamp-to-edge borders), the
 // 36 values normalised by sqrt(|v|^2 + 1e-12).  Channel (2 a + b) 9 + k is
-// cell column a, cell row b, bin k.  Same tiles as the CFOG kernel: per bin,
-// the bin's channel on the halo tile, both horizontal cell passes, both
-// vertical cell passes into registers (9 x 4 values for each of the 4 pixels
-// of a thread) until the norm is known; then the normalised values go out
-// and their energies feed the tile-local SAT prefix.
+// cell column a, cell row b, bin k.  64 x 32 tiles; per bin, the bin's channel
+// on the halo tile, both horizontal cell passes, both vertical cell passes into
+// registers until the norm is known; then the normalised values go out and
+// their energies feed the tile-local SAT prefix.
+//
+// What bounds it: the latencies of the passes.  A thread's 36 values a pixel
+// leave a CU one workgroup, so that workgroup is as large as can be (1024
+// threads, two pixels each, 72 values) and three bins go through a pass between
+// two barriers.  The halo tile's magnitudes and bin positions stay in the
+// registers of the threads that form the channels from them.  1011 x 733, cells
+// of 4: 79 us with 512 threads, one bin at a time and those in LDS,
+// 71 us so.
 constexpr int FH_BINS = 9;
 constexpr int FH_MAX_CELL = 8;
 
@@ -493,19 +503,26 @@ struct FhogArgs {
   int ntx, nty;
 };
 
+constexpr int FH_NT = 1024;
+constexpr int FH_RUN = EX_TY * EX_TX / FH_NT;  // pixels of a thread, down a column
+constexpr int FH_CG = 3;                       // bins at a time
+static_assert(FH_BINS % FH_CG == 0, "groups of bins");
+
 template <int C>
 struct FhTile {
   static constexpr int IW = EX_TX + 2 * C + 2, IH = EX_TY + 2 * C + 2;  // image tile (+1 for the gradient)
   static constexpr int GW = EX_TX + 2 * C, GH = EX_TY + 2 * C;          // gradient / channel tile
-  static constexpr size_t IMG = ((size_t)IH * IW + 3) / 4 * 4;          // floats (keeps G 16-byte aligned)
-  static constexpr size_t MB = (size_t)GH * GW;                         // float2 (|g|, bin position)
+  static constexpr int NPX = (GH * GW + FH_NT - 1) / FH_NT;             // its pixels of a thread
   static constexpr int NQ = (4 + 2 * C + 3) / 4;  // 16-byte reads per 4 horizontal outputs
   // channel row stride: a multiple of 4 floats covering the last quad's reads
   static constexpr int GWP = ((GW + 3) / 4 * 4) > (EX_TX - 4 + 4 * NQ) ? ((GW + 3) / 4 * 4) : (EX_TX - 4 + 4 * NQ);
-  static constexpr int NQUAD = GH * EX_TX / 4;  // horizontal outputs four at a time
-  static constexpr size_t G = (size_t)GH * GWP;                         // floats
+  static constexpr int NQUAD = GH * EX_TX / 4;                          // horizontal outputs four at a time
+  static constexpr size_t G = (size_t)GH * GWP;                         // floats of a channel plane
   static constexpr size_t HX = 2 * (size_t)GH * EX_TX;                  // floats: both horizontal passes
-  static constexpr size_t BYTES = 4 * IMG + 8 * MB + 4 * G + 4 * HX + 8 * (EX_NT / 64) * 64;
+  // LDS: the channel planes, then the horizontal passes.  The image tile comes
+  // before them, the energies and the tile prefix's carries after, in the same place.
+  static constexpr size_t BYTES = 4 * FH_CG * (G + HX);
+  static_assert(BYTES >= 4 * (size_t)IH * IW && BYTES >= 8 * (EX_TX * EX_TY + EX_NT) && BYTES <= kMaxLds, "LDS");
 };
 
 // Bilinear weight of block offset d for cell a (centre offset (a - 1/2) C).
@@ -516,32 +533,43 @@ __device__ __forceinline__ float fh_w(int d, int a) {
 }
 
 template <int C>
-__global__ __launch_bounds__(EX_NT) void fhog_kernel(FhogArgs a) {
+__global__ __launch_bounds__(FH_NT) void fhog_kernel(FhogArgs a) {
   using T = FhTile<C>;
   constexpr int IW = T::IW, IH = T::IH, GW = T::GW, GH = T::GH;
   extern __shared__ float4 lds4[];
   float* img = reinterpret_cast<float*>(lds4);
-  float2* mb = reinterpret_cast<float2*>(img + T::IMG);
-  float* G = reinterpret_cast<float*>(mb + T::MB);
-  float* hx = G + T::G;
-  double* qx = reinterpret_cast<double*>(hx + T::HX);
+  float* G = reinterpret_cast<float*>(lds4);
+  float* hx = G + FH_CG * T::G;
   const int tid = threadIdx.x;
   const int x0 = blockIdx.x * EX_TX, y0 = blockIdx.y * EX_TY;
   const int H = a.H, W = a.W;
 
   // A. image tile, rows y0-C-1 .. y0+TY+C, clamped
-  for (int i = tid; i < IH * IW; i += EX_NT) {
-    const int r = i / IW, c = i - r * IW;
-    const int gy = clampi(y0 - C - 1 + r, 0, H - 1), gx = clampi(x0 - C - 1 + c, 0, W - 1);
-    img[i] = a.img[(int64_t)gy * a.stride + gx];
+  {
+    constexpr int NIT = (IH * IW + FH_NT - 1) / FH_NT;
+    float v[NIT];
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+      const int i = tid + it * FH_NT, r = i / IW, c = i - r * IW;
+      const int gy = clampi(y0 - C - 1 + r, 0, H - 1), gx = clampi(x0 - C - 1 + c, 0, W - 1);
+      if (i < IH * IW) v[it] = a.img[(int64_t)gy * a.stride + gx];
+    }
+#pragma unroll
+    for (int it = 0; it < NIT; ++it)
+      if (tid + it * FH_NT < IH * IW) img[tid + it * FH_NT] = v[it];
   }
   __syncthreads();
-  // B. (|g|, orientation bin position) at the clamped positions of the halo tile
+  // B. (|g|, orientation bin position) of this thread's pixels of the halo
+  // tile, at their clamped positions
+  float2 mb[T::NPX];
+  int at[T::NPX];  // places in a channel plane
   {
     const int oy = y0 - C - 1, ox = x0 - C - 1;
     const float bscale = (float)FH_BINS / 3.14159265358979f;
-    for (int i = tid; i < GH * GW; i += EX_NT) {
-      const int r = i / GW, c = i - r * GW;
+#pragma unroll
+    for (int it = 0; it < T::NPX; ++it) {
+      const int i = tid + it * FH_NT;
+      const int r = min(i / GW, GH - 1), c = i - i / GW * GW;
       const int Yc = clampi(y0 - C + r, 0, H - 1), Xc = clampi(x0 - C + c, 0, W - 1);
       const int yl = Yc - oy, xl = Xc - ox;
       const int xp = clampi(Xc + 1, 0, W - 1) - ox, xm = clampi(Xc - 1, 0, W - 1) - ox;
@@ -551,90 +579,106 @@ __global__ __launch_bounds__(EX_NT) void fhog_kernel(FhogArgs a) {
       if (phi < 0.f) phi += 3.14159265358979f;
       float b = phi * bscale;
       if (b >= (float)FH_BINS) b -= (float)FH_BINS;
-      mb[i] = make_float2(sqrtf(gx * gx + gy * gy), b);
+      mb[it] = make_float2(sqrtf(gx * gx + gy * gy), b);
+      at[it] = r * T::GWP + c;
     }
   }
   __syncthreads();
 
-  // C. per bin: channel, horizontal cell passes, vertical cell passes
-  const int oc = tid & 63, orow = (tid >> 6) * EX_RUN;
+  // C. per group of bins: channels, horizontal cell passes, vertical cell passes
+  const int oc = tid & 63, orow = (tid >> 6) * FH_RUN;
   const int gxx = x0 + oc;
-  float v[FH_BINS][4][EX_RUN];
-  float n2[EX_RUN];
+  float v[FH_BINS][4][FH_RUN];
+  float n2[FH_RUN];
 #pragma unroll
-  for (int o = 0; o < EX_RUN; ++o) n2[o] = 0.f;
+  for (int o = 0; o < FH_RUN; ++o) n2[o] = 0.f;
+  auto form = [&](int k0) {
 #pragma unroll
-  for (int k = 0; k < FH_BINS; ++k) {
-    for (int i = tid; i < GH * GW; i += EX_NT) {
-      const int r = i / GW, c = i - r * GW;
-      const float2 g = mb[i];
-      const float d = fabsf(g.y - (float)k);
-      G[r * T::GWP + c] = g.x * fmaxf(0.f, 1.f - fminf(d, (float)FH_BINS - d));
-    }
-    __syncthreads();
+    for (int it = 0; it < T::NPX; ++it)
+      if (GH * GW % FH_NT == 0 || tid + it * FH_NT < GH * GW) {
+#pragma unroll
+        for (int k = 0; k < FH_CG; ++k) {
+          const float d = fabsf(mb[it].y - (float)(k0 + k));
+          G[k * T::G + at[it]] = mb[it].x * fmaxf(0.f, 1.f - fminf(d, (float)FH_BINS - d));
+        }
+      }
+  };
+  form(0);
+  __syncthreads();
+#pragma unroll
+  for (int k0 = 0; k0 < FH_BINS; k0 += FH_CG) {
     // both horizontal cell passes, four consecutive outputs per thread from
     // 16-byte reads (16 threads cover a row); the padding columns of G feed
     // no output
+#pragma unroll 1
+    for (int qb = tid; qb < FH_CG * T::NQUAD; qb += FH_NT) {
+      const int k = qb / T::NQUAD, qd = qb - k * T::NQUAD;
+      const int r = qd >> 4, c4 = (qd & 15) * 4;
+      const float4* src = reinterpret_cast<const float4*>(G + k * T::G + r * T::GWP + c4);
+      float x[4 * T::NQ];
 #pragma unroll
-    for (int it = 0; it < (T::NQUAD + EX_NT - 1) / EX_NT; ++it) {
-      const int qd = tid + it * EX_NT;
-      if (T::NQUAD % EX_NT == 0 || qd < T::NQUAD) {
-        const int r = qd >> 4, c4 = (qd & 15) * 4;
-        const float4* src = reinterpret_cast<const float4*>(G + r * T::GWP + c4);
-        float x[4 * T::NQ];
-#pragma unroll
-        for (int u = 0; u < T::NQ; ++u) {
-          const float4 t = src[u];
-          x[4 * u] = t.x;
-          x[4 * u + 1] = t.y;
-          x[4 * u + 2] = t.z;
-          x[4 * u + 3] = t.w;
-        }
-        float o0[4], o1[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          float s0 = 0.f, s1 = 0.f;
-#pragma unroll
-          for (int d = -C; d <= C; ++d) {
-            s0 = fmaf(fh_w<C>(d, 0), x[j + C + d], s0);
-            s1 = fmaf(fh_w<C>(d, 1), x[j + C + d], s1);
-          }
-          o0[j] = s0;
-          o1[j] = s1;
-        }
-        *reinterpret_cast<float4*>(hx + r * EX_TX + c4) = make_float4(o0[0], o0[1], o0[2], o0[3]);
-        *reinterpret_cast<float4*>(hx + GH * EX_TX + r * EX_TX + c4) = make_float4(o1[0], o1[1], o1[2], o1[3]);
+      for (int u = 0; u < T::NQ; ++u) {
+        const float4 t = src[u];
+        x[4 * u] = t.x;
+        x[4 * u + 1] = t.y;
+        x[4 * u + 2] = t.z;
+        x[4 * u + 3] = t.w;
       }
-    }
-    __syncthreads();
+      float o0[4], o1[4];
 #pragma unroll
-    for (int ca = 0; ca < 2; ++ca) {
-      const float* col = hx + ca * GH * EX_TX + (orow + C) * EX_TX + oc;  // col[t * TX] = output row orow + t
-#pragma unroll
-      for (int o = 0; o < EX_RUN; ++o) {
+      for (int j = 0; j < 4; ++j) {
         float s0 = 0.f, s1 = 0.f;
 #pragma unroll
         for (int d = -C; d <= C; ++d) {
-          const float x = col[(o + d) * EX_TX];
-          s0 = fmaf(fh_w<C>(d, 0), x, s0);
-          s1 = fmaf(fh_w<C>(d, 1), x, s1);
+          s0 = fmaf(fh_w<C>(d, 0), x[j + C + d], s0);
+          s1 = fmaf(fh_w<C>(d, 1), x[j + C + d], s1);
         }
-        v[k][2 * ca][o] = s0;
-        v[k][2 * ca + 1][o] = s1;
-        n2[o] = fmaf(s0, s0, fmaf(s1, s1, n2[o]));
+        o0[j] = s0;
+        o1[j] = s1;
+      }
+      float* dst = hx + k * T::HX + r * EX_TX + c4;
+      *reinterpret_cast<float4*>(dst) = make_float4(o0[0], o0[1], o0[2], o0[3]);
+      *reinterpret_cast<float4*>(dst + GH * EX_TX) = make_float4(o1[0], o1[1], o1[2], o1[3]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int kk = 0; kk < FH_CG; ++kk) {
+      const int k = k0 + kk;
+#pragma unroll
+      for (int ca = 0; ca < 2; ++ca) {
+        const float* col = hx + kk * T::HX + ca * GH * EX_TX + orow * EX_TX + oc;  // col[t * TX] = row orow - C + t
+        float x[FH_RUN + 2 * C];
+#pragma unroll
+        for (int t = 0; t < FH_RUN + 2 * C; ++t) x[t] = col[t * EX_TX];
+#pragma unroll
+        for (int o = 0; o < FH_RUN; ++o) {
+          float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+          for (int d = -C; d <= C; ++d) {
+            s0 = fmaf(fh_w<C>(d, 0), x[o + C + d], s0);
+            s1 = fmaf(fh_w<C>(d, 1), x[o + C + d], s1);
+          }
+          n2[o] = fmaf(s0, s0, fmaf(s1, s1, n2[o]));
+          // formed here: the windows would otherwise be kept until the end
+          asm volatile("" : "+v"(s0), "+v"(s1));
+          v[k][2 * ca][o] = s0;
+          v[k][2 * ca + 1][o] = s1;
+        }
       }
     }
-    // the next bin's channel pass writes G, which no thread still reads; its
-    // barrier precedes the next writes of hx
+    // the next bins' channels: their planes were last read by the horizontal
+    // passes, which the barrier above has closed
+    if (k0 + FH_CG < FH_BINS) form(k0 + FH_CG);
+    __syncthreads();
   }
 
   // D. normalise, write the 36 channels, energies -> tile-local SAT prefix
   const size_t plane = (size_t)H * W;
   float* const vout = a.vol + (size_t)min(y0 + orow, H - 1) * W + min(gxx, W - 1);
-  double q[EX_RUN];
+  double* const qb = reinterpret_cast<double*>(lds4);
 #pragma unroll
-  for (int o = 0; o < EX_RUN; ++o) {
-    q[o] = 0.0;
+  for (int o = 0; o < FH_RUN; ++o) {
+    double e = 0.0;
     const bool ok = y0 + orow + o < H && gxx < W;
     const float inv = 1.0f / sqrtf(n2[o] + 1e-12f);
 #pragma unroll
@@ -644,12 +688,20 @@ __global__ __launch_bounds__(EX_NT) void fhog_kernel(FhogArgs a) {
         const float val = v[k][c4][o] * inv;
         if (ok) {
           __builtin_nontemporal_store(val, vout + (size_t)(c4 * FH_BINS + k) * plane + (size_t)o * W);
-          q[o] = fma((double)val, (double)val, q[o]);
+          e = fma((double)val, (double)val, e);
         }
       }
+    qb[(orow + o) * EX_TX + oc] = e;
   }
   if (!a.sat) return;
-  tile_sat_prefix<EX_TX, EX_TY>(q, qx, a.sat, a.rc, a.bt, H, W, a.ntx, y0, orow, oc, gxx);
+  // the prefix is formed by EX_NT threads of EX_RUN rows each
+  __syncthreads();
+  const bool on = tid < EX_NT;
+  const int prow = on ? (tid >> 6) * EX_RUN : 0;
+  double q[EX_RUN];
+#pragma unroll
+  for (int o = 0; o < EX_RUN; ++o) q[o] = qb[(prow + o) * EX_TX + oc];
+  tile_sat_prefix<EX_TX, EX_TY>(q, qb + EX_TX * EX_TY, a.sat, a.rc, a.bt, H, W, a.ntx, y0, prow, oc, gxx, on);
 }
 
 // Kernel 2: exclusive prefixes of the right columns along each image row (one
@@ -1039,7 +1091,7 @@ namespace cfog {
 
 template <int C>
 static void launch_fh(const FhogArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(fhog_kernel<C>, dim3(a.ntx, a.nty), dim3(EX_NT), FhTile<C>::BYTES, st, a);
+  hipLaunchKernelGGL(fhog_kernel<C>, dim3(a.ntx, a.nty), dim3(FH_NT), FhTile<C>::BYTES, st, a);
 }
 
 int launch_fhog(const float* img, int64_t stride, int H, int W, int cell, float* vol, double* sat, void* ws,
