@@ -11,17 +11,27 @@
 //   K = (c, s, tx)  (all channels, all search rows, the template columns),
 // so every output tile of C accumulates in MFMA registers with no scatter.
 // v_mfma_f32_16x16x32_bf16 tiles: M and N are padded to 16, the template
-// width to 32.  Per channel the template (bf16, with 15 zero rows above and
-// below) and the search window (bf16) are staged in LDS.  Every wave keeps
-// all (2r+1)^2 outputs in registers (up to 5 x 5 tiles) and takes every 8th
-// search row s, so per (s, 32-column chunk) it reads 5 A and at most 5 B
-// fragments for up to 25 MFMAs; the waves' partial sums are added in wave
-// order at the end (deterministic).  Operand fragments:
+// width to 32.  Every wave keeps all (2r+1)^2 outputs in registers (up to 5 x 5
+// tiles) and takes every 8th search row s; the waves' partial sums are added in
+// wave order at the end (deterministic).  Operand fragments:
 //   A (lane l, u_x block m): 8 bf16 of search row s from column
 //      32kc + 8(l/16) + 16m + l%16, read as 5 aligned dwords and realigned by a
-//      byte shift;
+//      byte shift (chunk kc + 1 shares all but two of chunk kc's);
 //   B (lane l, u_y block n): 8 bf16 of template row s - 16n - l%16, columns
 //      32kc + 8(l/16) .. +7, one aligned 16-byte LDS read.
+// A search row is used by one wave only, which brings it in by itself, two rows
+// ahead: from memory to registers, rounded into a pair of rows of LDS of its own.
+// The template (bf16, with 15 zero rows above and below) is shared; where two
+// fit LDS, the next channel's is brought in a row at a time meanwhile, so that
+// loads and MFMAs overlap and a channel has one barrier.
+//
+// What bounds it: the matrix cores.  N = 128, r = 32 (65 offsets in 80) executes
+// 1.1 PFLOP/s at the 2.0 GHz that the clock then has, of which 0.6 are not
+// padding; a large library product reaches 1.24.  1000 points: 2407 us where
+// each channel's rows were staged before its MFMAs and all fragments read per
+// chunk; 2195 with shared fragments, the next chunk's read ahead; 1995 without
+// the moves and address arithmetic of that; 1884 with rows brought in as now.
+// A body without tests for rows that meet all blocks spills and is slower.
 // Precision: inputs are rounded to BF16 (round to nearest, 8 significant bits,
 // unit roundoff u = 2^-8), products are exact in FP32, so
 //   |C_bf16 - C| <= [(2u + u^2) + gamma_L (1 + u)^2] sum |T S|,
@@ -34,6 +44,7 @@
 // 0.0095 at N = 128, r = 32, m = 9, against ~1e-6 for the FP32 FFT path.
 #include <hip/hip_runtime.h>
 #include <algorithm>
+#include <utility>
 #include "cfog.h"
 #include "epilogue.hpp"
 #include "kernels.hpp"
@@ -48,7 +59,8 @@ constexpr int D_NB = 5;            // max 16-wide blocks of u_x (and u_y): 2r+1 
 constexpr int D_NW = 8;            // waves per workgroup
 constexpr int D_NT = 64 * D_NW;
 constexpr int D_TPAD = 15;         // zero template rows above and below
-constexpr int D_RB = 8;            // rows staged per batch of loads
+constexpr int D_KC = 6;            // most 32-column chunks of a template row (N <= 192)
+constexpr int D_RB = 12;           // template rows of a wave staged per batch of loads
 constexpr int D_PW = 4;            // waves whose partial correlations are summed together
 
 struct DirectGeom {
@@ -56,7 +68,8 @@ struct DirectGeom {
   int TROWS;  // template rows staged: N + 2 * D_TPAD (row tr holds template row tr - D_TPAD)
   int TLD;    // template row stride in dwords, NP/2 + 4: an odd multiple of 4, so the
               // 16 rows one B fragment reads start in 16 different 4-bank groups
-  int SLD;    // search row stride in dwords (NP + 16 nblk + 2 bf16: the fragment over-read)
+  int SLD;    // dwords of a search row (NP + 16 nblk + 2 bf16: the fragment over-read)
+  int tbufs;  // template buffers: 2 where they fit, else 1
   size_t t_bytes, lds;
 };
 
@@ -72,11 +85,12 @@ static DirectGeom direct_geom(int N, int r) {
   g.TLD = g.NP / 2 + 4;
   g.SLD = (g.NP + 16 * g.nblk + 2) / 2;
   g.t_bytes = (size_t)g.TROWS * g.TLD * 4;
-  const size_t sb = (size_t)g.Ws * g.SLD * 4;
+  const size_t sb = (size_t)2 * D_NW * g.SLD * 4;
+  g.tbufs = 2 * g.t_bytes + sb <= kMaxLds ? 2 : 1;
   // after the channels: Cs (K x K) and D_PW partial surfaces; the epilogue's
   // argmin scratch sits behind Cs once the partials are summed
   const size_t c = (size_t)g.K * g.K * 4 * (1 + D_PW) + 16 * D_NW;
-  g.lds = std::max(g.t_bytes + sb, c);
+  g.lds = std::max(g.tbufs * g.t_bytes + sb, c);
   return g;
 }
 
@@ -85,40 +99,37 @@ __device__ __forceinline__ unsigned pack_bf16x2(float lo, float hi) {
   return (unsigned)__builtin_bit_cast(unsigned short, a) | ((unsigned)__builtin_bit_cast(unsigned short, b) << 16);
 }
 
-// Stage `nrows` rows of `ncols` valid fp32 values (row r at src + r * ld when
-// valid(r), zeros otherwise) as packed bf16 pairs, `width` bf16 per row, into
-// dst with a row stride of `ldd` dwords.  Rows r = wv, wv + NW, ...; the
-// loads of D_RB rows are issued before their conversions.
-template <class Valid>
-__device__ __forceinline__ void stage_rows(unsigned* dst, int ldd, int nrows, int width, const float* src,
-                                           size_t ld, int ncols, Valid valid, int wv, int lane) {
-  for (int r0 = wv; r0 < nrows; r0 += D_NW * D_RB) {
-    for (int x = 2 * lane; x < width; x += 128) {
-      float a[D_RB], b[D_RB];
+// A row's values 2 (lane + 64 i) and the next, i < NX, of the `bytes` at src
+// (wave-uniform); zero past them.  The row is a buffer of its own, whose range
+// check gives the zeros.  odd: a pair may straddle the end, so two loads.
+template <int NX>
+__device__ __forceinline__ void load_row(const float* src, int bytes, bool odd, int lane, float2 (&v)[NX]) {
+  const __amdgpu_buffer_rsrc_t rs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(uniform_ptr(src)), 0, bytes, 0x00027000);
 #pragma unroll
-      for (int u = 0; u < D_RB; ++u) {
-        const int r = r0 + u * D_NW;
-        a[u] = b[u] = 0.f;
-        if (r < nrows && valid(r)) {
-          const float* p = src + (size_t)r * ld;
-          if (x < ncols) a[u] = p[x];
-          if (x + 1 < ncols) b[u] = p[x + 1];
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < D_RB; ++u) {
-        const int r = r0 + u * D_NW;
-        if (r < nrows) dst[(size_t)r * ldd + x / 2] = pack_bf16x2(a[u], b[u]);
-      }
+  for (int i = 0; i < NX; ++i) {
+    const int o = 8 * lane + 512 * i;
+    if (odd) {
+      v[i].x = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, o, 0, 0));
+      v[i].y = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, o + 4, 0, 0));
+    } else {
+      v[i] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rs, o, 0, 0));
     }
   }
 }
+// Those as packed bf16 pairs, the first n dwords, to dst.
+template <int NX>
+__device__ __forceinline__ void store_row(unsigned* dst, int n, int lane, const float2 (&v)[NX]) {
+#pragma unroll
+  for (int i = 0; i < NX; ++i)
+    if (lane + 64 * i < n) dst[lane + 64 * i] = pack_bf16x2(v[i].x, v[i].y);
+}
 
-template <int NB>
+template <int NB, int NKC>
 __global__ __launch_bounds__(D_NT) void match_direct_kernel(MatchJob jd, DirectGeom g) {
   extern __shared__ unsigned char dsm[];
-  unsigned* Tl = reinterpret_cast<unsigned*>(dsm);                             // TROWS x TLD dwords
-  unsigned* Sl = reinterpret_cast<unsigned*>(dsm + g.t_bytes);                 // Ws x SLD dwords
+  constexpr int SX = (16 * NKC + 8 * NB + 1 + 63) / 64;  // dwords of a search row per lane
+  constexpr int TX = (16 * NKC + 63) / 64;               // and of a template row
   float* Cs = reinterpret_cast<float*>(dsm);                                    // K x K, after the channels
   ArgminState* red = reinterpret_cast<ArgminState*>(dsm + (size_t)g.K * g.K * 4);
   const int lane = threadIdx.x & 63;
@@ -126,6 +137,10 @@ __global__ __launch_bounds__(D_NT) void match_direct_kernel(MatchJob jd, DirectG
   const int l16 = lane & 15, kg = lane >> 4;
   const int N = g.N, r = g.r, K = g.K, NP = g.NP, Ws = g.Ws;
   const size_t planeA = (size_t)jd.hA * jd.wA, planeB = (size_t)jd.hB * jd.wB;
+  const bool odd = N & 1;
+  unsigned* const T0 = reinterpret_cast<unsigned*>(dsm);          // template buffers, TROWS x TLD dwords
+  const int tstep = g.tbufs == 2 ? (int)(g.t_bytes / 4) : 0;      // to the other buffer
+  unsigned* const Sw = T0 + g.tbufs * (g.t_bytes / 4) + 2 * wv * g.SLD;  // this wave's two search rows
 
   for (int cpi = blockIdx.x; cpi < jd.n_cps; cpi += gridDim.x) {
     const int4 cp = jd.cps[cpi];
@@ -144,56 +159,151 @@ __global__ __launch_bounds__(D_NT) void match_direct_kernel(MatchJob jd, DirectG
 #pragma unroll
       for (int n = 0; n < NB; ++n) acc[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+    const float* tsrc = jd.volA + (size_t)ty0 * jd.wA + tx0;
+    const float* ssrc = jd.volB + (size_t)sy0 * jd.wB + sx0;
+    // the zero rows around the template
+    for (int i = threadIdx.x; i < D_TPAD * g.TLD; i += D_NT)
+      for (int b = 0; b < g.tbufs; ++b) {
+        T0[b * tstep + i] = 0;
+        T0[b * tstep + (D_TPAD + N) * g.TLD + i] = 0;
+      }
+    // this wave's template rows of channel c into buffer Tc
+    auto stage_template = [&](int c, unsigned* Tc) {
+#pragma unroll 1
+      for (int n0 = wv; n0 < N; n0 += D_NW * D_RB) {
+        float2 v[D_RB][TX];
+#pragma unroll
+        for (int u = 0; u < D_RB; ++u) {
+          const int n = n0 + u * D_NW;
+          load_row<TX>(tsrc + c * planeA + (size_t)min(n, N - 1) * jd.wA, n < N ? N * 4 : 0, odd, lane, v[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < D_RB; ++u) {
+          const int n = n0 + u * D_NW;
+          if (n < N) store_row<TX>(Tc + (D_TPAD + n) * g.TLD, NP / 2, lane, v[u]);
+        }
+      }
+    };
+    // This wave's search rows are s = wv, wv + NW, ... of every channel, one
+    // after the other; it alone reads them, so it brings them in by itself: row
+    // t + 2 of that sequence is on its way to registers and row t + 1 in LDS while
+    // row t is used.
+    float2 sv[SX];
+    int lc = 0, ls = wv;  // the next row to load
+    auto next_row = [&] {
+      const bool more = ls < Ws && lc < jd.m;
+      load_row<SX>(ssrc + (more ? lc * planeB + (size_t)ls * jd.wB : 0), more ? Ws * 4 : 0, odd, lane, sv);
+      ls += D_NW;
+      if (ls >= Ws) {
+        ls = wv;
+        ++lc;
+      }
+    };
+    unsigned* srow = Sw;  // the row in use; the other of the two is the next one's
+    if (wv < Ws) {
+      next_row();
+      store_row<SX>(Sw, g.SLD, lane, sv);
+      next_row();
+    }
+    stage_template(0, T0);
+    __syncthreads();
+
+    unsigned* Tl = T0;
     for (int c = 0; c < jd.m; ++c) {
-      __syncthreads();  // MFMA reads of the previous channel are done
-      stage_rows(Tl, g.TLD, g.TROWS, NP, jd.volA + c * planeA + (ptrdiff_t)(ty0 - D_TPAD) * jd.wA + tx0, jd.wA, N,
-                 [&](int tr) { return tr >= D_TPAD && tr < D_TPAD + N; }, wv, lane);
-      stage_rows(Sl, g.SLD, Ws, 2 * g.SLD, jd.volB + c * planeB + (size_t)sy0 * jd.wB + sx0, jd.wB, Ws,
-                 [](int) { return true; }, wv, lane);
-      __syncthreads();
-      // this wave's search rows; for row s the u_y blocks n whose template
-      // rows s - u_y meet [0, N) are those with 0 <= s - 16 n <= N + 14
+      // the next channel's template goes into the other buffer, a row of each
+      // wave per search row
+      const bool ahead = g.tbufs == 2 && c + 1 < jd.m;
+      unsigned* const Tn = T0 + (Tl == T0 ? tstep : 0);
+      const float* tnext = tsrc + (c + 1) * planeA;
+      float2 tv[TX];
+      const unsigned sh = (l16 & 1) * 2;  // e & 1 for every m
+      // fragment j: 8 bf16 of a search row from column 16 j + 8 kg + lane % 16;
+      // chunk kc takes j = 2 kc + m for block m, so two in a row share all but two
+      const int alo = (8 * kg + l16) >> 1;
+      auto load_a = [&](const unsigned* row, int j, unsigned (&raw)[5]) {
+#pragma unroll
+        for (int i = 0; i < 5; ++i) raw[i] = row[8 * j + alo + i];
+      };
+      auto align = [&](const unsigned (&raw)[5]) {
+        unsigned av[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) av[i] = __builtin_amdgcn_alignbyte(raw[i + 1], raw[i], sh);
+        return __builtin_bit_cast(bf16x8, av);
+      };
+      // template row s - 16 n - lane % 16, columns 32 kc + 8 kg .. + 7 (for a
+      // block that row s does not meet some other row, not used)
+      const unsigned* tb = Tl + (D_TPAD - l16) * g.TLD + 4 * kg;
+      auto load_b = [&](int s, int kc, uint4 (&bw)[NB]) {
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+          bw[n] = *reinterpret_cast<const uint4*>(tb + min(max(s - 16 * n, 0), N + D_TPAD - 1) * g.TLD + 16 * kc);
+      };
+      constexpr int NEW = NB < 2 ? NB : 2;  // fragments that the next chunk does not share
+      bf16x8 A[NB];
+      uint4 B[NB];
+      if (wv < Ws) {
+        unsigned raw[NB][5];
+#pragma unroll
+        for (int m = 0; m < NB; ++m) load_a(srow, m, raw[m]);
+        load_b(wv, 0, B);
+#pragma unroll
+        for (int m = 0; m < NB; ++m) A[m] = align(raw[m]);
+      }
+#pragma unroll 1
       for (int s = wv; s < Ws; s += D_NW) {
+        // for row s the u_y blocks n whose template rows s - u_y meet [0, N) are
+        // those with 0 <= s - 16 n <= N + 14
         const int nhi = min(NB - 1, s >> 4);
         const int nlo = max(0, (s - N + 1) >> 4);
-        const unsigned* srow = Sl + (size_t)s * g.SLD;
-        for (int kc = 0; kc < NP / 32; ++kc) {
-          // issue every operand read of this chunk before the first use
+        const int sn = min(s + D_NW, Ws - 1);  // the next row (at the end any: not used)
+        unsigned* const snext = Sw + (srow == Sw ? g.SLD : 0);
+        store_row<SX>(snext, g.SLD, lane, sv);
+        if (ahead && s > wv && s - D_NW < N) store_row<TX>(Tn + (D_TPAD + s - D_NW) * g.TLD, NP / 2, lane, tv);
+        next_row();
+        if (ahead && s < N) load_row<TX>(tnext + (size_t)s * jd.wA, N * 4, odd, lane, tv);
+        // the wave's lanes read each other's parts of the row
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int kc = 0; kc < NKC; ++kc) {
+          // the next chunk's operands are on their way while this one's are used
+          const bool row_end = kc + 1 == NKC;
           unsigned raw[NB][5];
+          uint4 Bn[NB];
 #pragma unroll
-          for (int m = 0; m < NB; ++m) {
-            // 8 bf16 of search row s from column 32 kc + 8 kg + 16 m + lane % 16
-            const unsigned* sp = srow + ((32 * kc + 8 * kg + 16 * m + l16) >> 1);
-#pragma unroll
-            for (int i = 0; i < 5; ++i) raw[m][i] = sp[i];
-          }
-          uint4 bw[NB];
-#pragma unroll
-          for (int n = 0; n < NB; ++n) {
-            // template row s - 16 n - lane % 16, columns 32 kc + 8 kg .. + 7
-            // (rows of blocks outside [nlo, nhi] are clamped and not used)
-            const int tr = min(max(s - 16 * n - l16 + D_TPAD, 0), g.TROWS - 1);
-            bw[n] = *reinterpret_cast<const uint4*>(Tl + (size_t)tr * g.TLD + 16 * kc + 4 * kg);
-          }
-          const unsigned sh = (l16 & 1) * 2;  // e & 1 for every m
-          bf16x8 A[NB];
-#pragma unroll
-          for (int m = 0; m < NB; ++m) {
-            unsigned av[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) av[i] = __builtin_amdgcn_alignbyte(raw[m][i + 1], raw[m][i], sh);
-            A[m] = __builtin_bit_cast(bf16x8, av);
-          }
+          for (int m = row_end ? 0 : NB - NEW; m < NB; ++m)
+            load_a(row_end ? snext : srow, row_end ? m : 2 * (kc + 1) + m, raw[m]);
+          load_b(row_end ? sn : s, row_end ? 0 : kc + 1, Bn);
+          __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int n = 0; n < NB; ++n) {
             if (n >= nlo && n <= nhi) {
-              const bf16x8 B = __builtin_bit_cast(bf16x8, bw[n]);
 #pragma unroll
-              for (int m = 0; m < NB; ++m) acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[m], B, acc[m][n], 0, 0, 0);
+              for (int m = 0; m < NB; ++m)
+                acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[m], __builtin_bit_cast(bf16x8, B[n]), acc[m][n], 0, 0, 0);
             }
           }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int m = 0; m < NB; ++m) {
+            if (!row_end && m + 2 < NB) A[m] = A[m + 2];
+            else A[m] = align(raw[m]);
+          }
+#pragma unroll
+          for (int n = 0; n < NB; ++n) B[n] = Bn[n];
         }
+        srow = snext;
       }
+      if (ahead) {
+        // the last template row, where the loop ended before storing it
+        const int sl = wv + (Ws - 1 - wv) / D_NW * D_NW;
+        if (wv < Ws && sl < N) store_row<TX>(Tn + (D_TPAD + sl) * g.TLD, NP / 2, lane, tv);
+      } else if (c + 1 < jd.m) {
+        __syncthreads();  // MFMA reads of this channel are done
+        stage_template(c + 1, Tn);
+      }
+      __syncthreads();  // the next channel's template is whole, this one's no longer read
+      Tl = Tn;
     }
     __syncthreads();  // all MFMA reads of T/S are done: Cs and the partials may overwrite them
     // sum the waves' partial correlations in wave order (deterministic): D_PW
@@ -206,13 +316,15 @@ __global__ __launch_bounds__(D_NT) void match_direct_kernel(MatchJob jd, DirectG
     for (int w0 = 0; w0 < D_NW; w0 += D_PW) {
       if (wv >= w0 && wv < w0 + D_PW) {
         float* mine = part + (size_t)(wv - w0) * KK;
+        int lx = 4 * kg, ly = l16;  // (formed here, not kept across the points)
+        asm volatile("" : "+v"(lx), "+v"(ly));
 #pragma unroll
         for (int m = 0; m < NB; ++m)
 #pragma unroll
           for (int n = 0; n < NB; ++n)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-              const int ux = 16 * m + 4 * kg + q, uy = 16 * n + l16;
+              const int ux = 16 * m + lx + q, uy = 16 * n + ly;
               if (ux < K && uy < K) mine[uy * K + ux] = acc[m][n][q];
             }
       }
@@ -231,17 +343,32 @@ __global__ __launch_bounds__(D_NT) void match_direct_kernel(MatchJob jd, DirectG
 
 size_t direct_workspace_bytes(const cfog_job*, int, int, int) { return 0; }
 
-template <int NB>
-static void launch_nb(const MatchJob& d, const DirectGeom& g, int blocks, hipStream_t st) {
-  hipLaunchKernelGGL(match_direct_kernel<NB>, dim3(blocks), dim3(D_NT), g.lds, st, d, g);
+using DirectKernel = void (*)(MatchJob, DirectGeom);
+
+template <int NB, int... KC>
+static constexpr DirectKernel direct_kernel(int nkc, std::integer_sequence<int, KC...>) {
+  DirectKernel k = nullptr;
+  ((nkc == KC + 1 ? void(k = match_direct_kernel<NB, KC + 1>) : void()), ...);
+  return k;
+}
+// The kernel of nblk blocks of offsets and nkc chunks of template columns.
+static DirectKernel direct_kernel(int nblk, int nkc) {
+  constexpr std::make_integer_sequence<int, D_KC> kcs;
+  switch (nblk) {
+    case 1: return direct_kernel<1>(nkc, kcs);
+    case 2: return direct_kernel<2>(nkc, kcs);
+    case 3: return direct_kernel<3>(nkc, kcs);
+    case 4: return direct_kernel<4>(nkc, kcs);
+    default: return direct_kernel<5>(nkc, kcs);
+  }
 }
 
 int init_direct_attributes() {
-  const void* k[D_NB] = {(const void*)match_direct_kernel<1>, (const void*)match_direct_kernel<2>,
-                         (const void*)match_direct_kernel<3>, (const void*)match_direct_kernel<4>,
-                         (const void*)match_direct_kernel<5>};
-  for (int i = 0; i < D_NB; ++i)
-    if (hipFuncSetAttribute(k[i], hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds) != hipSuccess) return -2;
+  for (int nb = 1; nb <= D_NB; ++nb)
+    for (int kc = 1; kc <= D_KC; ++kc)
+      if (hipFuncSetAttribute((const void*)direct_kernel(nb, kc), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)kMaxLds) != hipSuccess)
+        return -2;
   return 0;
 }
 
@@ -263,13 +390,7 @@ int launch_match_direct(const cfog_job* jobs, int n_jobs, int m, int obj, void*,
     d.obj = obj;
     const int per_cu = std::max(1, (int)(kMaxLds / g.lds));
     const int blocks = std::min(j.n_cps, num_cus * per_cu);
-    switch (g.nblk) {
-      case 1: launch_nb<1>(d, g, blocks, st); break;
-      case 2: launch_nb<2>(d, g, blocks, st); break;
-      case 3: launch_nb<3>(d, g, blocks, st); break;
-      case 4: launch_nb<4>(d, g, blocks, st); break;
-      default: launch_nb<5>(d, g, blocks, st); break;
-    }
+    hipLaunchKernelGGL(direct_kernel(g.nblk, g.NP / 32), dim3(blocks), dim3(D_NT), g.lds, st, d, g);
     if (hipGetLastError() != hipSuccess) return -2;
   }
   return 0;
@@ -278,7 +399,8 @@ int launch_match_direct(const cfog_job* jobs, int n_jobs, int m, int obj, void*,
 bool direct_supported(int N, int r) {
   if (N < 1 || r < 0 || N > kMaxSide || r > kMaxSide) return false;
   const DirectGeom g = direct_geom(N, r);
-  return g.nblk <= D_NB && g.lds <= kMaxLds;
+  // the sizes that are taken: those whose template and search window fit LDS
+  return g.nblk <= D_NB && g.lds <= kMaxLds && g.t_bytes + (size_t)g.Ws * g.SLD * 4 <= kMaxLds;
 }
 
 }  // namespace cfog

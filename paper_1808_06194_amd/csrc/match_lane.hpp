@@ -127,14 +127,6 @@ constexpr LaneTables<C> make_lane_tables() {
 template <class C>
 __device__ const LaneTables<C> kLaneTables = make_lane_tables<C>();
 
-// The wave-uniform pointer p in scalar registers.
-template <class T>
-__device__ __forceinline__ const T* uniform_ptr(const T* p) {
-  const uint64_t v = reinterpret_cast<uint64_t>(p);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return reinterpret_cast<const T*>((uint64_t)hi << 32 | lo);
-}
-
 // One set of samples: n x n values at src, row stride ld (all wave-uniform, in
 // scalar registers: they make buffer descriptors).
 struct LaneSet {
