@@ -261,10 +261,12 @@ __global__ __launch_bounds__(HR_NT) void harris_grid_kernel(HarrisArgs a) {
     if (mine == bi && bi != INT_MAX) {
       cv[wv * a.k + q] = bv;
       cidx[wv * a.k + q] = bi;
+      if (q + 1 < a.k) {
 #pragma unroll
-      for (int t = 0; t < HR_RPT; ++t)
-        if (t == bt) rv[t] = NAN;
-      scan();
+        for (int t = 0; t < HR_RPT; ++t)
+          if (t == bt) rv[t] = NAN;
+        scan();
+      }
     }
     if (!tied) {
       if (x == 0) cidx[wv * a.k + q] = INT_MAX;
