@@ -142,12 +142,13 @@ __device__ __forceinline__ void tile_sat_prefix(double (&q)[EX_RUN], double* qx,
   if (!on) return;
   double up = 0.0;
   for (int i = 0; i < rg; ++i) up += qx[i * TX + oc];
-  const int W1 = W + 1;
+  const int W1 = W + 1, srow = __builtin_amdgcn_readfirstlane(y0 + orow);
+  double* const out = sat + (size_t)(srow + 1) * W1 + 1;
 #pragma unroll
   for (int o = 0; o < EX_RUN; ++o) {
     q[o] += up;
-    const int gyy = y0 + orow + o;
-    if (gyy < H && gxx < W) sat[(size_t)(gyy + 1) * W1 + gxx + 1] = q[o];
+    const int gyy = srow + o;
+    if (gyy < H && gxx < W) (out + (size_t)o * W1)[gxx] = q[o];
     if (oc == TX - 1 && gyy < H) rc[(size_t)gyy * ntx + blockIdx.x] = q[o];
   }
   if (rg == NRG - 1 && gxx < W) bt[(size_t)blockIdx.y * W + gxx] = q[EX_RUN - 1];
@@ -230,22 +231,37 @@ __global__ __launch_bounds__(EX_NT) __attribute__((amdgpu_waves_per_eu(M > 0 && 
   // the LDS stores so their latencies overlap.  Ordinary (cached) loads: the
   // tile below is dispatched to the same XCD whenever the tile grid is a
   // multiple of 8 tiles wide, and reads these halo rows again from its L2.
+  // A wave has one row at a time: its address is scalar, and a thread's column
+  // is the same in all of them.
   {
-    constexpr int NIT = (IH * IW + EX_NT - 1) / EX_NT;
-    float v[NIT];
+    constexpr int HX = 2 * R + 2;  // columns right of the first TX, spread over the threads
+    constexpr int NR = (IH + T::RPP - 1) / T::RPP, NE = (HX * IH + EX_NT - 1) / EX_NT;
+    const int c = tid % TX, rw = __builtin_amdgcn_readfirstlane(tid / TX);
+    const int xb = clampi(x0 - R - 1, 0, W - 1);
+    const unsigned gx = clampi(x0 - R - 1 + c, 0, W - 1) - xb;
+    float v[NR], e[NE];
 #pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-      const int i = tid + it * EX_NT;
-      if (i < IH * IW) {
-        const int r = i / IW, c = i - r * IW;
-        const int gy = clampi(y0 - R - 1 + r, 0, H - 1), gx = clampi(x0 - R - 1 + c, 0, W - 1);
-        v[it] = I.img[(int64_t)gy * I.stride + gx];
-      }
+    for (int it = 0; it < NR; ++it) {
+      const int r = rw + it * T::RPP;
+      if (IH % T::RPP == 0 || r < IH)
+        v[it] = (I.img + (int64_t)clampi(y0 - R - 1 + r, 0, H - 1) * I.stride + xb)[gx];
     }
 #pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-      const int i = tid + it * EX_NT;
-      if (i < IH * IW) img[i] = v[it];
+    for (int it = 0; it < NE; ++it) {
+      const int i = tid + it * EX_NT, r = i / HX;
+      if (i < HX * IH)
+        e[it] = I.img[(int64_t)clampi(y0 - R - 1 + r, 0, H - 1) * I.stride +
+                      clampi(x0 - R - 1 + TX + (i - r * HX), 0, W - 1)];
+    }
+#pragma unroll
+    for (int it = 0; it < NR; ++it) {
+      const int r = rw + it * T::RPP;
+      if (IH % T::RPP == 0 || r < IH) img[r * IW + c] = v[it];
+    }
+#pragma unroll
+    for (int it = 0; it < NE; ++it) {
+      const int i = tid + it * EX_NT, r = i / HX;
+      if (i < HX * IH) img[r * IW + TX + (i - r * HX)] = e[it];
     }
   }
   __syncthreads();

@@ -11,14 +11,6 @@
 
 namespace cfog {
 
-// The wave-uniform pointer p in scalar registers.
-template <class T>
-__device__ __forceinline__ const T* uniform_ptr(const T* p) {
-  const uint64_t v = reinterpret_cast<uint64_t>(p);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return reinterpret_cast<const T*>((uint64_t)hi << 32 | lo);
-}
-
 // Loads and stores through global-address-space pointers.  Device pointers
 // that reach a kernel inside job records have no known address space, so the
 // compiler would issue flat accesses, which also count as LDS operations:

@@ -6,6 +6,14 @@
 
 namespace cfog {
 
+// The wave-uniform pointer p in scalar registers.
+template <class T>
+__device__ __forceinline__ const T* uniform_ptr(const T* p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return reinterpret_cast<const T*>((uint64_t)hi << 32 | lo);
+}
+
 constexpr int kMaxOrient = 16;        // m <= 16 orientation channels (CFOG extraction)
 constexpr int kMaxChannels = 64;      // channels of a volume the matcher takes (FHOG: 36)
 constexpr int kMaxGaussRadius = 8;    // Gaussian radius R <= 8 taps each side
