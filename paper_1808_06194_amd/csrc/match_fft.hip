@@ -540,8 +540,10 @@ __global__ __launch_bounds__(C::NT) void match_fft_kernel(MatchJob job0, const M
 //  or more workgroups share a CU (16 waves at 128 VGPRs, so NT and WPE), above
 //  it one has the plane to itself.  Spread is for launches that leave each
 //  workgroup its CU, where a point's own waves are all there is to hide
-//  latency: 200 points took 61 -> 48, 70 -> 50, 73 -> 54, 104 -> 71, 71 -> 66,
-//  80 -> 66, 99 -> 84, 94 -> 79, 104 -> 94 us with it from P = 60 to 120.
+//  latency: 200 points took 61 -> 48, 70 -> 50, 73 -> 54, 104 -> 63, 71 -> 66,
+//  80 -> 65, 99 -> 84, 94 -> 79, 104 -> 89 us with it from P = 60 to 120.
+//  There 768 threads at three waves per SIMD (168 VGPRs) do not spill, where
+//  held to four they do (P = 120: 95 us).
 #define CFOG_PLANS(G, L)                                         \
   G(16, 4, 4, 64)                                                \
   G(24, 6, 4, 128)                                               \
@@ -551,12 +553,12 @@ __global__ __launch_bounds__(C::NT) void match_fft_kernel(MatchJob job0, const M
   L((60, 6, 10, 15, 4, 10, 6), (192, 1, 4), (512, 1, 4))         \
   L((64, 8, 8, 8, 8, 8, 8), (256, 1, 4), (512, 1, 4))            \
   L((72, 6, 12, 9, 8, 9, 8), (256, 1, 4), (512, 1, 4))           \
-  L((80, 5, 16, 5, 16, 10, 8), (256, 0, 4), (1024, 1, 4))        \
+  L((80, 5, 16, 5, 16, 10, 8), (256, 0, 4), (768, 2, 3))         \
   L((90, 9, 10, 9, 10, 10, 9), (512, 1, 4), (768, 1, 4))         \
-  L((96, 8, 12, 12, 8, 12, 8), (512, 1, 4), (768, 1, 4))         \
+  L((96, 8, 12, 12, 8, 12, 8), (512, 1, 4), (768, 1, 3))         \
   L((100, 10, 10, 5, 20, 10, 10), (512, 0, 4), (1024, 1, 4))     \
   L((108, 9, 12, 9, 12, 12, 9), (512, 1, 4), (1024, 1, 4))       \
-  L((120, 8, 15, 15, 8, 12, 10), (512, 1, 4), (768, 1, 4))       \
+  L((120, 8, 15, 15, 8, 12, 10), (512, 1, 4), (768, 1, 3))       \
   L((144, 12, 12, 12, 12, 12, 12), (1024, 1, 4), (1024, 1, 4))   \
   L((160, 10, 16, 20, 8, 16, 10), (896, 0, 4), (896, 0, 4))      \
   L((192, 24, 8, 24, 8, 16, 12), (512, 0, 2), (512, 0, 2))       \
