@@ -358,14 +358,12 @@ struct RDftPfa {
   }
 };
 
-template <> struct RDft<6> : RDftPfa<2, 3> {};
 template <> struct RDft<8> : RDftSplit<4, 2> {};
 template <> struct RDft<9> : RDftSplit<3, 3> {};
 template <> struct RDft<10> : RDftPfa<2, 5> {};
 template <> struct RDft<12> : RDftPfa<4, 3> {};
 template <> struct RDft<15> : RDftPfa<3, 5> {};
 template <> struct RDft<16> : RDftSplit<4, 4> {};
-template <> struct RDft<18> : RDftPfa<2, 9> {};
 template <> struct RDft<20> : RDftPfa<4, 5> {};
 template <> struct RDft<24> : RDftPfa<8, 3> {};
 
