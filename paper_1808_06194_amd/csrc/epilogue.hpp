@@ -67,8 +67,10 @@ __device__ __forceinline__ double parabola_vertex(double a, double b, double c) 
   return den > 0.0 ? 0.5 * (a - c) / den : 0.0;
 }
 
-// Writes the result of control point cpi of job jd from the correlation, read
-// as corr(u_y * K + u_x, u_y, u_x) (all K*K values visible to the workgroup):
+// Writes the result of control point cpi of job jd from the correlation
+// Cs[u_y * K + u_x] in LDS.  The pass over the offsets takes each value as
+// corr(u_y * K + u_x), which either reads it from Cs (all K*K values visible to
+// the workgroup) or forms it and leaves it there:
 //   SSD(u) = E1 + E2(u) - 2 C(u), summed in FP64 and rounded to FP32
 //   (objective of Eq. 7: -C(u) instead, without the energies),
 // surfaces (if requested), argmin (ties to the smallest index), the smallest
@@ -78,7 +80,7 @@ __device__ __forceinline__ double parabola_vertex(double a, double b, double c) 
 // red: NT/64 ArgminState of LDS scratch.
 template <int NT, class Corr>
 __device__ __forceinline__ void ssd_epilogue(const MatchJob& jd, int cpi, int tx0, int ty0, int sx0, int sy0,
-                                             Corr&& corr, ArgminState* red) {
+                                             const float* Cs, Corr&& corr, ArgminState* red) {
   const int N = jd.N, r = jd.r, K = 2 * r + 1;
   const bool eq7 = jd.obj != 0;
   ArgminState st{INFINITY, INT_MAX, INFINITY, 0};
@@ -89,29 +91,27 @@ __device__ __forceinline__ void ssd_epilogue(const MatchJob& jd, int cpi, int tx
   auto value_at = [&](int idx) -> float {
     const int uy = idx / K, ux = idx - uy * K;
     const double E2 = energy(uy, ux);
-    return value(E2, corr(idx, uy, ux));
+    return value(E2, Cs[idx]);
   };
   float* surf = jd.surfaces ? jd.surfaces + (size_t)cpi * K * K : nullptr;
   // EP offsets of a thread at a time: their table reads are in flight together
   // (one at a time, 9 rounds of a far table's latency at K = 65 and 512
   // threads)
   constexpr int EP = 4;
+  const int wave0 = __builtin_amdgcn_readfirstlane((int)threadIdx.x);  // a wave without offsets has none to read
   for (int b = 0; b < K * K; b += EP * NT) {
     double E2[EP];
-    int uy[EP], ux[EP];
 #pragma unroll
     for (int t = 0; t < EP; ++t) {
-      if (b + t * NT >= K * K) break;
-      const int idx = min(b + t * NT + (int)threadIdx.x, K * K - 1);
-      uy[t] = idx / K;
-      ux[t] = idx - uy[t] * K;
-      E2[t] = energy(uy[t], ux[t]);
+      if (b + t * NT + wave0 >= K * K) break;
+      const int idx = min(b + t * NT + (int)threadIdx.x, K * K - 1), uy = idx / K;
+      E2[t] = energy(uy, idx - uy * K);
     }
 #pragma unroll
     for (int t = 0; t < EP; ++t) {
       const int idx = b + t * NT + (int)threadIdx.x;
       if (idx < K * K) {
-        const float s = value(E2[t], corr(idx, uy[t], ux[t]));
+        const float s = value(E2[t], corr(idx));
         am_push(st, s, idx);
         if (surf) stg(surf + idx, s);
       }

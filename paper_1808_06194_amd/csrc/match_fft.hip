@@ -472,7 +472,7 @@ __device__ __forceinline__ void match_one(const Lane<C>& L, const MatchJob& jd, 
     for (int i = threadIdx.x; i < K * K; i += NT) stg(part + i, Cs[i]);
     return;
   }
-  ssd_epilogue<NT>(jd, cpi, tx0, ty0, sx0, sy0, [&](int i, int, int) { return Cs[i]; }, red);
+  ssd_epilogue<NT>(jd, cpi, tx0, ty0, sx0, sy0, Cs, [&](int i) { return Cs[i]; }, red);
 }
 
 // One kernel for both paths: with jobs == nullptr every task t is control
@@ -652,13 +652,19 @@ int plan_split_slots(const FftPlan* p, int num_cus) {
 }
 
 // One workgroup per split task: the epilogue over the sum of its G partial
-// surfaces (in item order), which each thread forms as it goes.  Bound by the
-// latency of its reads, so all of an offset's are in flight together.
+// surfaces (in item order), which each thread forms as it goes and leaves in
+// LDS for the sub-pixel step's neighbours.  Bound by the latency of its reads, so
+// all of an offset's are in flight together; and two workgroups share a CU,
+// which needs the SGPRs of eight waves per SIMD: seven left a CU one (300 points
+// of N = 16, r = 3 with sub-pixel output, both launches: 25.5 us with one
+// workgroup to a CU and the neighbours' partials read again, 22.2 so).
 constexpr int SR_NT = 1024;
 constexpr int SR_MAX_G = 16;  // plan_split_choice's limit
-__global__ __launch_bounds__(SR_NT) void split_reduce_kernel(MatchJob job0, const MatchJob* __restrict__ jobs,
-                                                            const int2* __restrict__ tasks, SplitArgs sp) {
-  __shared__ ArgminState red[SR_NT / 64];
+__global__ __launch_bounds__(SR_NT) __attribute__((amdgpu_waves_per_eu(8))) void split_reduce_kernel(
+    MatchJob job0, const MatchJob* __restrict__ jobs, const int2* __restrict__ tasks, SplitArgs sp) {
+  extern __shared__ float4 sr_lds[];
+  ArgminState* red = reinterpret_cast<ArgminState*>(sr_lds);
+  float* Cs = reinterpret_cast<float*>(red + SR_NT / 64);
   const int t = sp.n_whole + blockIdx.x;
   MatchJob jd = job0;
   int cpi = t;
@@ -671,25 +677,33 @@ __global__ __launch_bounds__(SR_NT) void split_reduce_kernel(MatchJob job0, cons
   const CpBoxes bx = cp_boxes(cp.x, cp.y, cp.z, cp.w, jd.N, jd.r, jd.hA, jd.wA, jd.hB, jd.wB);
   if (!bx.inside) return;  // reported by the task's first item
   const float* p = sp.part + (size_t)blockIdx.x * sp.G * sp.slot;
-  auto corr = [&](int idx, int, int) -> float {
+  auto corr = [&](int idx) -> float {
     float v[SR_MAX_G];
+    unsigned o = idx;
 #pragma unroll
-    for (int g = 0; g < SR_MAX_G; ++g)
-      if (g < sp.G) v[g] = ldg(p + (size_t)g * sp.slot + idx);
+    for (int g = 0; g < SR_MAX_G; ++g) {
+      if (g >= sp.G) break;
+      v[g] = ldg(p + o);
+      o += sp.slot;
+    }
     float s = v[0];
 #pragma unroll
-    for (int g = 1; g < SR_MAX_G; ++g)
-      if (g < sp.G) s += v[g];
-    return s;
+    for (int g = 1; g < SR_MAX_G; ++g) {
+      if (g >= sp.G) break;
+      s += v[g];
+    }
+    return Cs[idx] = s;
   };
-  ssd_epilogue<SR_NT>(jd, cpi, bx.tx0, bx.ty0, bx.sx0, bx.sy0, corr, red);
+  ssd_epilogue<SR_NT>(jd, cpi, bx.tx0, bx.ty0, bx.sx0, bx.sy0, Cs, corr, red);
 }
 
 int launch_split_reduce(const MatchJob& job0, const MatchJob* d_jobs, const int2* d_tasks, int n_tasks,
                         const SplitArgs& sp, hipStream_t st) {
   if (sp.G <= 1 || n_tasks <= sp.n_whole) return 0;
-  if (sp.G > SR_MAX_G) return -1;
-  hipLaunchKernelGGL(split_reduce_kernel, dim3(n_tasks - sp.n_whole), dim3(SR_NT), 0, st, job0, d_jobs, d_tasks, sp);
+  const size_t lds = sizeof(ArgminState) * (SR_NT / 64) + sizeof(float) * (size_t)sp.slot;
+  if (sp.G > SR_MAX_G || lds > 64 * 1024) return -1;
+  hipLaunchKernelGGL(split_reduce_kernel, dim3(n_tasks - sp.n_whole), dim3(SR_NT), lds, st, job0, d_jobs, d_tasks,
+                     sp);
   return hipGetLastError() == hipSuccess ? 0 : -2;
 }
 
