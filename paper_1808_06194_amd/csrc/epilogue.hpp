@@ -68,9 +68,7 @@ __device__ __forceinline__ double parabola_vertex(double a, double b, double c) 
 }
 
 // Writes the result of control point cpi of job jd from the correlation
-// Cs[u_y * K + u_x] in LDS.  The pass over the offsets takes each value as
-// corr(u_y * K + u_x), which either reads it from Cs (all K*K values visible to
-// the workgroup) or forms it and leaves it there:
+// Cs[u_y * K + u_x] (LDS, all K*K values visible to the workgroup):
 //   SSD(u) = E1 + E2(u) - 2 C(u), summed in FP64 and rounded to FP32
 //   (objective of Eq. 7: -C(u) instead, without the energies),
 // surfaces (if requested), argmin (ties to the smallest index), the smallest
@@ -78,9 +76,9 @@ __device__ __forceinline__ double parabola_vertex(double a, double b, double c) 
 // parabola through the best value and its axis neighbours.  (tx0, ty0):
 // template top-left in A; (sx0, sy0): search-window top-left in B.
 // red: NT/64 ArgminState of LDS scratch.
-template <int NT, class Corr>
+template <int NT, int EP = 4>
 __device__ __forceinline__ void ssd_epilogue(const MatchJob& jd, int cpi, int tx0, int ty0, int sx0, int sy0,
-                                             const float* Cs, Corr&& corr, ArgminState* red) {
+                                             const float* Cs, ArgminState* red) {
   const int N = jd.N, r = jd.r, K = 2 * r + 1;
   const bool eq7 = jd.obj != 0;
   ArgminState st{INFINITY, INT_MAX, INFINITY, 0};
@@ -97,7 +95,6 @@ __device__ __forceinline__ void ssd_epilogue(const MatchJob& jd, int cpi, int tx
   // EP offsets of a thread at a time: their table reads are in flight together
   // (one at a time, 9 rounds of a far table's latency at K = 65 and 512
   // threads)
-  constexpr int EP = 4;
   const int wave0 = __builtin_amdgcn_readfirstlane((int)threadIdx.x);  // a wave without offsets has none to read
   for (int b = 0; b < K * K; b += EP * NT) {
     double E2[EP];
@@ -111,7 +108,7 @@ __device__ __forceinline__ void ssd_epilogue(const MatchJob& jd, int cpi, int tx
     for (int t = 0; t < EP; ++t) {
       const int idx = b + t * NT + (int)threadIdx.x;
       if (idx < K * K) {
-        const float s = value(E2[t], corr(idx));
+        const float s = value(E2[t], Cs[idx]);
         am_push(st, s, idx);
         if (surf) stg(surf + idx, s);
       }

@@ -337,7 +337,7 @@ __global__ __launch_bounds__(D_NT) void match_direct_kernel(MatchJob jd, DirectG
       }
       __syncthreads();
     }
-    ssd_epilogue<D_NT>(jd, cpi, tx0, ty0, sx0, sy0, Cs, [&](int i) { return Cs[i]; }, red);
+    ssd_epilogue<D_NT>(jd, cpi, tx0, ty0, sx0, sy0, Cs, red);
   }
 }
 

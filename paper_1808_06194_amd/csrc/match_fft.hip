@@ -472,7 +472,7 @@ __device__ __forceinline__ void match_one(const Lane<C>& L, const MatchJob& jd, 
     for (int i = threadIdx.x; i < K * K; i += NT) stg(part + i, Cs[i]);
     return;
   }
-  ssd_epilogue<NT>(jd, cpi, tx0, ty0, sx0, sy0, Cs, [&](int i) { return Cs[i]; }, red);
+  ssd_epilogue<NT>(jd, cpi, tx0, ty0, sx0, sy0, Cs, red);
 }
 
 // One kernel for both paths: with jobs == nullptr every task t is control
@@ -651,16 +651,16 @@ int plan_split_slots(const FftPlan* p, int num_cus) {
   return p->lane ? num_cus * (p->P <= 72 ? 2 : 1) : plan_slots(p, num_cus);
 }
 
-// One workgroup per split task: the epilogue over the sum of its G partial
-// surfaces (in item order), which each thread forms as it goes and leaves in
-// LDS for the sub-pixel step's neighbours.  Bound by the latency of its reads, so
-// all of an offset's are in flight together; and two workgroups share a CU,
-// which needs the SGPRs of eight waves per SIMD: seven left a CU one (300 points
-// of N = 16, r = 3 with sub-pixel output, both launches: 25.5 us with one
-// workgroup to a CU and the neighbours' partials read again, 22.2 so).
+// One workgroup per split task: the sum of its G partial surfaces (in item
+// order) into LDS, eight of an offset's partials in flight at a time, then the
+// epilogue of the whole sum.  Bound by the latency of those reads, and past 256
+// tasks by the rounds of workgroups: 52 SGPRs let two share a CU.  Summing as
+// the epilogue goes took 106 (one to a CU), and with sub-pixel output read the
+// neighbours' partials again: N = 16, r = 3, 272 points in both launches 22.2 us,
+// with sub-pixel output 25.1; 20.3 and 21.1 so.
 constexpr int SR_NT = 1024;
-constexpr int SR_MAX_G = 16;  // plan_split_choice's limit
-__global__ __launch_bounds__(SR_NT) __attribute__((amdgpu_waves_per_eu(8))) void split_reduce_kernel(
+constexpr int SR_NG = 8;
+__global__ __launch_bounds__(SR_NT) void split_reduce_kernel(
     MatchJob job0, const MatchJob* __restrict__ jobs, const int2* __restrict__ tasks, SplitArgs sp) {
   extern __shared__ float4 sr_lds[];
   ArgminState* red = reinterpret_cast<ArgminState*>(sr_lds);
@@ -677,31 +677,35 @@ __global__ __launch_bounds__(SR_NT) __attribute__((amdgpu_waves_per_eu(8))) void
   const CpBoxes bx = cp_boxes(cp.x, cp.y, cp.z, cp.w, jd.N, jd.r, jd.hA, jd.wA, jd.hB, jd.wB);
   if (!bx.inside) return;  // reported by the task's first item
   const float* p = sp.part + (size_t)blockIdx.x * sp.G * sp.slot;
-  auto corr = [&](int idx) -> float {
-    float v[SR_MAX_G];
-    unsigned o = idx;
+  const int KK = (2 * jd.r + 1) * (2 * jd.r + 1);
+  for (int i = threadIdx.x; i < KK; i += SR_NT) {
+    unsigned o = i;
+    float s = ldg(p + o);
+    for (int g = 1; g < sp.G; g += SR_NG) {
+      float v[SR_NG];
 #pragma unroll
-    for (int g = 0; g < SR_MAX_G; ++g) {
-      if (g >= sp.G) break;
-      v[g] = ldg(p + o);
-      o += sp.slot;
-    }
-    float s = v[0];
+      for (int u = 0; u < SR_NG; ++u) {
+        if (g + u >= sp.G) break;
+        o += sp.slot;
+        v[u] = ldg(p + o);
+      }
 #pragma unroll
-    for (int g = 1; g < SR_MAX_G; ++g) {
-      if (g >= sp.G) break;
-      s += v[g];
+      for (int u = 0; u < SR_NG; ++u) {
+        if (g + u >= sp.G) break;
+        s += v[u];
+      }
     }
-    return Cs[idx] = s;
-  };
-  ssd_epilogue<SR_NT>(jd, cpi, bx.tx0, bx.ty0, bx.sx0, bx.sy0, Cs, corr, red);
+    Cs[i] = s;
+  }
+  __syncthreads();
+  ssd_epilogue<SR_NT, 1>(jd, cpi, bx.tx0, bx.ty0, bx.sx0, bx.sy0, Cs, red);
 }
 
 int launch_split_reduce(const MatchJob& job0, const MatchJob* d_jobs, const int2* d_tasks, int n_tasks,
                         const SplitArgs& sp, hipStream_t st) {
   if (sp.G <= 1 || n_tasks <= sp.n_whole) return 0;
   const size_t lds = sizeof(ArgminState) * (SR_NT / 64) + sizeof(float) * (size_t)sp.slot;
-  if (sp.G > SR_MAX_G || lds > 64 * 1024) return -1;
+  if (lds > 64 * 1024) return -1;
   hipLaunchKernelGGL(split_reduce_kernel, dim3(n_tasks - sp.n_whole), dim3(SR_NT), lds, st, job0, d_jobs, d_tasks,
                      sp);
   return hipGetLastError() == hipSuccess ? 0 : -2;

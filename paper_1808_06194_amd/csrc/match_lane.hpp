@@ -499,7 +499,7 @@ __device__ __forceinline__ void lane_match_one(const MatchJob& jd, int cpi, floa
     for (int i = threadIdx.x; i < K * K; i += NT) stg(part + i, Cs[i]);
     return;
   }
-  ssd_epilogue<NT>(jd, cpi, bx.tx0, bx.ty0, bx.sx0, bx.sy0, Cs, [&](int i) { return Cs[i]; }, red);
+  ssd_epilogue<NT>(jd, cpi, bx.tx0, bx.ty0, bx.sx0, bx.sy0, Cs, red);
 }
 
 // The kernel: arguments and work items as match_fft_kernel.
