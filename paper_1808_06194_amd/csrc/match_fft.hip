@@ -525,43 +525,45 @@ __global__ __launch_bounds__(C::NT) void match_fft_kernel(MatchJob job0, const M
 //  lane layout (46-50, 55-60 and 67-71 against 49, 57 and 65 us per 1,024
 //  points): there a point is a few waves' work on either.
 //  Lane layout, L((P, R1, R2, RA, RB, I1, I2), full, spread), each a workgroup
-//  (NT, PF, waves per SIMD): from 49 up, per 1,024 points of template N and
+//  (NT, PF, waves per SIMD, SEP): from 49 up, per 1,024 points of template N and
 //  radius r, unsplit, before (the group layout) and after:
 //    N, r     P   before  after     N, r     P   before  after
-//    44,  8   60   142 ->  80 us    72, 12   96   336 -> 205 us
-//    44,  9   64   129 ->  99       70, 15  100   319 -> 238
-//    52, 10   72   261 -> 107       80, 14  108   356 -> 254
-//    60, 10   80   246 -> 151       80, 20  120   405 -> 294
-//    66, 12   90   278 -> 185      100, 20  144   541 -> 449
-//                                  118, 20  160   732 -> 555
-//                                  128, 32  192   922 -> 849
+//    44,  8   60   127 ->  66 us    72, 12   96   311 -> 170 us
+//    44,  9   64   116 ->  85       70, 15  100   290 -> 195
+//    52, 10   72   249 ->  89       80, 14  108   319 -> 202
+//    60, 10   80   228 -> 127       80, 20  120   362 -> 246
+//    66, 12   90   251 -> 162      100, 20  144   494 -> 400
+//                                  118, 20  160   707 -> 498
+//                                  128, 32  192   882 -> 809
 //  The factors keep the wave-sized pieces of each phase at a multiple of four
 //  (a SIMD each) and the x2 items at one or two to a thread; up to P = 120 two
 //  or more workgroups share a CU (16 waves at 128 VGPRs, so NT and WPE), above
 //  it one has the plane to itself.  Spread is for launches that leave each
 //  workgroup its CU, where a point's own waves are all there is to hide
-//  latency: 200 points took 61 -> 48, 70 -> 50, 73 -> 54, 104 -> 63, 71 -> 66,
-//  80 -> 65, 99 -> 84, 94 -> 79, 104 -> 89 us with it from P = 60 to 120.
-//  There 768 threads at three waves per SIMD (168 VGPRs) do not spill, where
-//  held to four they do (P = 120: 95 us).
+//  latency (launch_lane).  768 threads at three waves per SIMD (168 VGPRs) do not
+//  spill, where held to four they may (P = 120, 200 points: 95 us against 79;
+//  P = 100: 74 us with 1,024 threads against 66).
+//  P = 80 had factors 5 16 (x) and 5 16 (y), 256 threads at 49 spilled VGPRs to a
+//  full workgroup: alone on a CU one took 106 us, so that 272 points were slower
+//  than with the group layout (76 us; now 60).
 #define CFOG_PLANS(G, L)                                         \
   G(16, 4, 4, 64)                                                \
   G(24, 6, 4, 128)                                               \
   G(32, 8, 4, 256)                                               \
   G(40, 8, 5, 256)                                               \
   G(48, 8, 6, 256)                                               \
-  L((60, 6, 10, 15, 4, 10, 6), (192, 1, 4), (512, 1, 4))         \
-  L((64, 8, 8, 8, 8, 8, 8), (256, 1, 4), (512, 1, 4))            \
-  L((72, 6, 12, 9, 8, 9, 8), (256, 1, 4), (512, 1, 4))           \
-  L((80, 5, 16, 5, 16, 10, 8), (256, 0, 4), (768, 2, 3))         \
-  L((90, 9, 10, 9, 10, 10, 9), (512, 1, 4), (768, 1, 4))         \
-  L((96, 8, 12, 12, 8, 12, 8), (512, 1, 4), (768, 1, 3))         \
-  L((100, 10, 10, 5, 20, 10, 10), (512, 0, 4), (1024, 1, 4))     \
-  L((108, 9, 12, 9, 12, 12, 9), (512, 1, 4), (1024, 1, 4))       \
-  L((120, 8, 15, 15, 8, 12, 10), (512, 1, 4), (768, 1, 3))       \
-  L((144, 12, 12, 12, 12, 12, 12), (1024, 1, 4), (1024, 1, 4))   \
-  L((160, 10, 16, 20, 8, 16, 10), (896, 0, 4), (896, 0, 4))      \
-  L((192, 24, 8, 24, 8, 16, 12), (512, 0, 2), (512, 0, 2))       \
+  L((60, 6, 10, 15, 4, 10, 6), (192, 1, 4, 1), (512, 1, 4, 1))       \
+  L((64, 8, 8, 8, 8, 8, 8), (256, 1, 4, 0), (512, 1, 4, 1))          \
+  L((72, 6, 12, 9, 8, 9, 8), (256, 1, 4, 1), (512, 1, 4, 1))         \
+  L((80, 10, 8, 10, 8, 10, 8), (512, 1, 2, 1), (768, 1, 3, 1))       \
+  L((90, 9, 10, 9, 10, 10, 9), (512, 1, 4, 0), (768, 1, 4, 1))       \
+  L((96, 8, 12, 12, 8, 12, 8), (512, 1, 4, 1), (768, 1, 3, 1))       \
+  L((100, 10, 10, 5, 20, 10, 10), (512, 1, 4, 1), (768, 2, 3, 1))    \
+  L((108, 9, 12, 9, 12, 12, 9), (512, 1, 4, 1), (1024, 1, 4, 0))     \
+  L((120, 8, 15, 15, 8, 12, 10), (512, 1, 4, 0), (768, 1, 3, 0))     \
+  L((144, 12, 12, 12, 12, 12, 12), (1024, 1, 4, 0), (1024, 1, 4, 0)) \
+  L((160, 10, 16, 20, 8, 16, 10), (896, 0, 4, 0), (896, 0, 4, 0))    \
+  L((192, 24, 8, 24, 8, 16, 12), (512, 0, 2, 1), (512, 0, 2, 1))     \
   G(192, 16, 12, 512)
 
 #define CFOG_ARGS(...) __VA_ARGS__
@@ -580,13 +582,24 @@ constexpr int resident() {
   return std::max(1, std::min((int)(kMaxLds / W::LDS), 4 * W::WPE / W::NW));
 }
 
-// C, or where the whole launch is resident at once with the larger workgroup,
-// W: the points then have the CUs to themselves, and more waves to a point is
-// what is left.
+// W (spread) where the whole launch is resident at once with it, else C (full):
+// the points then have the CUs to themselves, and more waves to a point is what is
+// left.  Full against spread workgroups, us at 256 / 272 / 400 points:
+//   P = 80    53 against 50   60 / 65     80 / 92
+//   P = 90    64         60   71 / 76     96 / 109
+//   P = 100   81         68   88 / 87    119 / 123
+//   P = 120   94         80  105 / 103   141 / 148
+// With two W to a CU (P = 60 to 72), where full workgroups of half its waves are
+// four to a CU, a whole round and a split rest are still shorter with W while that
+// rest is small: P = 64 at 520, 600 and 700 points 77 / 59, 80 / 69 and 97 / 83,
+// but at 768 points 83 / 87; P = 72 at 768 points 85 / 95.
 template <class C, class W>
 static int launch_lane(const MatchJob& job0, const MatchJob* jobs, const int2* tasks, int n_tasks, int n_blocks,
                        const SplitArgs& sp, int num_cus, hipStream_t st) {
-  if (n_blocks <= resident<W>() * num_cus)
+  const int slots = resident<W>() * num_cus;
+  const bool round_and_rest = resident<W>() > 1 && 2 * C::NT >= W::NT && sp.n_whole == slots &&
+                              5 * (n_tasks - slots) <= 2 * slots;
+  if (n_blocks <= slots || round_and_rest)
     hipLaunchKernelGGL(match_lane_kernel<W>, dim3(n_blocks), dim3(W::NT), W::LDS, st, job0, jobs, tasks, n_tasks, sp);
   else
     hipLaunchKernelGGL(match_lane_kernel<C>, dim3(n_blocks), dim3(C::NT), C::LDS, st, job0, jobs, tasks, n_tasks, sp);

@@ -59,14 +59,18 @@ constexpr int max_offsets(int P) {
 
 // PF: y1 items of a thread whose loads are issued during the x2 phase before.
 // WPE: waves per SIMD that the registers are held to.
+// SEP: the real items of y2 are the last threads', so that no wave has both a
+// real and a complex transform to run one after the other; else the first ones',
+// which takes fewer registers.
 // Coprime R1, R2 use the prime-factor map (DftPfa in dft.hpp): no twiddles
 // between the x stages.  Column x = (R2 a + R1 b) mod P of the plane is then
 // kept at position a R2 + b, so that the accesses are those of the
 // common-factor case, where position and column are the same.
-template <int P_, int R1_, int R2_, int RA_, int RB_, int I1_, int I2_, int NT_, int PF_ = 0, int WPE_ = 0>
+template <int P_, int R1_, int R2_, int RA_, int RB_, int I1_, int I2_, int NT_, int PF_, int WPE_, int SEP_>
 struct LaneCfg {
   static constexpr int P = P_, R1 = R1_, R2 = R2_, RA = RA_, RB = RB_, I1 = I1_, I2 = I2_, NT = NT_, PF = PF_;
-  static constexpr int WPE = WPE_ ? WPE_ : (NT + 255) / 256;  // waves per SIMD the registers must allow
+  static constexpr int WPE = WPE_;
+  static constexpr bool SEP = SEP_ != 0;
   static_assert(P == R1 * R2 && P == RA * RB && P == I1 * I2, "factors");
   static constexpr int PH = P / 2 + 1;
   static_assert(NT % 64 == 0 && NT <= 1024, "bad workgroup size");
@@ -201,32 +205,41 @@ __device__ __forceinline__ void lane_ypass(const LaneSet& S, float (&u)[C::PF ? 
     lane_y1<C>(it.x, it.y, w, X, twy, pos);
   }
   __syncthreads();
+  // The real transform of column x's k1 = 0 values, and the complex one of the
+  // values at col.
+  auto real = [&](float2* col) {
+    float r[RB + 1];
+    float2 v[RB / 2 + 1];
+#pragma unroll
+    for (int t = 0; t < (RB + 1) / 2; ++t) {
+      const float2 z = col[t * LD];
+      r[2 * t] = z.x;
+      r[2 * t + 1] = z.y;
+    }
+    rdft<RB>(r, v);
+#pragma unroll
+    for (int k = 0; k < RB / 2 + 1; ++k) col[k * LD] = v[k];
+  };
+  auto complex = [&](float2* col) {
+    float2 v[RB];
+#pragma unroll
+    for (int b = 0; b < RB; ++b) v[b] = col[b * LD];
+    dft<RB, -1>(v);
+#pragma unroll
+    for (int b = 0; b < RB; ++b) col[b * LD] = v[b];
+  };
+  constexpr int FIRST = C::SEP ? 1 : 0;  // the k1 of item 0
   const float inv = 1.0f / (float)n;
 #pragma unroll 1
-  for (int i = threadIdx.x; i < n * (C::KH + 1); i += NT) {
-    const int k1 = (int)(((float)i + 0.5f) * inv), x = i - k1 * n, p = C::PFA ? pos[x] : x;
-    if (k1 == 0) {
-      float2* col = X + p;
-      float r[RB + 1];
-      float2 v[RB / 2 + 1];
-#pragma unroll
-      for (int t = 0; t < (RB + 1) / 2; ++t) {
-        const float2 z = col[t * LD];
-        r[2 * t] = z.x;
-        r[2 * t + 1] = z.y;
-      }
-      rdft<RB>(r, v);
-#pragma unroll
-      for (int k = 0; k < RB / 2 + 1; ++k) col[k * LD] = v[k];
-    } else {
-      float2* col = X + (C::ROW1 + (k1 - 1) * RB) * LD + p;
-      float2 v[RB];
-#pragma unroll
-      for (int b = 0; b < RB; ++b) v[b] = col[b * LD];
-      dft<RB, -1>(v);
-#pragma unroll
-      for (int b = 0; b < RB; ++b) col[b * LD] = v[b];
-    }
+  for (int i = threadIdx.x; i < n * (C::KH + 1 - FIRST); i += NT) {
+    const int q = (int)(((float)i + 0.5f) * inv), x = i - q * n, k1 = q + FIRST;
+    float2* col = X + (C::PFA ? pos[x] : x);
+    if (!C::SEP && k1 == 0) real(col);
+    else complex(col + (C::ROW1 + (k1 - 1) * RB) * LD);
+  }
+  if constexpr (C::SEP) {
+#pragma unroll 1
+    for (int x = NT - 1 - (int)threadIdx.x; x < n; x += NT) real(X + (C::PFA ? pos[x] : x));
   }
   // the columns past the set are zero (the x stages of the set before wrote
   // them): a thread stays in its row

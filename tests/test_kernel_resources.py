@@ -48,3 +48,16 @@ def test_two_reduce_workgroups_share_a_cu(kernels):
     assert k["vgpr_count"] <= 64 and k["sgpr_count"] <= 96 and k["private_segment_fixed_size"] == 0
     largest = max((2 * r + 1) ** 2 for r in range(96) if cfog.fft_size(1, r))
     assert 4 * largest + 16 * 16 + k["group_segment_fixed_size"] <= 64 * 1024
+
+
+def _lane(kernels, head, team):
+    return kernels["match_lane_kernel<LaneCfg<%s, %s> >" % (head, team)]
+
+
+def test_lane_workgroups_of_80_and_100(kernels):
+    """Two full workgroups of 512 threads to a CU (128 VGPRs), and no spills at P = 80 and in the spread forms."""
+    for head, team in (("80, 10, 8, 10, 8, 10, 8", "512, 1, 2, 1"), ("80, 10, 8, 10, 8, 10, 8", "768, 1, 3, 1"),
+                       ("100, 10, 10, 5, 20, 10, 10", "768, 2, 3, 1")):
+        k = _lane(kernels, head, team)
+        assert k["private_segment_fixed_size"] == 0 and k["vgpr_count"] <= (128 if "512" in team else 168)
+    assert _lane(kernels, "100, 10, 10, 5, 20, 10, 10", "512, 1, 4, 1")["vgpr_count"] <= 128
