@@ -94,8 +94,9 @@ __device__ __forceinline__ void ssd_epilogue(const MatchJob& jd, int cpi, int tx
   float* surf = jd.surfaces ? jd.surfaces + (size_t)cpi * K * K : nullptr;
   // EP offsets of a thread at a time: their table reads are in flight together
   // (one at a time, 9 rounds of a far table's latency at K = 65 and 512
-  // threads)
-  const int wave0 = __builtin_amdgcn_readfirstlane((int)threadIdx.x);  // a wave without offsets has none to read
+  // threads).  With EP = 1, the reduce's 16 waves, most may have no offsets and
+  // then read nothing.
+  const int wave0 = EP == 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x) : 0;
   for (int b = 0; b < K * K; b += EP * NT) {
     double E2[EP];
 #pragma unroll
