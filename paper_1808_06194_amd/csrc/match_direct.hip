@@ -73,7 +73,8 @@ struct DirectGeom {
   size_t t_bytes, lds;
 };
 
-static DirectGeom direct_geom(int N, int r) {
+// tbufs: at most that many template buffers.
+static DirectGeom direct_geom(int N, int r, int tbufs = 2) {
   DirectGeom g;
   g.N = N;
   g.r = r;
@@ -86,7 +87,7 @@ static DirectGeom direct_geom(int N, int r) {
   g.SLD = (g.NP + 16 * g.nblk + 2) / 2;
   g.t_bytes = (size_t)g.TROWS * g.TLD * 4;
   const size_t sb = (size_t)2 * D_NW * g.SLD * 4;
-  g.tbufs = 2 * g.t_bytes + sb <= kMaxLds ? 2 : 1;
+  g.tbufs = tbufs * g.t_bytes + sb <= kMaxLds ? tbufs : 1;
   // after the channels: Cs (K x K) and D_PW partial surfaces; the epilogue's
   // argmin scratch sits behind Cs once the partials are summed
   const size_t c = (size_t)g.K * g.K * 4 * (1 + D_PW) + 16 * D_NW;
@@ -101,15 +102,16 @@ __device__ __forceinline__ unsigned pack_bf16x2(float lo, float hi) {
 
 // A row's values 2 (lane + 64 i) and the next, i < NX, of the `bytes` at src
 // (wave-uniform); zero past them.  The row is a buffer of its own, whose range
-// check gives the zeros.  odd: a pair may straddle the end, so two loads.
-template <int NX>
+// check gives the zeros.  odd: the last pair straddles the end, so two loads each;
+// PAIRS: only the whole pairs.
+template <int NX, bool PAIRS>
 __device__ __forceinline__ void load_row(const float* src, int bytes, bool odd, int lane, float2 (&v)[NX]) {
-  const __amdgpu_buffer_rsrc_t rs =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(uniform_ptr(src)), 0, bytes, 0x00027000);
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(uniform_ptr(src)), 0,
+                                                                      PAIRS ? bytes & ~7 : bytes, 0x00027000);
 #pragma unroll
   for (int i = 0; i < NX; ++i) {
     const int o = 8 * lane + 512 * i;
-    if (odd) {
+    if (!PAIRS && odd) {
       v[i].x = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, o, 0, 0));
       v[i].y = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, o + 4, 0, 0));
     } else {
@@ -117,15 +119,29 @@ __device__ __forceinline__ void load_row(const float* src, int bytes, bool odd, 
     }
   }
 }
-// Those as packed bf16 pairs, the first n dwords, to dst.
+// An odd row's last value, in all lanes.
+__device__ __forceinline__ float load_last(const float* src, int bytes) {
+  const __amdgpu_buffer_rsrc_t rs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(uniform_ptr(src)), 0, bytes, 0x00027000);
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, 0, bytes ? bytes - 4 : 0, 0));
+}
 template <int NX>
-__device__ __forceinline__ void store_row(unsigned* dst, int n, int lane, const float2 (&v)[NX]) {
+__device__ __forceinline__ void put_last(int n, int lane, float last, float2 (&v)[NX]) {
 #pragma unroll
   for (int i = 0; i < NX; ++i)
-    if (lane + 64 * i < n) dst[lane + 64 * i] = pack_bf16x2(v[i].x, v[i].y);
+    if (lane + 64 * i == n / 2) v[i].x = last;
+}
+// Those as packed bf16 pairs, the first w dwords, to dst.
+template <int NX>
+__device__ __forceinline__ void store_row(unsigned* dst, int w, int lane, const float2 (&v)[NX]) {
+#pragma unroll
+  for (int i = 0; i < NX; ++i)
+    if (lane + 64 * i < w) dst[lane + 64 * i] = pack_bf16x2(v[i].x, v[i].y);
 }
 
-template <int NB, int NKC>
+// LAST (odd N only): rows as their whole pairs and the last value by itself, which
+// halves the loads for more registers and the selection.
+template <int NB, int NKC, bool LAST>
 __global__ __launch_bounds__(D_NT) void match_direct_kernel(MatchJob jd, DirectGeom g) {
   extern __shared__ unsigned char dsm[];
   constexpr int SX = (16 * NKC + 8 * NB + 1 + 63) / 64;  // dwords of a search row per lane
@@ -175,7 +191,7 @@ __global__ __launch_bounds__(D_NT) void match_direct_kernel(MatchJob jd, DirectG
 #pragma unroll
         for (int u = 0; u < D_RB; ++u) {
           const int n = n0 + u * D_NW;
-          load_row<TX>(tsrc + c * planeA + (size_t)min(n, N - 1) * jd.wA, n < N ? N * 4 : 0, odd, lane, v[u]);
+          load_row<TX, LAST>(tsrc + c * planeA + (size_t)min(n, N - 1) * jd.wA, n < N ? N * 4 : 0, odd, lane, v[u]);
         }
 #pragma unroll
         for (int u = 0; u < D_RB; ++u) {
@@ -183,16 +199,22 @@ __global__ __launch_bounds__(D_NT) void match_direct_kernel(MatchJob jd, DirectG
           if (n < N) store_row<TX>(Tc + (D_TPAD + n) * g.TLD, NP / 2, lane, v[u]);
         }
       }
+      const int n = wv + D_NW * lane;  // the rows' last values, a row per lane, over the zeros just stored
+      if (LAST && n < N)
+        Tc[(D_TPAD + n) * g.TLD + N / 2] = pack_bf16x2(ldg(tsrc + c * planeA + (size_t)n * jd.wA + N - 1), 0.f);
     };
     // This wave's search rows are s = wv, wv + NW, ... of every channel, one
     // after the other; it alone reads them, so it brings them in by itself: row
     // t + 2 of that sequence is on its way to registers and row t + 1 in LDS while
     // row t is used.
     float2 sv[SX];
+    float slast;
     int lc = 0, ls = wv;  // the next row to load
     auto next_row = [&] {
       const bool more = ls < Ws && lc < jd.m;
-      load_row<SX>(ssrc + (more ? lc * planeB + (size_t)ls * jd.wB : 0), more ? Ws * 4 : 0, odd, lane, sv);
+      const float* src = ssrc + (more ? lc * planeB + (size_t)ls * jd.wB : 0);
+      load_row<SX, LAST>(src, more ? Ws * 4 : 0, odd, lane, sv);
+      if (LAST) slast = load_last(src, more ? Ws * 4 : 0);
       ls += D_NW;
       if (ls >= Ws) {
         ls = wv;
@@ -202,6 +224,7 @@ __global__ __launch_bounds__(D_NT) void match_direct_kernel(MatchJob jd, DirectG
     unsigned* srow = Sw;  // the row in use; the other of the two is the next one's
     if (wv < Ws) {
       next_row();
+      if (LAST) put_last<SX>(Ws, lane, slast, sv);
       store_row<SX>(Sw, g.SLD, lane, sv);
       next_row();
     }
@@ -216,6 +239,7 @@ __global__ __launch_bounds__(D_NT) void match_direct_kernel(MatchJob jd, DirectG
       unsigned* const Tn = T0 + (Tl == T0 ? tstep : 0);
       const float* tnext = tsrc + (c + 1) * planeA;
       float2 tv[TX];
+      float tlast;
       const unsigned sh = (l16 & 1) * 2;  // e & 1 for every m
       // fragment j: 8 bf16 of a search row from column 16 j + 8 kg + lane % 16;
       // chunk kc takes j = 2 kc + m for block m, so two in a row share all but two
@@ -257,10 +281,17 @@ __global__ __launch_bounds__(D_NT) void match_direct_kernel(MatchJob jd, DirectG
         const int nlo = max(0, (s - N + 1) >> 4);
         const int sn = min(s + D_NW, Ws - 1);  // the next row (at the end any: not used)
         unsigned* const snext = Sw + (srow == Sw ? g.SLD : 0);
+        if (LAST) put_last<SX>(Ws, lane, slast, sv);
         store_row<SX>(snext, g.SLD, lane, sv);
-        if (ahead && s > wv && s - D_NW < N) store_row<TX>(Tn + (D_TPAD + s - D_NW) * g.TLD, NP / 2, lane, tv);
+        if (ahead && s > wv && s - D_NW < N) {
+          if (LAST) put_last<TX>(N, lane, tlast, tv);
+          store_row<TX>(Tn + (D_TPAD + s - D_NW) * g.TLD, NP / 2, lane, tv);
+        }
         next_row();
-        if (ahead && s < N) load_row<TX>(tnext + (size_t)s * jd.wA, N * 4, odd, lane, tv);
+        if (ahead && s < N) {
+          load_row<TX, LAST>(tnext + (size_t)s * jd.wA, N * 4, odd, lane, tv);
+          if (LAST) tlast = load_last(tnext + (size_t)s * jd.wA, N * 4);
+        }
         // the wave's lanes read each other's parts of the row
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -297,7 +328,10 @@ __global__ __launch_bounds__(D_NT) void match_direct_kernel(MatchJob jd, DirectG
       if (ahead) {
         // the last template row, where the loop ended before storing it
         const int sl = wv + (Ws - 1 - wv) / D_NW * D_NW;
-        if (wv < Ws && sl < N) store_row<TX>(Tn + (D_TPAD + sl) * g.TLD, NP / 2, lane, tv);
+        if (wv < Ws && sl < N) {
+          if (LAST) put_last<TX>(N, lane, tlast, tv);
+          store_row<TX>(Tn + (D_TPAD + sl) * g.TLD, NP / 2, lane, tv);
+        }
       } else if (c + 1 < jd.m) {
         __syncthreads();  // MFMA reads of this channel are done
         stage_template(c + 1, Tn);
@@ -348,7 +382,7 @@ using DirectKernel = void (*)(MatchJob, DirectGeom);
 template <int NB, int... KC>
 static constexpr DirectKernel direct_kernel(int nkc, std::integer_sequence<int, KC...>) {
   DirectKernel k = nullptr;
-  ((nkc == KC + 1 ? void(k = match_direct_kernel<NB, KC + 1>) : void()), ...);
+  ((nkc == KC + 1 ? void(k = match_direct_kernel<NB, KC + 1, false>) : void()), ...);
   return k;
 }
 // The kernel of nblk blocks of offsets and nkc chunks of template columns.
@@ -362,6 +396,26 @@ static DirectKernel direct_kernel(int nblk, int nkc) {
     default: return direct_kernel<5>(nkc, kcs);
   }
 }
+// How a launch of n points runs: two template buffers where they fit, but one
+// where two would leave each CU one workgroup although it has registers for two
+// and there are points for two (one or two blocks, 118 <= N <= 128 mostly).  There
+// odd rows count, and get kernels of their own.  1,000 points, r = 5, two
+// buffers against one: N = 118 369 and 344 us, N = 121 392 and 358 (one buffer and
+// loads of single values: 392).  A launch with a CU for each point keeps two
+// buffers: N = 118, 200 points 95 and 112 us.
+static DirectKernel direct_launch(int N, int r, int n, int num_cus, DirectGeom* g) {
+  *g = direct_geom(N, r);
+  const int nkc = g->NP / 32;
+  const bool registers = g->nblk == 1 || (g->nblk == 2 && nkc <= 4);
+  if (n > num_cus && registers && 2 * g->lds > kMaxLds) {
+    const DirectGeom one = direct_geom(N, r, 1);
+    if (2 * one.lds <= kMaxLds) {
+      *g = one;
+      if (N % 2 && nkc == 4) return g->nblk == 1 ? match_direct_kernel<1, 4, true> : match_direct_kernel<2, 4, true>;
+    }
+  }
+  return direct_kernel(g->nblk, nkc);
+}
 
 int init_direct_attributes() {
   for (int nb = 1; nb <= D_NB; ++nb)
@@ -369,6 +423,9 @@ int init_direct_attributes() {
       if (hipFuncSetAttribute((const void*)direct_kernel(nb, kc), hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)kMaxLds) != hipSuccess)
         return -2;
+  for (const DirectKernel k : {match_direct_kernel<1, 4, true>, match_direct_kernel<2, 4, true>})
+    if (hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds) != hipSuccess)
+      return -2;
   return 0;
 }
 
@@ -378,7 +435,8 @@ int launch_match_direct(const cfog_job* jobs, int n_jobs, int m, int obj, void*,
   for (int i = 0; i < n_jobs; ++i) {
     const cfog_job& j = jobs[i];
     if (j.n_cps == 0) continue;
-    const DirectGeom g = direct_geom(j.N, j.r);
+    DirectGeom g;
+    const DirectKernel kernel = direct_launch(j.N, j.r, j.n_cps, num_cus, &g);
     MatchJob d{};
     d.volA = j.volA; d.satA = j.satA; d.hA = j.hA; d.wA = j.wA;
     d.volB = j.volB; d.satB = j.satB; d.hB = j.hB; d.wB = j.wB;
@@ -390,7 +448,7 @@ int launch_match_direct(const cfog_job* jobs, int n_jobs, int m, int obj, void*,
     d.obj = obj;
     const int per_cu = std::max(1, (int)(kMaxLds / g.lds));
     const int blocks = std::min(j.n_cps, num_cus * per_cu);
-    hipLaunchKernelGGL(direct_kernel(g.nblk, g.NP / 32), dim3(blocks), dim3(D_NT), g.lds, st, d, g);
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(D_NT), g.lds, st, d, g);
     if (hipGetLastError() != hipSuccess) return -2;
   }
   return 0;

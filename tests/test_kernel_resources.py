@@ -61,3 +61,10 @@ def test_lane_workgroups_of_80_and_100(kernels):
         k = _lane(kernels, head, team)
         assert k["private_segment_fixed_size"] == 0 and k["vgpr_count"] <= (128 if "512" in team else 168)
     assert _lane(kernels, "100, 10, 10, 5, 20, 10, 10", "512, 1, 4, 1")["vgpr_count"] <= 128
+
+
+@pytest.mark.parametrize("team", ["1, 4, false", "1, 5, false", "1, 6, false", "2, 4, false", "1, 4, true", "2, 4, true"])
+def test_two_bf16_workgroups_share_a_cu(kernels, team):
+    """Where a launch takes one template buffer for two workgroups of eight waves to a CU: 128 VGPRs."""
+    k = kernels["match_direct_kernel<%s>" % team]
+    assert k["vgpr_count"] <= 128 and k["private_segment_fixed_size"] == 0
