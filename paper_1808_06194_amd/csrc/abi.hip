@@ -147,11 +147,11 @@ const cfog::FftPlan* select_plan(cfog_ctx* ctx, int N, int r, int m) {
   return cfog::choose_fft_plan(N, r);
 }
 
-// The plan a job runs with: its size's, but on images too wide for the lane
-// layout's offsets the one that has none.
+// The plan a job runs with: its size's, on images too wide for the lane layout's
+// 32-bit offsets in the form without them.
 const cfog::FftPlan* job_plan(cfog_ctx* ctx, const cfog_job& j, int m) {
   const cfog::FftPlan* p = select_plan(ctx, j.N, j.r, m);
-  return p && p->lane && std::max(j.wA, j.wB) > cfog::kLaneMaxWidth ? cfog::wide_plan() : p;
+  return p && std::max(j.wA, j.wB) > cfog::kLaneMaxWidth ? cfog::wide_plan(p) : p;
 }
 
 // ------------------------------------------------------------- batch plans
@@ -216,9 +216,9 @@ int build_batch(cfog_ctx* ctx, const cfog_job* jobs, int n_jobs, int m, int obj,
   B.jobs.resize(n_jobs);
   for (int i = 0; i < n_jobs; ++i) B.jobs[i] = to_device_job(jobs[i], m, obj);
   int nplans = 0;
-  const cfog::FftPlan* all = cfog::fft_plans(&nplans);
+  const cfog::FftPlan* all = cfog::fft_plans(&nplans, true);
   std::vector<size_t> split_bytes;
-  for (int p = 0; p <= nplans; ++p) {  // the last: wide_plan()
+  for (int p = 0; p < nplans; ++p) {
     Bucket b{&all[p], (int)B.tasks.size(), 0, 0, cfog::SplitArgs{0, 1, 0, nullptr}, 0};
     int Nmax = 0, Wmax = 0, Kmax = 0;
     for (int i = 0; i < n_jobs; ++i)
@@ -351,7 +351,6 @@ int autotune(cfog_ctx* ctx, const cfog_job& j, int m, hipStream_t st) {
   const cfog::FftPlan* all = cfog::fft_plans(&nplans);
   const cfog::FftPlan* first = cfog::choose_fft_plan(j.N, j.r);
   if (!first) return CFOG_EUNSUPPORTED;
-  if (std::max(j.wA, j.wB) > cfog::kLaneMaxWidth) return CFOG_OK;  // job_plan leaves no choice
   std::vector<const cfog::FftPlan*> cands;
   for (int p = 0; p < nplans && cands.size() < 3; ++p)
     if (all[p].P >= first->P && cfog::plan_fits(&all[p], j.N, j.r)) cands.push_back(&all[p]);
@@ -372,6 +371,7 @@ int autotune(cfog_ctx* ctx, const cfog_job& j, int m, hipStream_t st) {
   float best = 1e30f;
   int bestP = first->P;
   for (const cfog::FftPlan* p : cands) {
+    if (std::max(j.wA, j.wB) > cfog::kLaneMaxWidth) p = cfog::wide_plan(p);
     const int blocks = dj.n_cps;
     float ms = 0.f;
     bool ok = true;

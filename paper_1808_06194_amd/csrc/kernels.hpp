@@ -89,15 +89,16 @@ struct FftPlan {
   bool lane;
   int (*launch)(const MatchJob&, const MatchJob*, const int2*, int, int, const SplitArgs&, int, hipStream_t);
 };
-// The plans that are chosen by size, in increasing order of it.
-const FftPlan* fft_plans(int* count);
+// The plans that are chosen by size, in increasing order of it; with_wide: and
+// after them the lane layout's for wide images.
+const FftPlan* fft_plans(int* count, bool with_wide = false);
 // Smallest supported plan with P >= Ws whose LDS scratch also fits the
 // inverse row pass for K = 2r + 1; nullptr if none.
 const FftPlan* choose_fft_plan(int N, int r);
 // Whether plan p can match template side N with radius r.
 bool plan_fits(const FftPlan* p, int N, int r);
-// The plan for images wider than kLaneMaxWidth (any N, r that some plan takes).
-const FftPlan* wide_plan();
+// Plan p for images wider than kLaneMaxWidth.
+const FftPlan* wide_plan(const FftPlan* p);
 // Set the dynamic-LDS limits of every kernel of the library on the current
 // device (once per device, from context creation, before any stream capture;
 // safe to call from several host threads).  0 on success.

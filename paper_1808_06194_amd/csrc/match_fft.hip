@@ -19,16 +19,13 @@
 //           two half-spectra separated via Z(k) and conj Z(-k);
 //   y-pass: complex column FFTs of the half-spectrum kx in [0, P/2];
 //   ACC(ky, kx) += conj(T^_c) * S^_c  in registers, T^_c parked in registers
-//           between the T and S passes of the channel (the DC and Nyquist
-//           columns, both real, as one complex column job where that saves a
-//           round);
+//           between the T and S passes of the channel;
 // then one inverse: column IFFTs (kept rows u_y < K) and a C2R row IFFT with
 // two output rows packed per complex FFT (kept columns u_x < K), the SSD
 // assembly in FP64, and a lexicographic argmin + second-best over (SSD, index).
 //
-// Two kernels share this scheme: this file's (small windows, where one control
-// point's transforms fit a few waves, and images too wide for the other's
-// 32-bit offsets) and match_lane.hpp's (windows above 48).
+// Two kernels share this scheme: this file's (windows up to 48, where one control
+// point's transforms fit a few waves) and match_lane.hpp's (larger ones).
 //
 // Execution: every 1-D FFT of length P = R1 * R2 is owned by a group of
 // G = max(R1, R2) lanes of one wave:
@@ -78,14 +75,7 @@ struct FftCfg {
   static constexpr int GPW = 64 / G;           // groups per wave
   static constexpr int NW = NT / 64;
   static constexpr int NG = NW * GPW;          // groups per workgroup
-  // The DC and Nyquist columns of the x-pass half-spectra are real.  Where
-  // P/2 is a multiple of NG, the P/2 + 1 columns would take a whole round
-  // more than P/2 columns, so those two go through one complex column FFT as
-  // its real and imaginary parts (the packed job, column index 0): P/2 column
-  // jobs, a round and its accumulators fewer.
-  static constexpr bool PACK = (P / 2) % NG == 0;
-  static constexpr int NCOL = PACK ? P / 2 : PH;   // column jobs of a y-pass
-  static constexpr int KF = (NCOL + NG - 1) / NG;  // column rounds per group
+  static constexpr int KF = (PH + NG - 1) / NG;  // column rounds per group
   static constexpr size_t LDS = sizeof(float2) * ((size_t)P * PH + P) + NW * 16;
 };
 
@@ -103,8 +93,8 @@ struct Lane {
 
 // The inputs of a stage-2 DFT of lane k1: w[b] = get(b) W_P^{-k1 b} (INV:
 // W_P^{+k1 b}).  The twiddles come by recurrence from W_P^{k1}: one LDS read
-// instead of R2 - 1 (measured 3% faster at P = 144, 15% at P = 192), at most
-// R2 - 2 more FP32 roundings in each.
+// instead of R2 - 1 (3% faster at P = 144, 15% at P = 192, when those sides took
+// this layout), at most R2 - 2 more FP32 roundings in each.
 template <class C, bool INV, class Get>
 __device__ __forceinline__ void stage2_inputs(float2 (&w)[C::R2], const float2* tw, int k1, Get&& get) {
   float2 t1 = tw[C::R1 + k1];
@@ -121,13 +111,10 @@ __device__ __forceinline__ void stage2_inputs(float2 (&w)[C::R2], const float2* 
 // Where lane j of an x-pass group leaves stage-1 output k in its pair's row
 // buffer (2 PH = P + 2 slots), chosen so that neither the group's writes
 // (fixed k) nor its stage-2 reads (fixed j) share LDS banks: j R1 + k plus
-// j / 4 (unpadded, the stride R1 puts lanes j and j + 8 in one bank at
-// R1 = 12: 1% at P = 144, 12% at P = 192), and for R1 = 16 with R2 >= 10,
-// where that still pairs lanes, k R2 + j plus k / 8 (a further 5% at P = 192).
+// j / 4 (unpadded, the stride R1 puts lanes j and j + 32 / R1 in one bank).
 template <class C>
 __device__ __forceinline__ int s1_pos(int j, int k) {
-  static_assert((C::R2 - 1) / 4 <= 2 && (C::R1 - 1) / 8 <= 1, "the stage-1 outputs must fit the pair's two rows");
-  if constexpr (C::R1 == 16 && C::R2 >= 10) return k * C::R2 + j + (k >> 3);
+  static_assert((C::R2 - 1) / 4 <= 2, "the stage-1 outputs must fit the pair's two rows");
   return j * C::R1 + k + (j >> 2);
 }
 
@@ -135,8 +122,7 @@ __device__ __forceinline__ int s1_pos(int j, int k) {
 // the column, i.e. back in the rows it read (j + R2 a), so stage 1 is in place
 // per lane and consecutive lanes write consecutive rows; stage 2 then reads
 // rows k1 R2 + b.  (The natural order, row j R1 + k, puts a group's writes
-// R1 rows apart, which at R1 = 16 lands 12 lanes in two LDS banks; measured:
-// 2% faster at P = 144, 17% at P = 192.)
+// R1 rows apart, in few LDS banks.)
 template <class C>
 __device__ __forceinline__ int s1c(int j, int k) { return k * C::R2 + j; }
 
@@ -155,8 +141,7 @@ template <class C>
 __device__ __forceinline__ void xpass_fwd(const Lane<C>& L, const XRows& R, const float2* tw) {
   constexpr int R1 = C::R1, R2 = C::R2, PH = C::PH;
   const int total = (R.nrows + 1) >> 1;
-  // each pair is loaded just before its transform: fetching the next pair
-  // ahead lost by 1% at P = 192, whose registers spill
+  // each pair is loaded just before its transform: a group has one or two
   for (int q = L.g; q < total; q += C::NG) {
     float2* base = R.X + 2 * opaque(q) * PH;
     if (L.li < R2) {
@@ -205,14 +190,13 @@ __device__ __forceinline__ void xpass_stage2(const Lane<C>& L, float2* base, int
     // lane R1-k1 of the group (k1 > 0), or this lane's register (R2-k2) mod R2 (k1 = 0).
     const int lane = threadIdx.x & 63;
     const int msrc = lane - L.li + (k1 == 0 ? 0 : R1 - k1);
-    // the value of lane R1 - k1 of the group: where the group is a DPP row
-    // (R1 = 16) or half row (R1 = 8), a mirror within it and a shift by one
-    // lane (lane i then holds lane R1 - i's value; lane 0's is not used), on
-    // the vector units; otherwise an LDS permute
+    // the value of lane R1 - k1 of the group: where the group is a DPP half row
+    // (R1 = 8), a mirror within it and a shift by one lane (lane i then holds
+    // lane R1 - i's value; lane 0's is not used), on the vector units; otherwise
+    // an LDS permute
     auto from_mirror = [&](float x) -> float {
-      if constexpr (C::G == R1 && (R1 == 16 || R1 == 8)) {
-        constexpr int MIRROR = R1 == 16 ? 0x140 : 0x141;  // row_mirror, row_half_mirror
-        const int t = __builtin_amdgcn_update_dpp(0, __float_as_int(x), MIRROR, 0xf, 0xf, false);
+      if constexpr (C::G == R1 && R1 == 8) {
+        const int t = __builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x141, 0xf, 0xf, false);  // row_half_mirror
         return __int_as_float(__builtin_amdgcn_update_dpp(0, t, 0x111, 0xf, 0xf, false));  // row_shr:1
       } else {
         return __shfl(x, msrc, 64);
@@ -234,70 +218,23 @@ __device__ __forceinline__ void xpass_stage2(const Lane<C>& L, float2* base, int
   }
 }
 
-// Row `row` of a y-pass input column: col[row PH], or for the packed job
-// (col = X, the DC column) the DC value plus i times the Nyquist value.
-template <class C>
-__device__ __forceinline__ float2 col_in(const float2* col, int row, bool pk) {
-  const float2 v = col[row * C::PH];
-  return pk ? make_float2(v.x, col[row * C::PH + C::P / 2].x) : v;
-}
-
-// The packed job's share of the spectral product, for lane k1 holding
-// ky = k1 + R1 k2.  zs and zt are the column FFTs of (DC + i Nyquist) of the
-// window and the template; with F(-ky) = F((P - ky) mod P),
-//   T0 = (zt + conj zt(-ky)) / 2,  TN = (zt - conj zt(-ky)) / 2i  (S likewise),
-// both Hermitian in ky, and acc += conj(T0) S0 + i conj(TN) SN, whose inverse
-// column FFT is the DC column's correlation plus i times the Nyquist one's:
-//   conj(T0) S0 + i conj(TN) SN = (u s + i v t) / 4,
-//   u, v = conj zt +- zt(-ky),  s, t = zs +- conj zs(-ky).
-// The values at -ky come through LDS: column 0 takes zs, column P/2 zt.
-template <class C>
-__device__ __forceinline__ void packed_mac(float2* col, int k1, const float2 (&zs)[C::R2], const float2 (&zt)[C::R2],
-                                           float2 (&acc)[C::R2]) {
-  constexpr int P = C::P, R1 = C::R1, R2 = C::R2, PH = C::PH;
-  wave_sync();  // the stage-2 reads of the column are done
-#pragma unroll
-  for (int k2 = 0; k2 < R2; ++k2) {
-    const int ky = k1 + R1 * k2;
-    col[ky * PH] = zs[k2];
-    col[ky * PH + P / 2] = zt[k2];
-  }
-  wave_sync();
-#pragma unroll
-  for (int k2 = 0; k2 < R2; ++k2) {
-    const int ky = k1 + R1 * k2;
-    const int km = ky == 0 ? 0 : P - ky;
-    const float2 sm = col[km * PH], tm = col[km * PH + P / 2];
-    const float2 ta = zt[k2], sc = zs[k2];
-    const float2 u = make_float2(ta.x + tm.x, tm.y - ta.y);
-    const float2 v = make_float2(ta.x - tm.x, -ta.y - tm.y);
-    const float2 sp = make_float2(sc.x + sm.x, sc.y - sm.y);
-    const float2 sq = make_float2(sc.x - sm.x, sc.y + sm.y);
-    const float2 us = cmul(u, sp), vt = cmul(v, sq);
-    acc[k2].x = fmaf(0.25f, us.x - vt.y, acc[k2].x);
-    acc[k2].y = fmaf(0.25f, us.y + vt.x, acc[k2].y);
-  }
-}
-
 // y-pass: forward column FFTs of the half-spectrum (rows >= nrows were zeroed
 // by the x-pass).
 // Column kx = g + rnd * NG; lane k1 < R1 of its group ends up with
-// ky = k1 + R1 k2 and hands each value to sink(rnd, k2, kx, value), or for
-// the packed job all of them to psink(rnd, k1, values, column).
-template <class C, class Sink, class PSink>
-__device__ __forceinline__ void ypass_fwd(const Lane<C>& L, float2* X, const float2* tw, Sink&& sink, PSink&& psink) {
+// ky = k1 + R1 k2 and hands each value to sink(rnd, k2, value).
+template <class C, class Sink>
+__device__ __forceinline__ void ypass_fwd(const Lane<C>& L, float2* X, const float2* tw, Sink&& sink) {
   constexpr int R1 = C::R1, R2 = C::R2, PH = C::PH;
   static_for<0, C::KF>([&](auto rndI) {
     constexpr int rnd = decltype(rndI)::value;
     const int kx = L.g + rnd * C::NG;
-    if (kx < C::NCOL) {
-      const bool pk = C::PACK && rnd == 0 && kx == 0;
+    if (kx < PH) {
       float2* col = X + opaque(kx);
       if (L.li < R2) {
         const int j = L.li;
         float2 v[R1];
 #pragma unroll
-        for (int a = 0; a < R1; ++a) v[a] = col_in<C>(col, j + R2 * a, pk);
+        for (int a = 0; a < R1; ++a) v[a] = col[(j + R2 * a) * PH];
         dft<R1, -1>(v);
 #pragma unroll
         for (int k = 0; k < R1; ++k) col[s1c<C>(j, k) * PH] = v[k];
@@ -308,14 +245,7 @@ __device__ __forceinline__ void ypass_fwd(const Lane<C>& L, float2* X, const flo
         float2 w[R2];
         stage2_inputs<C, false>(w, tw, k1, [&](int b) { return col[s1c<C>(b, k1) * PH]; });
         dft<R2, -1>(w);
-        if (pk) {
-          psink(rndI, k1, w, col);
-        } else {
-          static_for<0, R2>([&](auto k2I) {
-            constexpr int k2 = decltype(k2I)::value;
-            sink(rndI, k2I, kx, w[k2]);
-          });
-        }
+        static_for<0, R2>([&](auto k2I) { sink(rndI, k2I, w[decltype(k2I)::value]); });
       }
     }
   });
@@ -354,22 +284,13 @@ __device__ __forceinline__ void match_one(const Lane<C>& L, const MatchJob& jd, 
     __syncthreads();  // previous readers of X are done
     xpass_fwd<C>(L, XRows{tA + c * planeA, jd.wA, N, N, X}, tw);
     __syncthreads();
-    auto park = [&](auto rndI, auto k2I, int, float2 v) {
-      constexpr int rnd = decltype(rndI)::value, k2 = decltype(k2I)::value;
-      th[rnd][k2] = v;
-    };
-    ypass_fwd<C>(L, X, tw, park, [&](auto rndI, int, const float2 (&w)[R2], float2*) {
-      static_for<0, R2>([&](auto k2I) { park(rndI, k2I, 0, w[decltype(k2I)::value]); });
-    });
+    ypass_fwd<C>(L, X, tw, [&](auto rndI, auto k2I, float2 v) { th[decltype(rndI)::value][decltype(k2I)::value] = v; });
     __syncthreads();
     xpass_fwd<C>(L, XRows{sB + c * planeB, jd.wB, Ws, Ws, X}, tw);
     __syncthreads();
-    ypass_fwd<C>(L, X, tw, [&](auto rndI, auto k2I, int, float2 v) {
+    ypass_fwd<C>(L, X, tw, [&](auto rndI, auto k2I, float2 v) {
       constexpr int rnd = decltype(rndI)::value, k2 = decltype(k2I)::value;
       acc[rnd][k2] = cmac_conj(acc[rnd][k2], th[rnd][k2], v);
-    }, [&](auto rndI, int k1, const float2 (&w)[R2], float2* col) {
-      constexpr int rnd = decltype(rndI)::value;
-      packed_mac<C>(col, k1, w, th[rnd], acc[rnd]);
     });
   }
 
@@ -378,9 +299,7 @@ __device__ __forceinline__ void match_one(const Lane<C>& L, const MatchJob& jd, 
 #pragma unroll
   for (int rnd = 0; rnd < KF; ++rnd) {
     const int kx = L.g + rnd * C::NG;
-    if (kx < C::NCOL) {
-      // the packed job's outputs: real part the DC column, imaginary the Nyquist
-      const bool pk = C::PACK && rnd == 0 && kx == 0;
+    if (kx < PH) {
       float2* col = X + opaque(kx);
       if (L.li < R1) {
 #pragma unroll
@@ -405,14 +324,7 @@ __device__ __forceinline__ void match_one(const Lane<C>& L, const MatchJob& jd, 
 #pragma unroll
         for (int k2 = 0; k2 < R2; ++k2) {
           const int uy = k1 + R1 * k2;
-          if (uy < K) {
-            if (pk) {
-              col[uy * PH] = make_float2(w[k2].x, 0.f);
-              col[uy * PH + P / 2] = make_float2(w[k2].y, 0.f);
-            } else {
-              col[uy * PH] = w[k2];
-            }
-          }
+          if (uy < K) col[uy * PH] = w[k2];
         }
       }
     }
@@ -563,8 +475,7 @@ __global__ __launch_bounds__(C::NT) void match_fft_kernel(MatchJob job0, const M
   L((120, 8, 15, 15, 8, 12, 10), (512, 1, 4, 0), (768, 1, 3, 0))     \
   L((144, 12, 12, 12, 12, 12, 12), (1024, 1, 4, 0), (1024, 1, 4, 0)) \
   L((160, 10, 16, 20, 8, 16, 10), (896, 0, 4, 0), (896, 0, 4, 0))    \
-  L((192, 24, 8, 24, 8, 16, 12), (512, 0, 2, 1), (512, 0, 2, 1))     \
-  G(192, 16, 12, 512)
+  L((192, 24, 8, 24, 8, 16, 12), (512, 0, 2, 1), (512, 0, 2, 1))
 
 #define CFOG_ARGS(...) __VA_ARGS__
 #define CFOG_LANE_CFG(PLAN, TEAM) LaneCfg<CFOG_ARGS PLAN, CFOG_ARGS TEAM>
@@ -593,16 +504,16 @@ constexpr int resident() {
 // four to a CU, a whole round and a split rest are still shorter with W while that
 // rest is small: P = 64 at 520, 600 and 700 points 77 / 59, 80 / 69 and 97 / 83,
 // but at 768 points 83 / 87; P = 72 at 768 points 85 / 95.
-template <class C, class W>
+template <class C, class W, bool WIDE>
 static int launch_lane(const MatchJob& job0, const MatchJob* jobs, const int2* tasks, int n_tasks, int n_blocks,
                        const SplitArgs& sp, int num_cus, hipStream_t st) {
   const int slots = resident<W>() * num_cus;
   const bool round_and_rest = resident<W>() > 1 && 2 * C::NT >= W::NT && sp.n_whole == slots &&
                               5 * (n_tasks - slots) <= 2 * slots;
   if (n_blocks <= slots || round_and_rest)
-    hipLaunchKernelGGL(match_lane_kernel<W>, dim3(n_blocks), dim3(W::NT), W::LDS, st, job0, jobs, tasks, n_tasks, sp);
+    hipLaunchKernelGGL((match_lane_kernel<W, WIDE>), dim3(n_blocks), dim3(W::NT), W::LDS, st, job0, jobs, tasks, n_tasks, sp);
   else
-    hipLaunchKernelGGL(match_lane_kernel<C>, dim3(n_blocks), dim3(C::NT), C::LDS, st, job0, jobs, tasks, n_tasks, sp);
+    hipLaunchKernelGGL((match_lane_kernel<C, WIDE>), dim3(n_blocks), dim3(C::NT), C::LDS, st, job0, jobs, tasks, n_tasks, sp);
   return hipGetLastError() == hipSuccess ? 0 : -2;
 }
 
@@ -610,26 +521,33 @@ template <class C>
 static constexpr FftPlan group_plan() {
   return FftPlan{C::P, C::R1, C::R2, C::NT, C::LDS, C::P, false, launch_group<C>};
 }
-template <class C, class W>
+// WIDE: for images wider than kLaneMaxWidth.
+template <class C, class W, bool WIDE>
 static constexpr FftPlan lane_plan() {
-  return FftPlan{C::P, C::R1, C::R2, C::NT, C::LDS, C::P == 144 ? 134 : C::P, true, launch_lane<C, W>};
+  return FftPlan{C::P, C::R1, C::R2, C::NT, C::LDS, C::P == 144 ? 134 : C::P, true, launch_lane<C, W, WIDE>};
 }
 
+#define CFOG_NO_PLAN(...)
 static const FftPlan kPlans[] = {
 #define CFOG_PLAN_ENTRY(...) group_plan<FftCfg<__VA_ARGS__>>(),
-#define CFOG_LANE_ENTRY(PLAN, FULL, SPREAD) lane_plan<CFOG_LANE_CFG(PLAN, FULL), CFOG_LANE_CFG(PLAN, SPREAD)>(),
+#define CFOG_LANE_ENTRY(PLAN, FULL, SPREAD) lane_plan<CFOG_LANE_CFG(PLAN, FULL), CFOG_LANE_CFG(PLAN, SPREAD), false>(),
+#define CFOG_WIDE_ENTRY(PLAN, FULL, SPREAD) lane_plan<CFOG_LANE_CFG(PLAN, FULL), CFOG_LANE_CFG(PLAN, SPREAD), true>(),
     CFOG_PLANS(CFOG_PLAN_ENTRY, CFOG_LANE_ENTRY)
+    CFOG_PLANS(CFOG_NO_PLAN, CFOG_WIDE_ENTRY)
 #undef CFOG_PLAN_ENTRY
 #undef CFOG_LANE_ENTRY
+#undef CFOG_WIDE_ENTRY
 };
-constexpr int kNumPlans = sizeof(kPlans) / sizeof(kPlans[0]) - 1;  // those that are chosen by size
+#define CFOG_COUNT(...) + 1
+constexpr int kNumPlans = CFOG_PLANS(CFOG_COUNT, CFOG_COUNT);  // those that are chosen by size, which come first
+constexpr int kNumLane = CFOG_PLANS(CFOG_NO_PLAN, CFOG_COUNT);
+#undef CFOG_COUNT
+static_assert(sizeof(kPlans) / sizeof(kPlans[0]) == kNumPlans + kNumLane, "plans");
 
-// The last entry: the largest group layout, for images wider than the lane
-// layout's 32-bit offsets reach.
-const FftPlan* wide_plan() { return &kPlans[kNumPlans]; }
+const FftPlan* wide_plan(const FftPlan* p) { return p->lane ? p + kNumLane : p; }
 
-const FftPlan* fft_plans(int* count) {
-  *count = kNumPlans;
+const FftPlan* fft_plans(int* count, bool with_wide) {
+  *count = with_wide ? kNumPlans + kNumLane : kNumPlans;
   return kPlans;
 }
 
@@ -738,15 +656,20 @@ int init_match_fft_attributes() {
   };
 #define CFOG_PLAN_ATTR(...) \
   if (!set(match_fft_kernel<FftCfg<__VA_ARGS__>>, FftCfg<__VA_ARGS__>::NT, FftCfg<__VA_ARGS__>::LDS)) return -2;
-#define CFOG_LANE_ATTR(PLAN, FULL, SPREAD)                                                     \
-  {                                                                                            \
-    using C = CFOG_LANE_CFG(PLAN, FULL);                                                       \
-    using W = CFOG_LANE_CFG(PLAN, SPREAD);                                                     \
-    if (!set(match_lane_kernel<C>, C::NT, C::LDS) || !allow(match_lane_kernel<W>, W::LDS)) return -2; \
+#define CFOG_LANE_ATTR_OF(PLAN, FULL, SPREAD, WIDE)                                                              \
+  {                                                                                                              \
+    using C = CFOG_LANE_CFG(PLAN, FULL);                                                                         \
+    using W = CFOG_LANE_CFG(PLAN, SPREAD);                                                                       \
+    if (!set(match_lane_kernel<C, WIDE>, C::NT, C::LDS) || !allow(match_lane_kernel<W, WIDE>, W::LDS)) return -2; \
   }
+#define CFOG_LANE_ATTR(PLAN, FULL, SPREAD) CFOG_LANE_ATTR_OF(PLAN, FULL, SPREAD, false)
+#define CFOG_WIDE_ATTR(PLAN, FULL, SPREAD) CFOG_LANE_ATTR_OF(PLAN, FULL, SPREAD, true)
   CFOG_PLANS(CFOG_PLAN_ATTR, CFOG_LANE_ATTR)
+  CFOG_PLANS(CFOG_NO_PLAN, CFOG_WIDE_ATTR)
 #undef CFOG_PLAN_ATTR
+#undef CFOG_LANE_ATTR_OF
 #undef CFOG_LANE_ATTR
+#undef CFOG_WIDE_ATTR
   return 0;
 }
 

@@ -147,12 +147,22 @@ __device__ __forceinline__ int2 lane_item(int n, int i) {
 }
 
 // Rows j + RB a (a < RA) of column x of the set; zero past the set.
-// Buffer loads: the per-row offset is a scalar, and the descriptor's range
+// Where a window's byte offsets fit 31 bits, buffer loads: the per-row offset is a scalar, and the descriptor's range
 // check (offset of the lane >= size - scalar offset) makes rows past the set
 // read as zero.  The scalar offset is held to the size, past which that
-// difference would wrap.
-template <class C>
+// difference would wrap.  WIDE images: 64-bit addresses, and the rows tested.
+template <class C, bool WIDE>
 __device__ __forceinline__ void lane_load(const LaneSet& S, int j, int x, float (&v)[C::RA]) {
+  if constexpr (WIDE) {
+    const float* p = S.src + (int64_t)j * S.ld + x;
+#pragma unroll
+    for (int a = 0; a < C::RA; ++a) {
+      v[a] = 0.f;
+      if (j + C::RB * a < S.n) v[a] = ldg(p);
+      p += (int64_t)C::RB * S.ld;
+    }
+    return;
+  }
   const int size = ((S.n - 1) * S.ld + S.n) * 4, ld4 = S.ld * 4;
   const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(S.src), 0, size, 0x00027000);
   const int vo = j * ld4 + x * 4;
@@ -185,7 +195,7 @@ __device__ __forceinline__ void lane_y1(int j, int x, const float (&u)[C::RA], f
 
 // Phases y1 and y2 of one set.  u: this thread's first PF items, loaded.
 // Ends before the closing barrier.
-template <class C>
+template <class C, bool WIDE>
 __device__ __forceinline__ void lane_ypass(const LaneSet& S, float (&u)[C::PF ? C::PF : 1][C::RA], float2* X,
                                            const float2* twy, const unsigned short* pos) {
   constexpr int RB = C::RB, LD = C::LD, NT = C::NT, P = C::P;
@@ -201,7 +211,7 @@ __device__ __forceinline__ void lane_ypass(const LaneSet& S, float (&u)[C::PF ? 
   for (int i = threadIdx.x + C::PF * NT; i < total; i += NT) {
     float w[C::RA];
     const int2 it = lane_item(n, i);
-    lane_load<C>(S, it.x, it.y, w);
+    lane_load<C, WIDE>(S, it.x, it.y, w);
     lane_y1<C>(it.x, it.y, w, X, twy, pos);
   }
   __syncthreads();
@@ -444,7 +454,7 @@ __device__ __forceinline__ const float* lane_inverse(float2* X, float2 (&acc)[C:
 
 // Control point cpi of job jd over the channels [c0, c1): as match_one in
 // match_fft.hip.
-template <class C>
+template <class C, bool WIDE>
 __device__ __forceinline__ void lane_match_one(const MatchJob& jd, int cpi, float2* X, const float2* twy,
                                                const float2* twx, const float2* twi, const unsigned short* pos,
                                                ArgminState* red, int c0, int c1, float* __restrict__ part, int g) {
@@ -475,13 +485,13 @@ __device__ __forceinline__ void lane_match_one(const MatchJob& jd, int cpi, floa
       for (int s = 0; s < C::PF; ++s)
         if (s == 0 || s * NT < set.n * C::RB) {
           const int2 it = lane_item(set.n, threadIdx.x + s * NT);
-          lane_load<C>(set, it.x, it.y, u[s]);
+          lane_load<C, WIDE>(set, it.x, it.y, u[s]);
         }
     };
     preload(T);
 #pragma unroll 1
     for (int c = __builtin_amdgcn_readfirstlane(c1 - c0); c > 0; --c) {
-      lane_ypass<C>(T, u, X, twy, pos);
+      lane_ypass<C, WIDE>(T, u, X, twy, pos);
       __syncthreads();
       lane_x1<C>(X, twx);
       __syncthreads();
@@ -492,7 +502,7 @@ __device__ __forceinline__ void lane_match_one(const MatchJob& jd, int cpi, floa
         for (int k = 0; k < R2; ++k) th[s][k] = v[k];
       });
       __syncthreads();
-      lane_ypass<C>(S, u, X, twy, pos);
+      lane_ypass<C, WIDE>(S, u, X, twy, pos);
       __syncthreads();
       lane_x1<C>(X, twx);
       __syncthreads();
@@ -516,7 +526,7 @@ __device__ __forceinline__ void lane_match_one(const MatchJob& jd, int cpi, floa
 }
 
 // The kernel: arguments and work items as match_fft_kernel.
-template <class C>
+template <class C, bool WIDE>
 __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::WPE))) void match_lane_kernel(MatchJob job0, const MatchJob* __restrict__ jobs,
                                                            const int2* __restrict__ tasks, int n_tasks, SplitArgs sp) {
   extern __shared__ float2 smem[];
@@ -546,7 +556,7 @@ __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::WPE)))
       cpi = tk.y;
     }
     float* part = G > 1 ? sp.part + (size_t)(it - sp.n_whole) * sp.slot : nullptr;
-    lane_match_one<C>(jd, cpi, X, tw, twx, twi, pos, red, g * jd.m / G, (g + 1) * jd.m / G, part, g);
+    lane_match_one<C, WIDE>(jd, cpi, X, tw, twx, twi, pos, red, g * jd.m / G, (g + 1) * jd.m / G, part, g);
   }
 }
 

@@ -51,7 +51,7 @@ def test_two_reduce_workgroups_share_a_cu(kernels):
 
 
 def _lane(kernels, head, team):
-    return kernels["match_lane_kernel<LaneCfg<%s, %s> >" % (head, team)]
+    return kernels["match_lane_kernel<LaneCfg<%s, %s>, false>" % (head, team)]
 
 
 def test_lane_workgroups_of_80_and_100(kernels):
