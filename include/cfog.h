@@ -236,7 +236,9 @@ size_t match_batch_workspace_size(cfog_ctx* ctx, const cfog_job* jobs, int32_t n
  *   flags       one CFOG_PATH_* value, optionally | CFOG_OBJ_CORR (Eq. 7
  *               objective), | CFOG_NO_SPLIT and | CFOG_AUTOTUNE (FFT paths:
  *               the first call for a given (N, r, m) times up to three FFT sizes
- *               on the job's own points and keeps the fastest; with the
+ *               on the job's own points, as many of them and in the kind of
+ *               workgroups that this call's launch has, and keeps the fastest
+ *               for all calls; this synchronises and allocates; with the
  *               environment variable CFOG_PLAN_CACHE naming a file, choices
  *               persist across processes) and | CFOG_USE_GRAPH (batched path:
  *               the task-table upload and the bucket launches are captured into a

@@ -164,12 +164,18 @@ cfog::SplitArgs plan_split(cfog_ctx* ctx, const cfog::FftPlan* p, int n, int m, 
   return cfog::SplitArgs{c.n_whole, c.G, c.slot, nullptr};
 }
 
+// Whether a launch of n tasks takes spread workgroups.
+bool spread_launch(cfog_ctx* ctx, const cfog::FftPlan* p, int n, int n_blocks, const cfog::SplitArgs& sp) {
+  return p->lane && cfog::takes_spread(n, sp.n_whole, n_blocks, ctx->num_cus, p->spread_per_cu, p->spread_rest);
+}
+
 // Workspace layout of a plain-path launch of job j: the split partials (when
 // split_ok), one workgroup per work item (lane layout: at most those resident).
 struct PlainLayout {
   const cfog::FftPlan* p = nullptr;
   cfog::SplitArgs sp{0, 1, 0, nullptr};
   int blocks = 0;
+  bool spread = false;
   size_t split_off = 0, total = 0;
 };
 
@@ -183,6 +189,7 @@ PlainLayout plain_layout(cfog_ctx* ctx, const cfog_job& j, int m, bool split_ok)
                   : cfog::SplitArgs{j.n_cps, 1, 0, nullptr};
   const int items = cfog::split_items(j.n_cps, L.sp);
   L.blocks = L.p->lane ? std::min(items, S) : items;
+  L.spread = spread_launch(ctx, L.p, j.n_cps, L.blocks, L.sp);
   L.split_off = 0;
   L.total = sb;
   return L;
@@ -192,6 +199,7 @@ struct Bucket {
   const cfog::FftPlan* plan;
   int begin, count, blocks;
   cfog::SplitArgs sp;
+  bool spread;
   size_t split_off;  // its split partials (sp.G > 1)
 };
 
@@ -219,7 +227,7 @@ int build_batch(cfog_ctx* ctx, const cfog_job* jobs, int n_jobs, int m, int obj,
   const cfog::FftPlan* all = cfog::fft_plans(&nplans, true);
   std::vector<size_t> split_bytes;
   for (int p = 0; p < nplans; ++p) {
-    Bucket b{&all[p], (int)B.tasks.size(), 0, 0, cfog::SplitArgs{0, 1, 0, nullptr}, 0};
+    Bucket b{&all[p], (int)B.tasks.size(), 0, 0, cfog::SplitArgs{0, 1, 0, nullptr}, false, 0};
     int Nmax = 0, Wmax = 0, Kmax = 0;
     for (int i = 0; i < n_jobs; ++i)
       if (plans[i] == &all[p] && jobs[i].n_cps > 0) {
@@ -240,6 +248,7 @@ int build_batch(cfog_ctx* ctx, const cfog_job* jobs, int n_jobs, int m, int obj,
     split_budget -= sb;
     split_bytes.push_back(sb);
     b.blocks = std::min(cfog::split_items(b.count, b.sp), S);
+    b.spread = spread_launch(ctx, b.plan, b.count, b.blocks, b.sp);
     B.buckets.push_back(b);
   }
   B.jobs_off = 0;
@@ -271,7 +280,7 @@ int enqueue_batch(cfog_ctx* ctx, const BatchPlan& B, char* ws, const void* host,
     cfog::SplitArgs sp = b.sp;
     sp.part = sp.G > 1 ? (float*)(ws + b.split_off) : nullptr;
     return cfog::launch_match_fft(b.plan, cfog::MatchJob{}, d_jobs, d_tasks + b.begin, b.count, b.blocks, sp,
-                                  ctx->num_cus, s) == 0 &&
+                                  b.spread, s) == 0 &&
            cfog::launch_split_reduce(cfog::MatchJob{}, d_jobs, d_tasks + b.begin, b.count, sp, s) == 0;
   };
   if (B.buckets.size() == 1) {
@@ -340,60 +349,81 @@ void save_plan_cache(cfog_ctx* ctx) {
   rename(tmp.c_str(), ctx->plan_cache_path.c_str());
 }
 
-// Time the candidate FFT sizes for (N, r) on up to 2 x #CU control points of
-// job j and keep the fastest.  The trial launches write into the job's own
-// result buffer; the real launch that follows on the same stream overwrites
-// them.
-int autotune(cfog_ctx* ctx, const cfog_job& j, int m, hipStream_t st) {
+// Time the candidate FFT sizes for (N, r) as part of a launch of n points and
+// keep the fastest.  Each candidate runs in the workgroups, full or spread, and at
+// most as many of them as it would in that launch: on n points, or where these
+// make more than two rounds of every candidate, on two rounds of its own.  The
+// points are job j's, over and over, in a copy.
+int autotune(cfog_ctx* ctx, const cfog_job& j, int n, int m, hipStream_t st) {
   const long key = nrm_key(j.N, j.r, m);
   if (ctx->pinned.count(nr_key(j.N, j.r)) || ctx->tuned.count(key) || j.n_cps == 0) return CFOG_OK;
   int nplans = 0;
   const cfog::FftPlan* all = cfog::fft_plans(&nplans);
   const cfog::FftPlan* first = cfog::choose_fft_plan(j.N, j.r);
   if (!first) return CFOG_EUNSUPPORTED;
+  const bool wide = std::max(j.wA, j.wB) > cfog::kLaneMaxWidth;
   std::vector<const cfog::FftPlan*> cands;
+  int rounds2 = 0;  // two rounds of the candidate of the most workgroups
   for (int p = 0; p < nplans && cands.size() < 3; ++p)
-    if (all[p].P >= first->P && cfog::plan_fits(&all[p], j.N, j.r)) cands.push_back(&all[p]);
+    if (all[p].P >= first->P && cfog::plan_fits(&all[p], j.N, j.r)) {
+      cands.push_back(wide ? cfog::wide_plan(&all[p]) : &all[p]);
+      rounds2 = std::max(rounds2, 2 * cfog::plan_slots(cands.back(), ctx->num_cus));
+    }
   if (cands.size() <= 1) {
     ctx->tuned[key] = first->P;
     return CFOG_OK;
   }
-  hipEvent_t e0, e1;
-  if (hipEventCreate(&e0) != hipSuccess) return record(ctx, hipGetLastError());
-  if (hipEventCreate(&e1) != hipSuccess) {
-    (void)hipEventDestroy(e0);
+  struct Trial {
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    char* points = nullptr;  // control points, then results
+    ~Trial() {
+      if (points) (void)hipFree(points);
+      if (e0) (void)hipEventDestroy(e0);
+      if (e1) (void)hipEventDestroy(e1);
+    }
+  } t;
+  const int cap = std::min(n, rounds2);
+  const size_t cps_bytes = align_up(sizeof(int4) * (size_t)cap, 256);
+  if (hipEventCreate(&t.e0) != hipSuccess || hipEventCreate(&t.e1) != hipSuccess)
     return record(ctx, hipGetLastError());
+  if (hipMalloc((void**)&t.points, cps_bytes + sizeof(cfog::Result) * (size_t)cap) != hipSuccess) {
+    t.points = nullptr;
+    return CFOG_ENOMEM;
   }
   cfog::MatchJob dj = to_device_job(j, m, 0);
-  dj.n_cps = std::min(j.n_cps, 2 * ctx->num_cus);
+  int4* cps = reinterpret_cast<int4*>(t.points);
+  for (int have = 0, from = std::min(j.n_cps, cap); have < cap;) {
+    const int k = std::min(have ? have : from, cap - have);
+    if (hipMemcpyAsync(cps + have, have ? cps : dj.cps, sizeof(int4) * (size_t)k, hipMemcpyDeviceToDevice, st) != hipSuccess)
+      return record(ctx, hipGetLastError());
+    have += k;
+  }
+  dj.cps = cps;
+  dj.out = reinterpret_cast<cfog::Result*>(t.points + cps_bytes);
   dj.surfaces = nullptr;
   dj.subpix = nullptr;
   float best = 1e30f;
   int bestP = first->P;
   for (const cfog::FftPlan* p : cands) {
-    if (std::max(j.wA, j.wB) > cfog::kLaneMaxWidth) p = cfog::wide_plan(p);
-    const int blocks = dj.n_cps;
+    const int S = cfog::plan_slots(p, ctx->num_cus);
+    size_t sb = 0;
+    const cfog::SplitArgs sp = plan_split(ctx, p, n, m, j.N, j.N + 2 * j.r, 2 * j.r + 1, &sb);
+    const bool spread = spread_launch(ctx, p, n, std::min(cfog::split_items(n, sp), S), sp);
+    dj.n_cps = n > rounds2 ? 2 * S : n;
+    const int blocks = p->lane ? std::min(dj.n_cps, S) : dj.n_cps;
     float ms = 0.f;
-    bool ok = true;
-    for (int rep = 0; rep < 2 && ok; ++rep) {  // the first launch warms up
-      ok = hipEventRecord(e0, st) == hipSuccess &&
-           cfog::launch_match_fft(p, dj, nullptr, nullptr, dj.n_cps, blocks, cfog::SplitArgs{dj.n_cps, 1, 0, nullptr},
-                                  ctx->num_cus, st) == 0 &&
-           hipEventRecord(e1, st) == hipSuccess && hipEventSynchronize(e1) == hipSuccess &&
-           hipEventElapsedTime(&ms, e0, e1) == hipSuccess;
-    }
-    if (!ok) {
-      (void)hipEventDestroy(e0);
-      (void)hipEventDestroy(e1);
-      return record(ctx, hipGetLastError());
-    }
-    if (ms < best) {
-      best = ms;
+    for (int rep = 0; rep < 2; ++rep)  // the first launch warms up
+      if (hipEventRecord(t.e0, st) != hipSuccess ||
+          cfog::launch_match_fft(p, dj, nullptr, nullptr, dj.n_cps, blocks, cfog::SplitArgs{dj.n_cps, 1, 0, nullptr},
+                                 spread, st) != 0 ||
+          hipEventRecord(t.e1, st) != hipSuccess || hipEventSynchronize(t.e1) != hipSuccess ||
+          hipEventElapsedTime(&ms, t.e0, t.e1) != hipSuccess)
+        return record(ctx, hipGetLastError());
+    if (ms / dj.n_cps < best) {
+      best = ms / dj.n_cps;
       bestP = p->P;
     }
   }
-  (void)hipEventDestroy(e0);
-  (void)hipEventDestroy(e1);
   ctx->tuned[key] = bestP;
   save_plan_cache(ctx);
   return CFOG_OK;
@@ -687,7 +717,14 @@ static int match_batch_run(cfog_ctx* ctx, const cfog_job* jobs, int32_t n_jobs, 
     for (int i = 0; i < n_jobs; ++i) {
       if (seen.count(nr_key(jobs[i].N, jobs[i].r)) || jobs[i].n_cps == 0) continue;
       seen[nr_key(jobs[i].N, jobs[i].r)] = 1;
-      int rc = autotune(ctx, jobs[i], m, st);
+      int n = jobs[i].n_cps;  // points of the launch that the job will be part of
+      if (path == CFOG_PATH_BATCHED_FFT) {
+        const cfog::FftPlan* p = job_plan(ctx, jobs[i], m);
+        n = 0;
+        for (int k = 0; k < n_jobs; ++k)
+          if (job_plan(ctx, jobs[k], m) == p) n += jobs[k].n_cps;
+      }
+      int rc = autotune(ctx, jobs[i], n, m, st);
       if (rc != CFOG_OK) return rc;
     }
   }
@@ -702,7 +739,7 @@ static int match_batch_run(cfog_ctx* ctx, const cfog_job* jobs, int32_t n_jobs, 
       cfog::SplitArgs sp = L.sp;
       sp.part = sp.G > 1 ? (float*)(ws + L.split_off) : nullptr;
       const cfog::MatchJob dj = to_device_job(jobs[i], m, obj);
-      if (cfog::launch_match_fft(L.p, dj, nullptr, nullptr, jobs[i].n_cps, L.blocks, sp, ctx->num_cus, st) != 0 ||
+      if (cfog::launch_match_fft(L.p, dj, nullptr, nullptr, jobs[i].n_cps, L.blocks, sp, L.spread, st) != 0 ||
           cfog::launch_split_reduce(dj, nullptr, nullptr, jobs[i].n_cps, sp, st) != 0)
         return record(ctx, hipGetLastError());
     }

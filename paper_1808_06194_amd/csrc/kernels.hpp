@@ -81,13 +81,16 @@ struct SplitArgs {
 
 // FFT matcher plans: FFT side P = R1 * R2, NT threads per workgroup, lds
 // bytes of dynamic LDS, templates of up to t_rows rows.  lane: the lane layout
-// of match_lane.hpp, else the group layout of match_fft.hip.
+// of match_lane.hpp, else the group layout of match_fft.hip.  spread_per_cu and
+// spread_rest: of its spread workgroups (takes_spread in split_plan.hpp).
 struct FftPlan {
   int P, R1, R2, NT;
   size_t lds;
   int t_rows;
   bool lane;
-  int (*launch)(const MatchJob&, const MatchJob*, const int2*, int, int, const SplitArgs&, int, hipStream_t);
+  int spread_per_cu;
+  bool spread_rest;
+  int (*launch)(const MatchJob&, const MatchJob*, const int2*, int, int, const SplitArgs&, bool, hipStream_t);
 };
 // The plans that are chosen by size, in increasing order of it; with_wide: and
 // after them the lane layout's for wide images.
@@ -111,9 +114,10 @@ int plan_slots(const FftPlan* p, int num_cus);
 int plan_split_slots(const FftPlan* p, int num_cus);
 // Launch the FFT matcher.  d_jobs == nullptr: n_tasks control points of job0
 // (plain path).  Otherwise n_tasks (job, cp) pairs from d_tasks over d_jobs.
-// n_blocks: workgroups (a grid-stride loop covers the remaining items).
+// n_blocks: workgroups (a grid-stride loop covers the remaining items); spread:
+// the lane layout's spread workgroups.
 int launch_match_fft(const FftPlan* plan, const MatchJob& job0, const MatchJob* d_jobs, const int2* d_tasks,
-                     int n_tasks, int n_blocks, const SplitArgs& sp, int num_cus, hipStream_t st);
+                     int n_tasks, int n_blocks, const SplitArgs& sp, bool spread, hipStream_t st);
 // Finishes the split tasks [sp.n_whole, n_tasks) (no-op for G = 1).
 int launch_split_reduce(const MatchJob& job0, const MatchJob* d_jobs, const int2* d_tasks, int n_tasks,
                         const SplitArgs& sp, hipStream_t st);

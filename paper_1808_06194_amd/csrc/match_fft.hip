@@ -482,7 +482,7 @@ __global__ __launch_bounds__(C::NT) void match_fft_kernel(MatchJob job0, const M
 
 template <class C>
 static int launch_group(const MatchJob& job0, const MatchJob* jobs, const int2* tasks, int n_tasks, int n_blocks,
-                        const SplitArgs& sp, int, hipStream_t st) {
+                        const SplitArgs& sp, bool, hipStream_t st) {
   hipLaunchKernelGGL(match_fft_kernel<C>, dim3(n_blocks), dim3(C::NT), C::LDS, st, job0, jobs, tasks, n_tasks, sp);
   return hipGetLastError() == hipSuccess ? 0 : -2;
 }
@@ -493,24 +493,11 @@ constexpr int resident() {
   return std::max(1, std::min((int)(kMaxLds / W::LDS), 4 * W::WPE / W::NW));
 }
 
-// W (spread) where the whole launch is resident at once with it, else C (full):
-// the points then have the CUs to themselves, and more waves to a point is what is
-// left.  Full against spread workgroups, us at 256 / 272 / 400 points:
-//   P = 80    53 against 50   60 / 65     80 / 92
-//   P = 90    64         60   71 / 76     96 / 109
-//   P = 100   81         68   88 / 87    119 / 123
-//   P = 120   94         80  105 / 103   141 / 148
-// With two W to a CU (P = 60 to 72), where full workgroups of half its waves are
-// four to a CU, a whole round and a split rest are still shorter with W while that
-// rest is small: P = 64 at 520, 600 and 700 points 77 / 59, 80 / 69 and 97 / 83,
-// but at 768 points 83 / 87; P = 72 at 768 points 85 / 95.
+// Full or spread workgroups (takes_spread in split_plan.hpp).
 template <class C, class W, bool WIDE>
 static int launch_lane(const MatchJob& job0, const MatchJob* jobs, const int2* tasks, int n_tasks, int n_blocks,
-                       const SplitArgs& sp, int num_cus, hipStream_t st) {
-  const int slots = resident<W>() * num_cus;
-  const bool round_and_rest = resident<W>() > 1 && 2 * C::NT >= W::NT && sp.n_whole == slots &&
-                              5 * (n_tasks - slots) <= 2 * slots;
-  if (n_blocks <= slots || round_and_rest)
+                       const SplitArgs& sp, bool spread, hipStream_t st) {
+  if (spread)
     hipLaunchKernelGGL((match_lane_kernel<W, WIDE>), dim3(n_blocks), dim3(W::NT), W::LDS, st, job0, jobs, tasks, n_tasks, sp);
   else
     hipLaunchKernelGGL((match_lane_kernel<C, WIDE>), dim3(n_blocks), dim3(C::NT), C::LDS, st, job0, jobs, tasks, n_tasks, sp);
@@ -519,12 +506,13 @@ static int launch_lane(const MatchJob& job0, const MatchJob* jobs, const int2* t
 
 template <class C>
 static constexpr FftPlan group_plan() {
-  return FftPlan{C::P, C::R1, C::R2, C::NT, C::LDS, C::P, false, launch_group<C>};
+  return FftPlan{C::P, C::R1, C::R2, C::NT, C::LDS, C::P, false, 0, false, launch_group<C>};
 }
 // WIDE: for images wider than kLaneMaxWidth.
 template <class C, class W, bool WIDE>
 static constexpr FftPlan lane_plan() {
-  return FftPlan{C::P, C::R1, C::R2, C::NT, C::LDS, C::P == 144 ? 134 : C::P, true, launch_lane<C, W, WIDE>};
+  return FftPlan{C::P, C::R1, C::R2, C::NT, C::LDS, C::P == 144 ? 134 : C::P, true, resident<W>(), 2 * C::NT >= W::NT,
+                 launch_lane<C, W, WIDE>};
 }
 
 #define CFOG_NO_PLAN(...)
@@ -689,9 +677,9 @@ int init_kernel_attributes() {
 }
 
 int launch_match_fft(const FftPlan* plan, const MatchJob& job0, const MatchJob* d_jobs, const int2* d_tasks,
-                     int n_tasks, int n_blocks, const SplitArgs& sp, int num_cus, hipStream_t st) {
+                     int n_tasks, int n_blocks, const SplitArgs& sp, bool spread, hipStream_t st) {
   if (n_tasks <= 0) return 0;
-  return plan->launch(job0, d_jobs, d_tasks, n_tasks, n_blocks, sp, num_cus, st);
+  return plan->launch(job0, d_jobs, d_tasks, n_tasks, n_blocks, sp, spread, st);
 }
 
 }  // namespace cfog

@@ -49,4 +49,23 @@ inline SplitChoice plan_split_choice(int P, int n, int S, int m, int Nmax, int W
   return sp;
 }
 
+// Whether a launch of the lane layout takes its plan's spread workgroups, W, of
+// which `per_cu` share a CU: n_blocks workgroups for n tasks, of which n_whole
+// run unsplit.  rest: the plan's full workgroups have at least half of W's waves.
+// W where the whole launch is resident at once with it, else the full ones: the
+// points then have the CUs to themselves, and more waves to a point is what is
+// left.  Full against spread workgroups, us at 256 / 272 / 400 points:
+//   P = 80    53 against 50   60 / 65     80 / 92
+//   P = 90    64         60   71 / 76     96 / 109
+//   P = 100   81         68   88 / 87    119 / 123
+//   P = 120   94         80  105 / 103   141 / 148
+// With two W to a CU (P = 60 to 72), where full workgroups of half its waves are
+// four to a CU, a whole round and a split rest are still shorter with W while that
+// rest is small: P = 64 at 520, 600 and 700 points 77 / 59, 80 / 69 and 97 / 83,
+// but at 768 points 83 / 87; P = 72 at 768 points 85 / 95.
+inline bool takes_spread(int n, int n_whole, int n_blocks, int num_cus, int per_cu, bool rest) {
+  const int slots = per_cu * num_cus;
+  return n_blocks <= slots || (rest && per_cu > 1 && n_whole == slots && 5 * (n - slots) <= 2 * slots);
+}
+
 }  // namespace cfog
