@@ -26,6 +26,7 @@
 #include <math.h>
 #include <limits.h>
 #include "cfog.h"
+#include "root.hpp"
 
 namespace cfog {
 
@@ -371,30 +372,6 @@ __device__ __forceinline__ double lane_value(double v, int i) {
                                           (uint32_t)__builtin_amdgcn_readlane((int)x.hi, i)});
 }
 
-// The square root of a normal d > 0 and the reciprocal r of that root, from the
-// hardware's estimate of 1 / sqrt(d) by Goldschmidt's iteration and a final
-// correction by the residual d - g g; then quotients by the root as
-// Markstein's: q = t r corrected by its residual.  Shorter chains than a square
-// root and a division of their own, which check for ranges that a pivot of
-// the normal matrix cannot have, with the same roundings.
-__device__ __forceinline__ double sqrt_rcp(double d, double& r) {
-  const double y = __builtin_amdgcn_rsq(d);
-  double g = d * y, h = 0.5 * y;
-  const double e = fma(-h, g, 0.5);
-  g = fma(g, e, g);
-  h = fma(h, e, h);
-  g = fma(fma(-g, g, d), h, g);
-  g = fma(fma(-g, g, d), h, g);
-  r = h + h;
-  r = fma(fma(-g, r, 1.0), r, r);
-  r = fma(fma(-g, r, 1.0), r, r);
-  return g;
-}
-__device__ __forceinline__ double quotient(double t, double g, double r) {
-  const double q = t * r;
-  return fma(fma(-g, q, t), r, q);
-}
-
 __global__ __launch_bounds__(RS_NT, 1) void reject_small_kernel(const float2* __restrict__ src,
                                                                 const float2* __restrict__ dst, int n, float thr,
                                                                 unsigned char* keep, cfog_reject_result* out) {
@@ -533,7 +510,8 @@ __global__ __launch_bounds__(RS_NT, 1) void reject_small_kernel(const float2* __
     for (int j = 0; j < RJ_T; ++j) {
       const double d = lane_value(L[j], j);
       ok = ok && d > 0.0;
-      diag[j] = sqrt_rcp(d > 0.0 ? d : 1.0, rcp[j]);
+      const double p = d > 0.0 ? d : 1.0;
+      diag[j] = sqrt_rcp(p, __builtin_amdgcn_rsq(p), rcp[j]);
       L[j] = quotient(L[j], diag[j], rcp[j]);
 #pragma unroll
       for (int k = j + 1; k < RJ_T; ++k) L[k] -= L[j] * lane_value(L[j], k);
