@@ -11,8 +11,8 @@
 // tile-local prefixes, which kernel 3 reads again, are cached ones (two
 // 2048^2 images: 116.1 -> 113.7 us).
 //
-// Kernel 1 (cfog_extract_kernel<R, M>) produces a 64 x 32 output tile for all
-// m channels:
+// Kernel 1 (cfog_extract_kernel<R, M, S1, CG>) produces a 128 x 16 output tile for
+// all m channels:
 //   A. stage the image tile plus an (R+1)-pixel halo in LDS (clamp-to-edge);
 //   B. gx, gy by [-1,0,1] (the filters given after Eq. 2) at every pixel of
 //      the tile + R halo, at the clamped pixel (which is what clamp-to-edge
@@ -31,14 +31,15 @@
 //   D. the tile-local 2-D inclusive prefix L of Q (row scan across the 64 lanes
 //      of a wave, column scan down the tile), written into the SAT buffer,
 //      plus the tile's right column and bottom row into a small workspace.
-// LDS holds the channel plane and one row-pass buffer (the image tile shares
-// its storage; the wave carries of D reuse the dead channel plane), about
-// 22 KB at R = 3; four 512-thread workgroups (32 waves) share a CU; two
-// barriers per channel.  (Measured on 2048^2 images: 64 x 16 tiles of 256
-// threads, eight per CU, 4% slower; with two row-pass buffers, one barrier per
-// channel and six per CU, 7-8% slower.  Forming g_k from two gradient planes
-// inside the horizontal pass computed each value three times.)
-
+// LDS holds the channel plane, two channels' outputs and one row-pass buffer (the
+// image tile shares the first's storage; the wave carries of D reuse the dead
+// channel plane), 39.6 KB at R = 3; four 512-thread workgroups (32 waves) share a
+// CU; two barriers per channel.  (Measured on 2048^2 images with tiles of 64
+// columns: 16 rows of 256 threads, eight per CU, 4% slower than 32 rows of 512;
+// with two row-pass buffers, one barrier per channel and six per CU, 7-8% slower.
+// Forming g_k from two gradient planes inside the horizontal pass computed each
+// value three times.)
+//
 // Global SAT from tile-local prefixes: for a tile (i, j) with origin (y0, x0),
 //   SAT(y, x) = L(y, x) + sum_{j'<j} Rc_{i,j'}(y) + sum_{i'<i} Bt_{i',j}(x)
 //             + sum_{i'<i, j'<j} total(i', j')
@@ -201,8 +202,9 @@ struct ExTile {
 // it from the arguments.  S1: scheme 1 instead of Eq. 2, fixed at compile
 // time so that the per-pixel channel value carries no branch.  CG: channels
 // that go through a pass between two barriers, each with planes of its own.
-// Several are for launches that leave each tile its CU, where the passes'
-// latencies and barriers X
+// Several (three) are for launches that leave each tile its CU, where the passes'
+// latencies and barriers are most of the time and the tile has all of LDS: 333 x
+// 251, nine channels, 12.3 -> 11.5 us.  With two tiles to a CU it is slower.
 template <int R, int M, bool S1, int CG>
 __global__ __launch_bounds__(EX_NT) __attribute__((amdgpu_waves_per_eu(M > 0 && CG == 1 ? 8 : 1, 8))) void cfog_extract_kernel(ExtractArgs a) {
   using T = ExTile<R, CG>;
@@ -360,7 +362,7 @@ __global__ __launch_bounds__(EX_NT) __attribute__((amdgpu_waves_per_eu(M > 0 && 
   // C. per channel: the horizontal Gaussian of the oriented gradient (the
   // channel values computed on the fly from the gradient planes), then the
   // vertical pass, which leaves the spatially smoothed channel Gs_k for the
-  // rows [4 (tid/64), +4) of column tid % 64 in registers.  A barrier after
+  // rows [4 (tid / 128), + 4) of column tid % 128 in registers.  A barrier after
   // each pass: the next channel's row pass rewrites the buffer.
   const int oc = tid % TX, orow = (tid / TX) * EX_RUN;
   const int gxx = x0 + oc;

@@ -23,14 +23,16 @@
 // ahead: from memory to registers, rounded into a pair of rows of LDS of its own.
 // The template (bf16, with 15 zero rows above and below) is shared; where two
 // fit LDS, the next channel's is brought in a row at a time meanwhile, so that
-// loads and MFMAs overlap and a channel has one barrier.
+// loads and MFMAs overlap and a channel has one barrier (direct_launch says where
+// one is taken).
 //
-// What bounds it: the matrix cores.  N = 128, r = 32 (65 offsets in 80) executes
-// 1.1 PFLOP/s at the 2.0 GHz that the clock then has, of which 0.6 are not
-// padding; a large library product reaches 1.24.  1000 points: 2407 us where
-// each channel's rows were staged before its MFMAs and all fragments read per
-// chunk; 2195 with shared fragments, the next chunk's read ahead; 1995 without
-// the moves and address arithmetic of that; 1884 with rows brought in as now.
+// What bounds it: the matrix cores.  N = 128, r = 32 (65 offsets in 80), 1,000
+// points: 1.61 ms, 2.18 where each channel's rows were staged before its MFMAs and
+// all fragments read per chunk.  That executes 1.28 PFLOP/s at the 2.0 to 2.1 GHz
+// that the clock then has, of which 0.77 are not padding; a large library product
+// reaches 1.24.  (Steps, in a loop of launches of their own: 2407 us staged; 2195
+// with shared fragments, the next chunk's read ahead; 1995 without the moves and
+// address arithmetic of that; 1884 with rows brought in by their waves.)
 // A body without tests for rows that meet all blocks spills and is slower.
 // Precision: inputs are rounded to BF16 (round to nearest, 8 significant bits,
 // unit roundoff u = 2^-8), products are exact in FP32, so
@@ -69,7 +71,7 @@ struct DirectGeom {
   int TLD;    // template row stride in dwords, NP/2 + 4: an odd multiple of 4, so the
               // 16 rows one B fragment reads start in 16 different 4-bank groups
   int SLD;    // dwords of a search row (NP + 16 nblk + 2 bf16: the fragment over-read)
-  int tbufs;  // template buffers: 2 where they fit, else 1
+  int tbufs;  // template buffers
   size_t t_bytes, lds;
 };
 
@@ -457,7 +459,9 @@ int launch_match_direct(const cfog_job* jobs, int n_jobs, int m, int obj, void*,
 bool direct_supported(int N, int r) {
   if (N < 1 || r < 0 || N > kMaxSide || r > kMaxSide) return false;
   const DirectGeom g = direct_geom(N, r);
-  // the sizes that are taken: those whose template and search window fit LDS
+  // the sizes that are taken: those whose template and whole search window fit LDS.
+  // The kernel no longer holds a window; the limit is kept so that the sizes taken
+  // stay the same.
   return g.nblk <= D_NB && g.lds <= kMaxLds && g.t_bytes + (size_t)g.Ws * g.SLD * 4 <= kMaxLds;
 }
 

@@ -24,19 +24,24 @@
 //
 // What bounds it: the vector units, through the phases' ends.  At P = 144
 // (N = 100, r = 20) a point issues 165K wave instructions where the group
-// layout issues 211K, with the vector units busy 68% of the time; a phase's
-// own instructions fill 75-80% of it, the rest is LDS latency at its start and
-// the barrier at its end.  Against the group layout it has no separation of
-// packed real rows (24 LDS permutes and as many extra LDS writes per row
-// pair), no 48-byte pieces of rows to load, no idle lanes in the groups and
-// half the plane, so that up to P = 120 two workgroups share a CU: 449 us per
-// 1,024 points against 541 at P = 144, 294 against 405 at P = 120, 107 against
-// 261 at P = 72 (the plan table in match_fft.hip has every size).
+// layout issued 211K, with the vector units busy 53% of the time and LDS 37%; the
+// rest is latency at each phase's start and the barrier at its end.  Against the
+// group layout it has no separation of packed real rows (24 LDS permutes and as
+// many extra LDS writes per row pair), no 48-byte pieces of rows to load, no idle
+// lanes in the groups and half the plane, so that up to P = 120 two workgroups
+// share a CU: 400 us per 1,024 points against 494 at P = 144, 246 against 362 at
+// P = 120, 89 against 249 at P = 72 (the plan table in match_fft.hip has every
+// size).  It loses by up to 4% where a template is far smaller than its window and
+// the points are fewer than CUs (N = 20, r = 26 and 30), as the x stages transform
+// the template's zero columns too.
 // Measured and not taken: two channels as one complex signal over all ky
 // (twice the plane: at P >= 144 in two classes of ky with every volume row
 // read twice; 642 us at P = 144, 1206 at P = 192); loads of two or three
 // y1 items in flight together (447 -> 450-485 us); touching the next set's
-// cache lines a phase ahead (slower at every size).
+// cache lines a phase ahead (slower at every size); no zero columns written and
+// x1 testing its columns instead (4% slower at P = 72 and 100, 8 to 10% at P = 60,
+// 80, 96 and 144, 27% at P = 192); the zero columns written four at a time (up to
+// 4% slower).
 #pragma once
 #include <hip/hip_runtime.h>
 #include "dft.hpp"
